@@ -460,33 +460,33 @@ constexpr int kCandMax = 0xFFFF - 2 * kBucket;
 // the k-1 nearest plus a boundary bin of up to 16, with slack enough that a
 // walk rarely has to drop the entries above its cut (measured faster than a
 // tighter list at higher occupancy).
-template <int KP2>
 struct QueryLds {
-    static constexpr int kList = KP2 > 32 ? 80 : 64;
+    static constexpr int kList = 64;
     static constexpr int kWords = kNB / 2 + kList;
 };
 constexpr uint32_t kSlotMask = (1u << 26) - 1;  // list word: bin << 26 | slot
-static_assert(QueryLds<32>::kList % 8 == 0 && QueryLds<64>::kList % 8 == 0, "the list is read 8 words at a time");
+static_assert(QueryLds::kList % 8 == 0, "the list is read 8 words at a time");
 static_assert(kC1 <= kNB / 2, "the boundary list reuses the counter words");
 static_assert(kNB <= 32, "list words keep the bin in 5 bits");
 
-template <bool PER, int KP2>
+template <bool PER>
 struct KnnQuery {
     using Args = KnnArgs;
     static constexpr int kThreads = kQBlock;
     static __device__ __forceinline__ void body(const Args& A, Blk B);
 };
 
-template <bool PER, int KP2>
+template <bool PER>
 __global__ __launch_bounds__(kQBlock) void k_knn_query(KnnArgs A)
 {
-    KnnQuery<PER, KP2>::body(A, Blk{int64_t(blockIdx.x), int64_t(gridDim.x)});
+    KnnQuery<PER>::body(A, Blk{int64_t(blockIdx.x), int64_t(gridDim.x)});
 }
 
-template <bool PER, int KP2>
-__device__ __forceinline__ void KnnQuery<PER, KP2>::body(const Args& A, Blk B)
+template <bool PER>
+__device__ __forceinline__ void KnnQuery<PER>::body(const Args& A, Blk B)
 {
-    using QL = QueryLds<KP2>;
+    using QL = QueryLds;
+    constexpr int KP2 = 32;  // row registers
     __shared__ uint32_t s_lds[QL::kWords * kQBlock];
     const int tid = threadIdx.x;
     int64_t q64;
@@ -1051,7 +1051,9 @@ int launch_knn(const gd_problem* p, const gd_neighbors* nb, void* ws, const Layo
     launch_fill_i32(A.stats, 8 * n, 0, st);
 #endif
     prof_mark(GD_PROF_KNN_QUERY, 0, st);
-    if (p->k > 64) {  // one wavefront per query: the per-lane search's lists hold at most 64
+    // one wavefront per query beyond the shared lists' 33 (at k = 48 on a
+    // 200K disk 0.86 ms per interval with the per-lane walk, 0.77 with this)
+    if (p->k > 33) {
         launch_knn_wave(A, per, nullptr, nullptr, n, st);
         prof_mark(GD_PROF_KNN_QUERY, 1, st);
         return 0;
@@ -1059,7 +1061,7 @@ int launch_knn(const gd_problem* p, const gd_neighbors* nb, void* ws, const Layo
     const dim3 grid(unsigned((n + kQBlock - 1) / kQBlock));
     const bool cleared = L.levels > 1;  // the tree's first pass cleared the counters
     if (!cleared) launch_fill_i32(A.xq, kXcd, 0, st);
-    if (p->k <= 33 && kTileSearch) {
+    if (kTileSearch) {
         // shared candidate tiles first; the queries they cannot complete go
         // through the per-lane search
         int32_t* fb0 = at<int32_t>(ws, L.keys1);  // keys1 and vals1 (n entries each): free after the sort
@@ -1073,19 +1075,14 @@ int launch_knn(const gd_problem* p, const gd_neighbors* nb, void* ws, const Layo
         A.list = fb0;
         A.list_n = hw->knn_fb_n;
     }
-    if (p->k <= 33) {
-        if (per) hipLaunchKernelGGL((k_knn_query<true, 32>), grid, dim3(kQBlock), 0, st, A);
-        else hipLaunchKernelGGL((k_knn_query<false, 32>), grid, dim3(kQBlock), 0, st, A);
-    } else {
-        if (per) hipLaunchKernelGGL((k_knn_query<true, 64>), grid, dim3(kQBlock), 0, st, A);
-        else hipLaunchKernelGGL((k_knn_query<false, 64>), grid, dim3(kQBlock), 0, st, A);
-    }
+    if (per) hipLaunchKernelGGL(k_knn_query<true>, grid, dim3(kQBlock), 0, st, A);
+    else hipLaunchKernelGGL(k_knn_query<false>, grid, dim3(kQBlock), 0, st, A);
     prof_mark(GD_PROF_KNN_QUERY, 1, st);
     return 0;
 }
 
 // The search of every run as stages of one interval: the bucket boxes, each
-// tree level over the runs that have it, then the queries: k > 64 one
+// tree level over the runs that have it, then the queries: k > 33 one
 // wavefront per query; k <= 33 (with tiles) the tile search, its fallback
 // wavefronts and the per-lane search of the first list; otherwise the
 // per-lane search over every query.  Runs are grouped by periodicity and
@@ -1117,19 +1114,19 @@ void many_knn(ManyBuilder& B, const std::vector<ManyRun>& R)
         }
         B.add<LevelBoxes>(tab, nb);
     }
-    // query groups: (periodic, class) with class 0: k <= 33, 1: 34..64, 2: > 64
+    // query groups: (periodic, class) with class 0: k <= 33, 1: beyond
     for (int per = 0; per < 2; ++per) {
-        for (int cls = 0; cls < 3; ++cls) {
+        for (int cls = 0; cls < 2; ++cls) {
             std::vector<int64_t> mine(nr, 0);
             bool any = false;
             for (size_t r = 0; r < nr; ++r) {
                 const int k = R[r].p.k;
-                const int c = k <= 33 ? 0 : (k <= 64 ? 1 : 2);
+                const int c = k <= 33 ? 0 : 1;
                 mine[r] = (int(S[r].per) == per && c == cls) ? 1 : 0;
                 any = any || mine[r];
             }
             if (!any) continue;
-            if (cls == 2) {
+            if (cls == 1) {
                 std::vector<WaveArgs> tab(nr);
                 for (size_t r = 0; r < nr; ++r) {
                     tab[r] = WaveArgs{S[r].A, nullptr, nullptr};
@@ -1138,7 +1135,7 @@ void many_knn(ManyBuilder& B, const std::vector<ManyRun>& R)
                 many_add_wave(B, tab, nb, per);
                 continue;
             }
-            const bool tile = cls == 0 && B.tune.knn_tile;
+            const bool tile = B.tune.knn_tile;
             std::vector<ClearArgs> clr(nr);
             for (size_t r = 0; r < nr; ++r) {
                 WsHeader* hw = at<WsHeader>(R[r].ws, R[r].L.hdr);
@@ -1167,13 +1164,8 @@ void many_knn(ManyBuilder& B, const std::vector<ManyRun>& R)
                 many_add_wave(B, wt, fnb, per);
             }
             for (size_t r = 0; r < nr; ++r) nb[r] = mine[r] ? cdiv(R[r].p.n, kQBlock) : 0;
-            if (cls == 0) {
-                if (per) B.add<KnnQuery<true, 32>>(qa, nb);
-                else B.add<KnnQuery<false, 32>>(qa, nb);
-            } else {
-                if (per) B.add<KnnQuery<true, 64>>(qa, nb);
-                else B.add<KnnQuery<false, 64>>(qa, nb);
-            }
+            if (per) B.add<KnnQuery<true>>(qa, nb);
+            else B.add<KnnQuery<false>>(qa, nb);
         }
     }
     // the active counts, for the runs that ask for them

@@ -1,7 +1,7 @@
 // gd_knn_wave.hip -- the N_K nearest neighbours of one query per wavefront
 // (Sect. 2.5.1), exact, for any k up to kMaxK.  It serves neighbourhoods too
-// large for the per-lane search's registers and LDS lists, and the queries
-// that search hands back.
+// large for the shared-list searches' registers and LDS lists, and the
+// queries those searches hand back.
 //
 // Per query (one 64-lane wavefront):
 //   1. the search radius: the particle's distance from the previous search
@@ -9,21 +9,25 @@
 //      three windows of k consecutive Morton slots holding the query, of the
 //      window's largest d^2 (each window holds k-1 others, so that is an upper
 //      bound of the (k-1)-th d^2), capped by the maximum search scale;
-//   2. a depth-first traversal of the box tree, eight nodes at a time: each
-//      lane tests one child box against the query's sphere (the conservative
-//      single-precision test of gd_knn.hpp); passing internal children go on
-//      an LDS stack, passing buckets to a bucket buffer;
+//   2. a depth-first traversal of the box tree in Morton order, kPop nodes at
+//      a time: each lane tests child boxes against the query's sphere (the
+//      conservative single-precision test of gd_knn.hpp); passing internal
+//      children go on an LDS stack, the leftmost on top, passing buckets to a
+//      bucket buffer.  Levels grow from the top of the stack down, so the
+//      level-1 nodes of a batch lie left of its other nodes and the buckets
+//      come out in ascending order;
 //   3. the buffered buckets' slots are evaluated four per lane: every other
 //      at or below the cut (d^2, slot) <= (R2, J) joins an LDS list of
-//      (d^2, slot) pairs, compacted across the wavefront.  When the list
-//      would overflow, it is sorted and cut to its k-1 smallest pairs, and the
-//      cut moves to the last of them (so equal distances beyond it are
-//      decided by slot, and the radius only shrinks, which keeps the pruning
-//      of step 2 exact);
+//      (d^2, slot) pairs, compacted across the wavefront in ascending slot
+//      order.  When the list would overflow, it is cut in place to its k-1
+//      smallest pairs, and the cut moves to the last of them (so equal
+//      distances beyond it are decided by slot, and the radius only shrinks,
+//      which keeps the pruning of step 2 exact);
 //   4. if the previous distance held fewer than k-1 others, the query runs
 //      again on the window bound;
-//   5. the list is sorted by (d^2, slot), its first min(n, k-1) pairs are
-//      sorted by slot and written as the row.
+//   5. the (k-1)-th smallest pair is selected (select_pair) and the pairs up
+//      to it are written as the row: the list is in slot order already, so
+//      nothing is sorted.
 // d^2 is (dx*dx + dy*dy) + dz*dz with every operation rounded on its own, and
 // non-negative doubles order as their bit patterns, so the selection is the
 // k-1 smallest (d^2, slot) exactly.
@@ -33,83 +37,158 @@
 
 namespace gd {
 
-constexpr int kWList = 512;    // (d^2, slot) pairs a query keeps; >= (kMaxK - 1) + 4 * kWave
-constexpr int kWStack = 1024;  // traversal stack: at most 64 children per level wait on it
-constexpr int kWBuf = 128;     // buckets waiting for evaluation: flushed from 64 on
-static_assert(kWList >= (kMaxK - 1) + 4 * kWave, "a flush after a cut must fit the list");
-static_assert(kWStack >= kMaxTreeLevels * kWave, "the stack holds one expansion per level");
+constexpr int kPop = 8;          // nodes expanded at a time, eight lanes each
+constexpr int kWBuf = 128;       // buckets waiting for evaluation: flushed from 64 on
+constexpr int kSelBins = 256;    // bins of the selection's distance histogram
 
+// A level's nodes join the stack only when fewer than kPop nodes of lower
+// levels were on it (a batch takes them all), so each level has at most
+// kPop * kFan nodes waiting.
+constexpr int kWStack = (kMaxTreeLevels - 1) * kPop * kFan;
+
+// NL: (d^2, slot) pairs a query keeps
+template <int NL>
 struct WaveLds {
-    uint64_t key[kWList];   // d^2 as its bit pattern
-    int32_t slot[kWList];
+    uint64_t key[NL];        // d^2 as its bit pattern
+    int32_t slot[NL];        // ascending
     int32_t stack[kWStack];  // node: level << 27 | index
-    int32_t buf[kWBuf];      // bucket indices
+    int32_t buf[kWBuf];      // bucket indices, ascending
+    uint32_t hist[kSelBins];
+    int32_t bnd[kWave];      // list places of the boundary bin's pairs
 };
 
-__device__ inline bool pair_less(uint64_t ka, int32_t sa, uint64_t kb, int32_t sb)
-{
-    return ka < kb || (ka == kb && sa < sb);
-}
-
-// Ascending bitonic sort of (key, slot) pairs [0, size) in LDS, size a power
-// of two in [64, kWList]; one wavefront.
-__device__ inline void wave_sort_pairs(uint64_t* key, int32_t* slot, int size, int lane)
-{
-    for (int len = 2; len <= size; len <<= 1) {
-        for (int stride = len >> 1; stride > 0; stride >>= 1) {
-            for (int i = lane; i < size; i += kWave) {
-                const int j = i ^ stride;
-                if (j > i) {
-                    const uint64_t ki = key[i], kj = key[j];
-                    const int32_t si = slot[i], sj = slot[j];
-                    const bool up = (i & len) == 0;
-                    const bool swap = up ? pair_less(kj, sj, ki, si) : pair_less(ki, si, kj, sj);
-                    if (swap) {
-                        key[i] = kj;
-                        key[j] = ki;
-                        slot[i] = sj;
-                        slot[j] = si;
-                    }
-                }
-            }
-            __syncthreads();
-        }
-    }
-}
-
-// Ascending bitonic sort of int32 [0, size) in LDS, size a power of two.
-__device__ inline void wave_sort_i32(int32_t* v, int size, int lane)
-{
-    for (int len = 2; len <= size; len <<= 1) {
-        for (int stride = len >> 1; stride > 0; stride >>= 1) {
-            for (int i = lane; i < size; i += kWave) {
-                const int j = i ^ stride;
-                if (j > i) {
-                    const int32_t a = v[i], b = v[j];
-                    const bool up = (i & len) == 0;
-                    if (up ? (b < a) : (a < b)) {
-                        v[i] = b;
-                        v[j] = a;
-                    }
-                }
-            }
-            __syncthreads();
-        }
-    }
-}
-
-__device__ inline int pow2_at_least(int n, int lo)
-{
-    int s = lo;
-    while (s < n) s <<= 1;
-    return s;
-}
-
 __device__ inline uint64_t d2_key(double d2) { return uint64_t(__double_as_longlong(d2)); }
+__device__ inline uint64_t lanes_below(int lane) { return (uint64_t(1) << lane) - 1; }
 
-template <bool PER>
-__device__ void knn_wave_query(const KnnArgs& A, int q, WaveLds& L, int lane)
+__device__ inline uint64_t readlane_u64(uint64_t x, int l)
 {
+    return (uint64_t(uint32_t(__builtin_amdgcn_readlane(int(x >> 32), l))) << 32) |
+           uint32_t(__builtin_amdgcn_readlane(int(x), l));
+}
+
+// The need-th smallest (key, slot) of the list's n >= need >= 1 pairs, whose
+// keys are d^2 <= R2: a histogram of d^2, linear over [0, R2], finds the bin
+// that holds it; that bin's pairs (about n / kSelBins of them) are ranked one
+// against all.  A bin of more than 64 pairs (many equal distances) is
+// resolved by bisection on the key's bits instead, and equal keys by their
+// order in the list, which is the slot order.  Sorting
+// the list in LDS instead, 45 bitonic stages for 512 pairs and then the slots,
+// was most of the search: on a disk of 131,072 particles at k = 256 an
+// interval took 4.21 ms with the sorts and takes 1.02 ms without.
+template <int NL>
+__device__ __forceinline__ void select_pair(WaveLds<NL>& L, int n, int need, double R2, int lane, uint64_t& T, int32_t& J)
+{
+    constexpr int NP = NL / kWave;
+    constexpr int NB = kSelBins / kWave;
+    uint64_t key[NP];
+#pragma unroll
+    for (int b = 0; b < NB; ++b) L.hist[b * kWave + lane] = 0;
+#pragma unroll
+    for (int p = 0; p < NP; ++p) key[p] = p * kWave + lane < n ? L.key[p * kWave + lane] : ~uint64_t(0);
+    const double sc = R2 > 0.0 ? double(kSelBins) / R2 : 0.0;
+    const bool lin = sc > 0.0 && sc < INFINITY;
+    auto bin_of_key = [&](uint64_t kk) {
+        if (!lin) return 0;
+        const double t = __longlong_as_double((long long)kk) * sc;
+        return t < double(kSelBins) ? int(t) : kSelBins - 1;
+    };
+    __syncthreads();
+#pragma unroll
+    for (int p = 0; p < NP; ++p)
+        if (p * kWave < n && p * kWave + lane < n) atomicAdd(&L.hist[bin_of_key(key[p])], 1u);
+    __syncthreads();
+    // lane l's bins: NB l .. NB l + NB - 1
+    int own[NB], sum = 0;
+#pragma unroll
+    for (int b = 0; b < NB; ++b) {
+        own[b] = int(L.hist[lane * NB + b]);
+        sum += own[b];
+    }
+    int incl = sum;
+#pragma unroll
+    for (int o = 1; o < kWave; o <<= 1) {
+        const int y = __shfl_up(incl, o, kWave);
+        if (lane >= o) incl += y;
+    }
+    const uint64_t reach = __ballot(incl >= need);
+    const int lsel = __ffsll((unsigned long long)reach) - 1;  // (n >= need: some lane reaches it)
+    int bsel = 0, before = incl - sum, inbin = 0;
+    bool found = false;
+#pragma unroll
+    for (int b = 0; b < NB; ++b) {
+        if (!found && before + own[b] >= need) {
+            found = true;
+            bsel = lane * NB + b;
+            inbin = own[b];
+        }
+        if (!found) before += own[b];
+    }
+    bsel = __builtin_amdgcn_readlane(bsel, lsel);
+    before = __builtin_amdgcn_readlane(before, lsel);
+    inbin = __builtin_amdgcn_readlane(inbin, lsel);
+    if (inbin <= kWave) {
+        const int want = need - before - 1;  // rank of the pair sought within the bin
+        int nb = 0;
+#pragma unroll
+        for (int p = 0; p < NP; ++p) {
+            if (p * kWave < n) {
+                const bool in = p * kWave + lane < n && bin_of_key(key[p]) == bsel;
+                const uint64_t bal = __ballot(in);
+                if (in) L.bnd[nb + int(__popcll(bal & lanes_below(lane)))] = p * kWave + lane;
+                nb += int(__popcll(bal));
+            }
+        }
+        __syncthreads();
+        const bool have = lane < nb;
+        const int at = have ? L.bnd[lane] : 0;
+        const uint64_t kk = have ? L.key[at] : ~uint64_t(0);
+        int rank = 0;  // equal keys: the list order (lane order) decides
+        for (int f = 0; f < nb; ++f) {
+            const uint64_t kf = readlane_u64(kk, f);
+            rank += (kf < kk) | ((kf == kk) & (f < lane));
+        }
+        const uint64_t hit = __ballot(have && rank == want);
+        const int l = __ffsll((unsigned long long)hit) - 1;
+        T = readlane_u64(kk, l);
+        J = L.slot[__builtin_amdgcn_readlane(at, l)];
+        __syncthreads();
+        return;
+    }
+    // the largest T with fewer than `need` keys below it
+    uint64_t t = 0;
+    int less = 0;
+    for (int bit = 62; bit >= 0; --bit) {
+        const uint64_t c = t | (uint64_t(1) << bit);
+        int cnt = 0;
+#pragma unroll
+        for (int p = 0; p < NP; ++p) cnt += int(__popcll(__ballot(key[p] < c)));
+        if (cnt < need) {
+            t = c;
+            less = cnt;
+        }
+    }
+    if (t == 0) less = 0;
+    T = t;
+    int left = need - less;  // the pair sought is the left-th of those with key T, in list order
+    J = -1;
+#pragma unroll
+    for (int p = 0; p < NP; ++p) {
+        const uint64_t bal = __ballot(p * kWave + lane < n && key[p] == t);
+        const int c = int(__popcll(bal));
+        if (left > 0 && left <= c) {
+            const bool it = ((bal >> lane) & 1u) && int(__popcll(bal & lanes_below(lane))) == left - 1;
+            const uint64_t hit = __ballot(it);
+            J = L.slot[p * kWave + __ffsll((unsigned long long)hit) - 1];
+        }
+        left -= c;
+    }
+    __syncthreads();
+}
+
+template <bool PER, int NL>
+__device__ __forceinline__ void knn_wave_query(const KnnArgs& A, int q, WaveLds<NL>& L, int lane)
+{
+    constexpr int NP = NL / kWave;
     const int na = A.h->n_active;
     const int k = A.k;
     const int need = k - 1;
@@ -191,26 +270,42 @@ __device__ void knn_wave_query(const KnnArgs& A, int q, WaveLds& L, int lane)
         n = 0;
         float R2f = r2f(R2);
         int sp = 0, nbuf = 0;
-        // cut the list to its k-1 smallest pairs; the cut moves to the last
-        auto cut_list = [&]() {
-            const int size = pow2_at_least(n, kWave);
-            for (int e = n + lane; e < size; e += kWave) {
-                L.key[e] = ~uint64_t(0);
-                L.slot[e] = INT32_MAX;
+        // cut the list to its k-1 smallest pairs, kept in order; the cut
+        // moves to the last of them (n > need here)
+        auto cut_list = [&]() __attribute__((always_inline)) {
+            uint64_t T;
+            int32_t J;
+            __syncthreads();
+            select_pair<NL>(L, n, need, R2, lane, T, J);
+            R2 = __longlong_as_double((long long)T);
+            Jc = J;
+            R2f = r2f(R2);
+            uint64_t key[NP];
+            int32_t slot[NP];
+#pragma unroll
+            for (int p = 0; p < NP; ++p) {
+                const bool in = p * kWave + lane < n;
+                key[p] = in ? L.key[p * kWave + lane] : ~uint64_t(0);
+                slot[p] = in ? L.slot[p * kWave + lane] : INT32_MAX;
             }
             __syncthreads();
-            wave_sort_pairs(L.key, L.slot, size, lane);
-            const int keep = need < n ? need : n;
-            if (keep > 0) {
-                R2 = __longlong_as_double((long long)L.key[keep - 1]);
-                Jc = L.slot[keep - 1];
-                R2f = r2f(R2);
+            int kept = 0;
+#pragma unroll
+            for (int p = 0; p < NP; ++p) {
+                const bool keep = key[p] < T || (key[p] == T && slot[p] <= J);
+                const uint64_t bal = __ballot(keep);
+                if (keep) {
+                    const int at = kept + int(__popcll(bal & lanes_below(lane)));
+                    L.key[at] = key[p];
+                    L.slot[at] = slot[p];
+                }
+                kept += int(__popcll(bal));
             }
-            n = keep;
+            n = kept;
             __syncthreads();
         };
-        // evaluate the buffered buckets, 64 at a time, four slots per lane
-        auto flush = [&]() {
+        // evaluate the buffered buckets in order, 64 at a time, four slots per lane
+        auto flush = [&]() __attribute__((always_inline)) {
             for (int b0 = 0; b0 < nbuf; b0 += kWave) {
                 const int nb = nbuf - b0 < kWave ? nbuf - b0 : kWave;
                 double d2[4];
@@ -222,13 +317,19 @@ __device__ void knn_wave_query(const KnnArgs& A, int q, WaveLds& L, int lane)
                     const int p = lane + kWave * t;
                     const int b = p >> 2;
                     const int j = b < nb ? L.buf[b0 + b] * kBucket + (p & 3) : -1;
-                    jj[t] = j;
                     const bool ok = j >= 0 && j < na && j != q;
-                    d2[t] = ok ? sep2_slot<PER>(A, qp, j) : INFINITY;
-                    acc[t] = ok && (d2[t] < R2 || (d2[t] == R2 && j <= Jc));
-                    total += __popcll(__ballot(acc[t]));
+                    jj[t] = ok ? j : -1;
                 }
-                if (n + total > kWList) {
+                // every lane reads a slot (a lane without one its own query)
+                // so that the four loads are in flight together
+#pragma unroll
+                for (int t = 0; t < 4; ++t) d2[t] = sep2_slot<PER>(A, qp, jj[t] >= 0 ? jj[t] : q);
+#pragma unroll
+                for (int t = 0; t < 4; ++t) {
+                    acc[t] = jj[t] >= 0 && (d2[t] < R2 || (d2[t] == R2 && jj[t] <= Jc));
+                    total += int(__popcll(__ballot(acc[t])));
+                }
+                if (n + total > NL) {
                     cut_list();
 #pragma unroll
                     for (int t = 0; t < 4; ++t)
@@ -238,7 +339,7 @@ __device__ void knn_wave_query(const KnnArgs& A, int q, WaveLds& L, int lane)
                 for (int t = 0; t < 4; ++t) {
                     const uint64_t bal = __ballot(acc[t]);
                     if (acc[t]) {
-                        const int at = n + int(__popcll(bal & ((uint64_t(1) << lane) - 1)));
+                        const int at = n + int(__popcll(bal & lanes_below(lane)));
                         L.key[at] = d2_key(d2[t]);
                         L.slot[at] = jj[t];
                     }
@@ -256,22 +357,23 @@ __device__ void knn_wave_query(const KnnArgs& A, int q, WaveLds& L, int lane)
             bool pass = false;
             if (valid) pass = box2f<PER>(A, qf, A.boxes[level_off(A.T, lv) + lane]) <= R2f;
             const uint64_t bal = __ballot(pass);
+            const int c = int(__popcll(bal)), at = int(__popcll(bal & lanes_below(lane)));
             if (pass) {
-                const int at = int(__popcll(bal & ((uint64_t(1) << lane) - 1)));
                 if (lv == 0) L.buf[at] = lane;
-                else L.stack[at] = (lv << 27) | lane;
+                else L.stack[c - 1 - at] = (lv << 27) | lane;
             }
-            if (lv == 0) nbuf = int(__popcll(bal));
-            else sp = int(__popcll(bal));
+            if (lv == 0) nbuf = c;
+            else sp = c;
             __syncthreads();
         }
-        while (sp > 0) {
-            const int nt = sp < kFan ? sp : kFan;
-            const int src = sp - nt;
+        for (;;) {
+            if (nbuf >= kWave || sp == 0) flush();
+            if (sp == 0) break;
+            const int nt = sp < kPop ? sp : kPop;
             const int my = lane >> 3, c = lane & 7;
-            const int32_t node = my < nt ? L.stack[src + my] : 0;
+            const int32_t node = my < nt ? L.stack[sp - 1 - my] : 0;  // the leftmost first
             __syncthreads();
-            sp = src;
+            sp -= nt;
             const int lv = node >> 27, idx = node & ((1 << 27) - 1);
             bool pass = false;
             bool leaf = false;
@@ -281,15 +383,14 @@ __device__ void knn_wave_query(const KnnArgs& A, int q, WaveLds& L, int lane)
                 leaf = lv == 1;
             }
             const uint64_t bin = __ballot(pass && !leaf), bleaf = __ballot(pass && leaf);
-            const uint64_t below = (uint64_t(1) << lane) - 1;
-            if (pass && !leaf) L.stack[sp + int(__popcll(bin & below))] = ((lv - 1) << 27) | (idx * kFan + c);
-            if (pass && leaf) L.buf[nbuf + int(__popcll(bleaf & below))] = idx * kFan + c;
-            sp += int(__popcll(bin));
+            const int ni = int(__popcll(bin));
+            if (pass && !leaf)
+                L.stack[sp + ni - 1 - int(__popcll(bin & lanes_below(lane)))] = ((lv - 1) << 27) | (idx * kFan + c);
+            if (pass && leaf) L.buf[nbuf + int(__popcll(bleaf & lanes_below(lane)))] = idx * kFan + c;
+            sp += ni;
             nbuf += int(__popcll(bleaf));
             __syncthreads();
-            if (nbuf >= kWave) flush();
         }
-        flush();
         if (use_hint && n < need && R2hint < R2cap) {
             use_hint = false;  // the previous distance held too few others: again on the bound
             R2cap = fmin(window_bound(), A.rmax2);
@@ -298,21 +399,35 @@ __device__ void knn_wave_query(const KnnArgs& A, int q, WaveLds& L, int lane)
         break;
     }
     // 5. the k-1 smallest pairs (all of them when fewer are within the cap),
-    //    then their slots in ascending order
-    const int size = pow2_at_least(n, kWave);
-    for (int e = n + lane; e < size; e += kWave) {
-        L.key[e] = ~uint64_t(0);
-        L.slot[e] = INT32_MAX;
+    //    in slot order
+    uint64_t T = ~uint64_t(0);
+    int32_t J = INT32_MAX;
+    int m = n;
+    double maxd2 = 0.0;
+    if (n > need) {
+        select_pair<NL>(L, n, need, R2, lane, T, J);
+        m = need;
     }
-    __syncthreads();
-    wave_sort_pairs(L.key, L.slot, size, lane);
-    const int m = need < n ? need : n;
-    const double maxd2 = m > 0 ? __longlong_as_double((long long)L.key[m - 1]) : 0.0;
-    const int size2 = pow2_at_least(m, kWave);
-    for (int e = m + lane; e < size2; e += kWave) L.slot[e] = INT32_MAX;
-    __syncthreads();
-    wave_sort_i32(L.slot, size2, lane);
-    for (int s = lane; s < k; s += kWave) row[s] = s == 0 ? q : (s - 1 < m ? L.slot[s - 1] : -1);
+    int at = 0;
+    if (lane == 0) row[0] = q;
+#pragma unroll
+    for (int p = 0; p < NP; ++p) {
+        if (p * kWave < n) {
+            const bool in = p * kWave + lane < n;
+            const uint64_t kk = in ? L.key[p * kWave + lane] : ~uint64_t(0);
+            const int32_t sl = in ? L.slot[p * kWave + lane] : 0;
+            const bool keep = in && (kk < T || (kk == T && sl <= J));
+            const uint64_t bal = __ballot(keep);
+            if (keep) {
+                row[1 + at + int(__popcll(bal & lanes_below(lane)))] = sl;
+                maxd2 = fmax(maxd2, __longlong_as_double((long long)kk));
+            }
+            at += int(__popcll(bal));
+        }
+    }
+    for (int s = 1 + m + lane; s < k; s += kWave) row[s] = -1;
+    maxd2 = n > need ? __longlong_as_double((long long)T) : wave_max_d(maxd2);
+    if (at != m && lane == 0) set_status(A.ws, GD_DEV_INTERNAL);
     if (lane == 0) {
         A.cnt[q] = 1 + m;
         A.dmax[q] = m > 0 ? sqrt(maxd2) : 0.0;
@@ -322,43 +437,68 @@ __device__ void knn_wave_query(const KnnArgs& A, int q, WaveLds& L, int lane)
 
 // One query per 64-thread workgroup: every slot [0, n), or the slots of
 // `list` [0, *count) when a list is given.
-template <bool PER>
+template <bool PER, int NL>
 struct KnnWave {
     using Args = WaveArgs;
     static constexpr int kThreads = kWave;
     static __device__ __forceinline__ void body(const Args& W, Blk B)
     {
-        __shared__ WaveLds L;
+        __shared__ WaveLds<NL> L;
         const int lane = threadIdx.x;
         if (W.list) {
             const int32_t nl = *W.count;
-            for (int64_t t = B.id; t < nl; t += B.n) knn_wave_query<PER>(W.A, W.list[t], L, lane);
+            for (int64_t t = B.id; t < nl; t += B.n) knn_wave_query<PER, NL>(W.A, W.list[t], L, lane);
         } else {
             const int64_t q = B.id;
-            if (q < W.A.n) knn_wave_query<PER>(W.A, int(q), L, lane);
+            if (q < W.A.n) knn_wave_query<PER, NL>(W.A, int(q), L, lane);
         }
     }
 };
 
-template <bool PER>
+template <bool PER, int NL>
 __global__ __launch_bounds__(kWave) void k_knn_wave(WaveArgs W)
 {
-    KnnWave<PER>::body(W, Blk{W.list ? int64_t(blockIdx.x) : xcd_block(), int64_t(gridDim.x)});
+    KnnWave<PER, NL>::body(W, Blk{W.list ? int64_t(blockIdx.x) : xcd_block(), int64_t(gridDim.x)});
 }
+
+// the list's length for neighbourhoods of k: k - 1 pairs kept by a cut and a
+// flush of 4 * kWave more always fit
+constexpr int kListSmall = 384, kListLarge = 512;
+constexpr int kSmallK = kListSmall - 4 * kWave + 1;
+static_assert(kListLarge >= (kMaxK - 1) + 4 * kWave, "a flush after a cut must fit the list");
 
 void launch_knn_wave(const KnnArgs& A, bool per, const int32_t* list, const int32_t* count, int64_t nblocks,
                      hipStream_t st)
 {
     const dim3 grid(unsigned(nblocks > 0 ? nblocks : 1));
     const WaveArgs W{A, list, count};
-    if (per) hipLaunchKernelGGL(k_knn_wave<true>, grid, dim3(kWave), 0, st, W);
-    else hipLaunchKernelGGL(k_knn_wave<false>, grid, dim3(kWave), 0, st, W);
+    if (A.k <= kSmallK) {
+        if (per) hipLaunchKernelGGL((k_knn_wave<true, kListSmall>), grid, dim3(kWave), 0, st, W);
+        else hipLaunchKernelGGL((k_knn_wave<false, kListSmall>), grid, dim3(kWave), 0, st, W);
+    } else {
+        if (per) hipLaunchKernelGGL((k_knn_wave<true, kListLarge>), grid, dim3(kWave), 0, st, W);
+        else hipLaunchKernelGGL((k_knn_wave<false, kListLarge>), grid, dim3(kWave), 0, st, W);
+    }
 }
 
 void many_add_wave(ManyBuilder& B, const std::vector<WaveArgs>& tab, const std::vector<int64_t>& nb, bool per)
 {
-    if (per) B.add<KnnWave<true>>(tab, nb);
-    else B.add<KnnWave<false>>(tab, nb);
+    std::vector<int64_t> small(nb), large(nb);
+    bool any_s = false, any_l = false;
+    for (size_t r = 0; r < nb.size(); ++r) {
+        const bool s = tab[r].A.k <= kSmallK;
+        (s ? large : small)[r] = 0;
+        any_s = any_s || small[r] > 0;
+        any_l = any_l || large[r] > 0;
+    }
+    if (any_s) {
+        if (per) B.add<KnnWave<true, kListSmall>>(tab, small);
+        else B.add<KnnWave<false, kListSmall>>(tab, small);
+    }
+    if (any_l) {
+        if (per) B.add<KnnWave<true, kListLarge>>(tab, large);
+        else B.add<KnnWave<false, kListLarge>>(tab, large);
+    }
 }
 
 }  // namespace gd

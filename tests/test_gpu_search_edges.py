@@ -1,0 +1,51 @@
+"""The wavefront-per-query search at its edges: neighbourhoods just beyond the
+shared lists, at the change of list length, and sets smaller than k, against
+brute force (exact lists; distances within one rounding)."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import workloads
+from paper_2609_35967_amd import Engine
+
+pytestmark = pytest.mark.gpu
+
+
+def _check(params, st):
+    eng = Engine(params, st, seed=3)
+    for _ in range(2):  # without previous distances, then with them
+        eng.build_neighbors()
+        torch.cuda.synchronize()
+        s = eng.state_numpy()
+        P = oracle.make_problem(params)
+        nbr, cnt, dmax = oracle.knn(P, s["x"], s["y"], s["z"], s["M"])
+        assert np.array_equal(eng.cnt.cpu().numpy(), cnt)
+        assert np.array_equal(eng.nbr.cpu().numpy(), nbr)
+        np.testing.assert_allclose(eng.dmax.cpu().numpy(), dmax, rtol=1e-15)
+    assert eng.status() & 0x21 == 0
+
+
+@pytest.mark.parametrize("k", [34, 48, 64, 65, 129, 130])
+@pytest.mark.parametrize("n", [37, 130, 3001])
+def test_disk(k, n):
+    params, st = workloads.by_name("disk3d", 5, n)
+    _check(dict(params, k=k), st)
+
+
+@pytest.mark.parametrize("k", [40, 64, 129])
+def test_many_equal_distances(k):
+    """A lattice: shells of equal distance larger than the bin the ranking takes."""
+    st = workloads.lattice_box(13)
+    _check(dict(workloads.const_box_params(13 ** 3, k=k)), st)
+
+
+@pytest.mark.parametrize("k", [50, 200])
+def test_clustered_first_search(k):
+    """Dense clumps in a sparse set: the first radius holds far more than the list."""
+    g = np.random.Generator(np.random.PCG64(11))
+    n = 4000
+    c = g.random((3, 8))
+    p = np.where(g.random(n) < 0.9, c[:, g.integers(0, 8, n)] + 1e-4 * g.standard_normal((3, n)), g.random((3, n))) % 1.0
+    st = dict(id=np.arange(n, dtype=np.uint32), x=p[0], y=p[1], z=p[2], M=np.full(n, 1.0 / n), m=np.ones(n))
+    _check(dict(workloads.const_box_params(n, k=k)), st)
