@@ -60,7 +60,8 @@ struct alignas(256) WsHeader {
     int32_t xq[4][8];            // per-die work queues of the gather-heavy kernels
     int32_t heavy_n;             // sampling: particles handed to the wavefront-per-particle pass
     int32_t heavy_next;          // sampling: next of them to take
-    int32_t knn_fb_n[2];         // neighbour search: queries the tile search handed back (two lists)
+    int32_t knn_fb_n;            // neighbour search: queries the tile search handed back
+    int32_t pad1;
     int32_t mc_seg[kXcd];        // sampling: particles with an event, per die's segment of the list
     int32_t mc_next;             // sampling: next group of them to take
     int32_t heavy_n0;            // sampling: particles the screen sent straight to the wavefront pass (at the list's end)

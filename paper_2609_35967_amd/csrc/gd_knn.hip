@@ -52,7 +52,6 @@ namespace gd {
 constexpr int kDMax = 3;  // levels of the nested bin chain
 constexpr int kRescales = 4;  // restarts of pass A on a finer distance scale
 constexpr int kQBlock = 128;
-constexpr bool kTileSearch = true;  // shared candidate tiles before the per-lane search (k <= 33)
 constexpr int kFallbackBlocks = 8192;  // one-wavefront workgroups that take the handed-back queries (about one each)
 constexpr int kQueue = 4;  // level-1 bucket masks a walk keeps queued
 static_assert(kQueue >= 1 && kQueue <= 4, "the queue keeps its masks in the bytes of one word");
@@ -181,15 +180,14 @@ __device__ __forceinline__ void LevelBoxes::body(const Args& A, Blk B)
 // level's capacity enter as empty boxes, which leave a union unchanged: the
 // boxes are those of the level-by-level passes.  The grid covers cap1 (it is
 // at most a multiple of 32 above cap0 / 8); the host passes box2 only when
-// 4 nodes per block cover cap2.  Block 0 also clears the query's counters
-// (zq: the per-die queue, kXcd entries; zf: the two fallback list lengths).
+// 4 nodes per block cover cap2.  Block 0 also clears the length zf of the
+// tile search's list of handed-back queries.
 struct TreeLowArgs {
     BucketArgs b;
     FBox* box1;
     int64_t cap1;
     FBox* box2;
     int64_t cap2;
-    int32_t* zq;
     int32_t* zf;
 };
 
@@ -198,10 +196,7 @@ __global__ __launch_bounds__(256) void k_tree_low(TreeLowArgs A)
     __shared__ FBox s0[256];
     __shared__ FBox s1[32];
     const int t = threadIdx.x;
-    if (blockIdx.x == 0) {
-        if (t < kXcd) A.zq[t] = 0;
-        if (t < 2) A.zf[t] = 0;
-    }
+    if (blockIdx.x == 0 && t == 0) *A.zf = 0;
     const int64_t b = int64_t(blockIdx.x) * 256 + t;
     FBox x = empty_box();
     if (b < A.b.cap0) {
@@ -477,26 +472,14 @@ struct KnnQuery {
 };
 
 template <bool PER>
-__global__ __launch_bounds__(kQBlock) void k_knn_query(KnnArgs A)
-{
-    KnnQuery<PER>::body(A, Blk{int64_t(blockIdx.x), int64_t(gridDim.x)});
-}
-
-template <bool PER>
 __device__ __forceinline__ void KnnQuery<PER>::body(const Args& A, Blk B)
 {
     using QL = QueryLds;
     constexpr int KP2 = 32;  // row registers
     __shared__ uint32_t s_lds[QL::kWords * kQBlock];
     const int tid = threadIdx.x;
-    int64_t q64;
-    if (A.list) {  // the queries of a list (those the tile search handed back)
-        const int64_t idx = (B.id * (kQBlock / kWave) + tid / kWave) * kWave + (tid & (kWave - 1));
-        q64 = idx < *A.list_n ? A.list[idx] : A.n;
-    } else {
-        const int32_t item = xcd_take(A.xq, int32_t(B.n * (kQBlock / kWave)));
-        q64 = item < 0 ? A.n : int64_t(item) * kWave + (tid & (kWave - 1));
-    }
+    const int32_t item = xcd_take(A.xq, int32_t(B.n * (kQBlock / kWave)));
+    const int64_t q64 = item < 0 ? A.n : int64_t(item) * kWave + (tid & (kWave - 1));
     if (q64 >= A.n) return;
     const int q = int(q64);
     const int na = A.h->n_active;
@@ -1033,7 +1016,7 @@ int launch_knn(const gd_problem* p, const gd_neighbors* nb, void* ws, const Layo
     } else {
         const bool two = L.levels > 2 && g0 * 4 >= T.cap[2];
         const TreeLowArgs TL{S.bucket, S.level[1].cur, T.cap[1], two ? S.level[2].cur : nullptr, two ? T.cap[2] : 0,
-                             S.A.xq, hw->knn_fb_n};
+                             &hw->knn_fb_n};
         hipLaunchKernelGGL(k_tree_low, dim3(unsigned(g0)), dim3(256), 0, st, TL);
         built = two ? 2 : 1;
     }
@@ -1058,34 +1041,21 @@ int launch_knn(const gd_problem* p, const gd_neighbors* nb, void* ws, const Layo
         prof_mark(GD_PROF_KNN_QUERY, 1, st);
         return 0;
     }
-    const dim3 grid(unsigned((n + kQBlock - 1) / kQBlock));
-    const bool cleared = L.levels > 1;  // the tree's first pass cleared the counters
-    if (!cleared) launch_fill_i32(A.xq, kXcd, 0, st);
-    if (kTileSearch) {
-        // shared candidate tiles first; the queries they cannot complete go
-        // through the per-lane search
-        int32_t* fb0 = at<int32_t>(ws, L.keys1);  // keys1 and vals1 (n entries each): free after the sort
-        int32_t* fb1 = at<int32_t>(ws, L.vals1);
-        if (!cleared) launch_fill_i32(hw->knn_fb_n, 2, 0, st);
-        launch_knn_tile(A, per, fb0, fb1, hw->knn_fb_n, st);
-        // handed-back queries with a previous distance (usually well under 1%:
-        // sparse regions with many candidates) take a wavefront each
-        launch_knn_wave(A, per, fb1, hw->knn_fb_n + 1, kFallbackBlocks, st);
-        // those without one (the first search of a run) take the per-lane search
-        A.list = fb0;
-        A.list_n = hw->knn_fb_n;
-    }
-    if (per) hipLaunchKernelGGL(k_knn_query<true>, grid, dim3(kQBlock), 0, st, A);
-    else hipLaunchKernelGGL(k_knn_query<false>, grid, dim3(kQBlock), 0, st, A);
+    // shared candidate tiles first; the queries they cannot complete (usually
+    // well under 1%: sparse regions with many candidates; some 15% in a
+    // run's first search) take a wavefront each
+    int32_t* fb = at<int32_t>(ws, L.vals1);  // n entries, free after the sort
+    if (L.levels == 1) launch_fill_i32(&hw->knn_fb_n, 1, 0, st);  // (else cleared by the tree's first pass)
+    launch_knn_tile(A, per, fb, &hw->knn_fb_n, st);
+    launch_knn_wave(A, per, fb, &hw->knn_fb_n, kFallbackBlocks, st);
     prof_mark(GD_PROF_KNN_QUERY, 1, st);
     return 0;
 }
 
 // The search of every run as stages of one interval: the bucket boxes, each
 // tree level over the runs that have it, then the queries: k > 33 one
-// wavefront per query; k <= 33 (with tiles) the tile search, its fallback
-// wavefronts and the per-lane search of the first list; otherwise the
-// per-lane search over every query.  Runs are grouped by periodicity and
+// wavefront per query; k <= 33 (with tiles) the tile search and its fallback
+// wavefronts; otherwise the per-lane search over every query.  Runs are grouped by periodicity and
 // k class, a launch per group and stage.
 void many_knn(ManyBuilder& B, const std::vector<ManyRun>& R)
 {
@@ -1139,31 +1109,31 @@ void many_knn(ManyBuilder& B, const std::vector<ManyRun>& R)
             std::vector<ClearArgs> clr(nr);
             for (size_t r = 0; r < nr; ++r) {
                 WsHeader* hw = at<WsHeader>(R[r].ws, R[r].L.hdr);
-                clr[r] = ClearArgs{S[r].A.xq, kXcd, tile ? hw->knn_fb_n : nullptr, 2};
+                clr[r] = tile ? ClearArgs{&hw->knn_fb_n, 1, nullptr, 0} : ClearArgs{S[r].A.xq, kXcd, nullptr, 0};
                 nb[r] = mine[r];
             }
             B.add<ClearCounters>(clr, nb);
-            std::vector<KnnArgs> qa(nr);
-            for (size_t r = 0; r < nr; ++r) qa[r] = S[r].A;
             if (tile) {
                 std::vector<TileArgs> tt(nr);
                 std::vector<WaveArgs> wt(nr);
                 std::vector<int64_t> fnb(nr);
                 for (size_t r = 0; r < nr; ++r) {
                     WsHeader* hw = at<WsHeader>(R[r].ws, R[r].L.hdr);
-                    int32_t* fb0 = at<int32_t>(R[r].ws, R[r].L.keys1);
-                    int32_t* fb1 = at<int32_t>(R[r].ws, R[r].L.vals1);
-                    tt[r] = TileArgs{S[r].A, fb0, fb1, hw->knn_fb_n};
-                    wt[r] = WaveArgs{S[r].A, fb1, hw->knn_fb_n + 1};
-                    qa[r].list = fb0;
-                    qa[r].list_n = hw->knn_fb_n;
+                    int32_t* fb = at<int32_t>(R[r].ws, R[r].L.vals1);
+                    tt[r] = TileArgs{S[r].A, fb, &hw->knn_fb_n};
+                    wt[r] = WaveArgs{S[r].A, fb, &hw->knn_fb_n};
                     nb[r] = mine[r] ? cdiv(R[r].p.n, kWave) : 0;
                     fnb[r] = mine[r] ? std::max<int64_t>(1, cdiv(R[r].p.n, B.tune.fallback_div)) : 0;
                 }
                 many_add_tile(B, tt, nb, per);
                 many_add_wave(B, wt, fnb, per);
+                continue;
             }
-            for (size_t r = 0; r < nr; ++r) nb[r] = mine[r] ? cdiv(R[r].p.n, kQBlock) : 0;
+            std::vector<KnnArgs> qa(nr);
+            for (size_t r = 0; r < nr; ++r) {
+                qa[r] = S[r].A;
+                nb[r] = mine[r] ? cdiv(R[r].p.n, kQBlock) : 0;
+            }
             if (per) B.add<KnnQuery<true>>(qa, nb);
             else B.add<KnnQuery<false>>(qa, nb);
         }

@@ -61,18 +61,15 @@ struct KnnArgs {
     double* dmax;
     int32_t row_vec;  // nbr is 16-byte aligned
     int32_t* xq;      // per-die work queue counters
-    const double* hint;  // previous neighbour distance per slot (search hint only)
+    double* hint;  // previous neighbour distance per slot (search hint only)
     void* ws;
-    const int32_t* list;    // when set: the queries are list[0 .. *list_n)
-    const int32_t* list_n;
 };
 
-// the tile search's arguments: the search's, and its two lists of handed-back
-// queries with their counts
+// the tile search's arguments: the search's, and its list of handed-back
+// queries with its count
 struct TileArgs {
     KnnArgs A;
-    int32_t* fb0;
-    int32_t* fb1;
+    int32_t* fb;
     int32_t* fb_n;
 };
 
@@ -209,9 +206,8 @@ __device__ inline void bitonic_sort(int32_t (&v)[N])
 void launch_knn_wave(const KnnArgs& A, bool per, const int32_t* list, const int32_t* count, int64_t nblocks,
                      hipStream_t st);
 // 64 Morton-consecutive queries per wavefront from shared candidate tiles
-// (gd_knn_tile.hip), k <= 33; the queries it cannot complete go to fb0 (no
-// usable previous distance) or fb1 (the rest)
-void launch_knn_tile(const KnnArgs& A, bool per, int32_t* fb0, int32_t* fb1, int32_t* fb_n, hipStream_t st);
+// (gd_knn_tile.hip), k <= 33; the queries it cannot complete go to fb
+void launch_knn_tile(const KnnArgs& A, bool per, int32_t* fb, int32_t* fb_n, hipStream_t st);
 // the same two searches as stages of a many-run interval
 void many_add_tile(ManyBuilder& B, const std::vector<TileArgs>& tab, const std::vector<int64_t>& nb, bool per);
 void many_add_wave(ManyBuilder& B, const std::vector<WaveArgs>& tab, const std::vector<int64_t>& nb, bool per);

@@ -6,8 +6,9 @@
 // its instructions go to box tests and walk bookkeeping, not to distances.
 // Here the wavefront's queries share the walk:
 //   1. each lane's radius is its particle's distance from the previous search
-//      widened by kHintSlack (a lane without a usable one is handed back, see
-//      6); eight groups of eight Morton-consecutive lanes each bound their
+//      widened by kHintSlack; a lane without a usable one (a run's first
+//      search) takes the k-th distance within the kGuess slots around the
+//      wavefront's, a guaranteed bound (guess_radius); eight groups of eight Morton-consecutive lanes each bound their
 //      spheres by one box, rounded outward to single precision;
 //   2. the box tree is traversed breadth first, eight nodes (64 child boxes)
 //      at a time, testing each child against the boxes of the groups its
@@ -25,10 +26,10 @@
 //   5. the bin holding the (k-1)-th other splits the list into sure entries
 //      and a boundary bin ranked by (d^2, slot); the row is written once, in
 //      slot order;
-//   6. lanes without a usable previous distance, whose radius held fewer
-//      than k-1 others, whose list or group list overflowed, or whose
-//      boundary bin is over-full, go to a list that the per-lane search then
-//      completes.  The result never depends on which lanes go there.
+//   6. lanes whose radius held fewer than k-1 others, whose list or group
+//      list overflowed, or whose boundary bin is over-full, go to a list that
+//      the wavefront-per-query search then completes.  The result never
+//      depends on which lanes go there.
 // d^2 is (dx*dx + dy*dy) + dz*dz with every operation rounded on its own, and
 // every bin function is monotone in d^2, so each row is the k-1 smallest
 // (d^2, slot) exactly.
@@ -45,6 +46,7 @@ constexpr int kFront = 512;          // traversal frontier (nodes of one level)
 constexpr int kPairs = 512;          // (bucket, group) pairs awaiting their sphere tests
 constexpr int kGList = 128;          // buckets per group after the sphere tests
 constexpr int kMaskW = kGList / 32;  // words of a lane's bucket mask
+constexpr int kGuess = 256;          // slots a first radius is guessed from
 static_assert(kGList * kBucket <= 2048, "a list entry keeps the bucket's place and slot in 11 bits");
 
 template <bool PER>
@@ -65,6 +67,12 @@ struct TileLds {
         struct {
             uint16_t list[kTList][kWave];
         } d;
+        // first radius: the slots' positions from the wavefront's first
+        // query, and per-lane bin counters (halves of a word: bins 2w, 2w + 1)
+        struct {
+            float4 p[kGuess];
+            uint32_t cnt[kNB / 2][kWave];
+        } g;
     } u;
     uint32_t glist[kNGrp][kGList];
     float gbox[kNGrp][6];            // group boxes: lo[3], hi[3]
@@ -108,6 +116,80 @@ __device__ inline bool group_meets(const KnnArgs& A, const float (&g)[6], const 
     return ok;
 }
 
+// The first radius (squared) of lanes without a previous distance: of the
+// kGuess slots around the wavefront's queries, the distance within which
+// k - 1 others lie, to the upper edge of a bin of 2^(1/8) in d^2.  On a 3D
+// disk and a uniform box it is 1.15 times the true k-th distance at the
+// median and 2 times at the 99th percentile (the k slots about the query
+// alone give several times it).  Single precision about the first query; the
+// rounding up leaves room for it, and a radius that still falls short only
+// sends its lane to the list.  Returns -1 without one.
+template <bool PER>
+__device__ inline double guess_radius(const KnnArgs& A, TileLds<PER>& L, int64_t q0, int q, bool mine,
+                                      const double (&qp)[3], int na, int k, int lane)
+{
+    int lo = int(q0) + kWave / 2 - kGuess / 2;
+    lo = lo + kGuess > na ? na - kGuess : lo;
+    lo = lo < 0 ? 0 : lo;
+    const int m = na - lo < kGuess ? na - lo : kGuess;  // slots taken (> k: the caller has na > k)
+    const double4 b = A.pos[q0];
+    const double base[3] = {b.x, b.y, b.z};
+    float Lf[3], rL[3];
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        Lf[a] = PER && A.per[a] ? float(A.L[a]) : 0.0f;
+        rL[a] = PER && A.per[a] ? 1.0f / float(A.L[a]) : 0.0f;
+    }
+#pragma unroll
+    for (int t = 0; t < kGuess / kWave; ++t) {
+        const int s = t * kWave + lane;
+        const double4 p = A.pos[lo + (s < m ? s : 0)];
+        L.u.g.p[s] = make_float4(float(p.x - base[0]), float(p.y - base[1]), float(p.z - base[2]), 0.0f);
+    }
+#pragma unroll
+    for (int w = 0; w < kNB / 2; ++w) L.u.g.cnt[w][lane] = 0;
+    __syncthreads();
+    const float f[3] = {float(qp[0] - base[0]), float(qp[1] - base[1]), float(qp[2] - base[2])};
+    auto d2_of = [&](int s) {
+        const float4 p = L.u.g.p[s];
+        float d[3] = {p.x - f[0], p.y - f[1], p.z - f[2]};
+#pragma unroll
+        for (int a = 0; a < 3; ++a)
+            if (PER) d[a] = d[a] - Lf[a] * rintf(d[a] * rL[a]);
+        return fmaf(d[2], d[2], fmaf(d[1], d[1], d[0] * d[0]));
+    };
+    // the scale: the largest distance to the k slots about the query
+    int f0 = (mine ? q : int(q0)) - lo - k / 2;
+    f0 = f0 + k > m ? m - k : f0;
+    f0 = f0 < 0 ? 0 : f0;
+    float R0 = 0.0f;
+    for (int s = 0; s < k; ++s) R0 = fmaxf(R0, d2_of(f0 + s));
+    const float sc = R0 > 0.0f ? 1.0f / R0 : 0.0f;
+    for (int s = 0; s < m; ++s) {
+        const float x = d2_of(s) * sc;
+        // 8 bins per octave below 1 (the bits of the float: 20 below the
+        // bin's three), bin 0 also everything smaller
+        const int bn = (__float_as_int(x) >> 20) - (127 * 8 - kNB);
+        const int bc = min(max(bn, 0), kNB - 1);
+        if (x < 1.0f) atomicAdd(&L.u.g.cnt[bc >> 1][lane], 1u << (16 * (bc & 1)));
+    }
+    __syncthreads();
+    // bins up to the one that completes the particle and k - 1 others
+    int cum = 0, bs = kNB;
+#pragma unroll
+    for (int w = 0; w < kNB / 2; ++w) {
+        const uint32_t c = L.u.g.cnt[w][lane];
+        cum += int(c & 0xFFFFu);
+        bs = (bs == kNB && cum >= k) ? 2 * w : bs;
+        cum += int(c >> 16);
+        bs = (bs == kNB && cum >= k) ? 2 * w + 1 : bs;
+    }
+    __syncthreads();
+    const float edge = bs < kNB - 1 ? __int_as_float((bs + 1 + 127 * 8 - kNB) << 20) : 1.0f;
+    const double R2 = double(R0) * double(edge) * (1.0 + 1e-5);
+    return mine && sc > 0.0f && sc < INFINITY && R2 < INFINITY ? R2 : -1.0;
+}
+
 template <bool PER>
 struct KnnTile {
     using Args = TileArgs;
@@ -130,9 +212,6 @@ template <bool PER>
 __device__ __forceinline__ void KnnTile<PER>::body(const Args& TA, Blk B)
 {
     const KnnArgs& A = TA.A;
-    int32_t* __restrict__ fb0 = TA.fb0;
-    int32_t* __restrict__ fb1 = TA.fb1;
-    int32_t* __restrict__ fb_n = TA.fb_n;
     __shared__ TileLds<PER> L;
     const int lane = threadIdx.x;
     const int64_t item = xcd_item(B.id, B.n);
@@ -169,8 +248,11 @@ __device__ __forceinline__ void KnnTile<PER>::body(const Args& TA, Blk B)
         }
     }
     // 1. radius from the previous distance: positive, finite, within the
-    //    diagonal of the active set's box and below the maximum search scale
+    //    diagonal of the active set's box and below the maximum search scale;
+    //    else guessed from the slots around (and kept as the distance that
+    //    the wavefront-per-query search of a handed-back lane starts from)
     double R2 = 0.0;
+    const bool may = ok;
     if (ok) {
         const double hv = A.hint[q] * kHintSlack;
         ok = hv > 0.0 && hv < INFINITY;
@@ -189,10 +271,18 @@ __device__ __forceinline__ void KnnTile<PER>::body(const Args& TA, Blk B)
                 e2 += ext * ext;
             }
             R2 = hv * hv;
-            ok = R2 <= e2 && R2 < A.rmax2;
+            ok = R2 <= e2;
         }
     }
-    const bool tried = ok;  // searched with a usable previous distance
+    if (__ballot(may && !ok)) {
+        const double g2 = guess_radius<PER>(A, L, item * kWave, q, may, qp, na, k, lane);
+        if (may && !ok) {
+            ok = g2 > 0.0;
+            R2 = ok ? g2 : 0.0;
+            A.hint[q] = ok ? sqrt(g2) * (1.0 / kHintSlack) : 0.0;
+        }
+    }
+    ok = ok && R2 < A.rmax2;
     QF qf;
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
@@ -672,27 +762,21 @@ __device__ __forceinline__ void KnnTile<PER>::body(const Args& TA, Blk B)
         w[6] = wave_ok ? 1 : 0;
     }
 #endif
-    // 6. the rest: lanes that had no usable previous distance to the per-lane
-    //    search (list 0), the others (sparse regions, many candidates) to the
-    //    wavefront-per-query search (list 1)
+    // 6. the rest (sparse regions, many candidates) to the
+    //    wavefront-per-query search
     fb = fb && !ok;
-#pragma unroll
-    for (int l = 0; l < 2; ++l) {
-        const bool mine = fb && (l == 0 ? !tried : tried);
-        const uint64_t fbm = __ballot(mine);
-        int32_t base = 0;
-        if (lane == 0 && fbm) base = atomicAdd(fb_n + l, int32_t(__popcll(fbm)));
-        base = __builtin_amdgcn_readfirstlane(base);
-        if (mine) (l == 0 ? fb0 : fb1)[base + int(__popcll(fbm & ((uint64_t(1) << lane) - 1)))] = q;
-    }
+    const uint64_t fbm = __ballot(fb);
+    int32_t base = 0;
+    if (lane == 0 && fbm) base = atomicAdd(TA.fb_n, int32_t(__popcll(fbm)));
+    base = __builtin_amdgcn_readfirstlane(base);
+    if (fb) TA.fb[base + int(__popcll(fbm & ((uint64_t(1) << lane) - 1)))] = q;
 }
 
-// fb0 and fb1 receive the handed-back queries (n entries each): those with no
-// usable previous distance, and the rest; fb_n[0], fb_n[1] count them
-void launch_knn_tile(const KnnArgs& A, bool per, int32_t* fb0, int32_t* fb1, int32_t* fb_n, hipStream_t st)
+// fb receives the handed-back queries (n entries), counted by *fb_n
+void launch_knn_tile(const KnnArgs& A, bool per, int32_t* fb, int32_t* fb_n, hipStream_t st)
 {
     const dim3 grid(unsigned((A.n + kWave - 1) / kWave));
-    const TileArgs TA{A, fb0, fb1, fb_n};
+    const TileArgs TA{A, fb, fb_n};
     if (per) hipLaunchKernelGGL(k_knn_tile<true>, grid, dim3(kWave), 0, st, TA);
     else hipLaunchKernelGGL(k_knn_tile<false>, grid, dim3(kWave), 0, st, TA);
 }
