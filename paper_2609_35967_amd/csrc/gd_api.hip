@@ -147,11 +147,6 @@ static int hip_ok(const char* what)
     return GD_OK;
 }
 
-__global__ void k_copy_na(const WsHeader* h, int32_t* out)
-{
-    if (threadIdx.x == 0) *out = h->n_active;
-}
-
 __global__ void k_clear_status(WsHeader* h)
 {
     if (threadIdx.x == 0) h->status = 0;
@@ -208,10 +203,9 @@ int32_t gd_build_neighbors(const gd_problem* p, const gd_particles* in, gd_parti
     if (rc) return rc;
     hipStream_t st = static_cast<hipStream_t>(stream);
     if (p->n == 0) return GD_OK;
-    launch_morton_sort(p, in, &o, nb->dmax, ws, L, st);
+    launch_morton_sort(p, in, &o, nb->dmax, nb->n_active, ws, L, st);
     out->cur = in->cur;
     launch_knn(p, nb, ws, L, st);
-    if (nb->n_active) hipLaunchKernelGGL(k_copy_na, dim3(1), dim3(64), 0, st, at<WsHeader>(ws, L.hdr), nb->n_active);
     return hip_ok("gd_build_neighbors");
 }
 
@@ -340,7 +334,7 @@ int32_t gd_sample_audit(const gd_problem* p, const gd_particles* s, gd_interval*
     rc = check_ws(p, ws, ws_bytes, L);
     if (rc) return rc;
     if (p->n == 0) return GD_OK;
-    launch_audit(p, s, iv, ws, L, static_cast<hipStream_t>(stream));
+    launch_audit(p, s->m[s->cur], s->M, s->m[s->cur ^ 1], p->n, iv, ws, L, static_cast<hipStream_t>(stream));
     return hip_ok("gd_sample_audit");
 }
 

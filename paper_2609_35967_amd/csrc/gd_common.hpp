@@ -15,7 +15,7 @@ constexpr int kXcd = 8;             // accelerator dies, each with its own L2
 constexpr int kNBin = 128;          // controller bins: ilogb(m) in [-64, 63]
 constexpr int kBinOff = 64;
 constexpr int64_t kTicks = int64_t(1) << 30;  // ticks per collision step
-constexpr int kSortTile = 4096;     // keys per radix-sort block
+constexpr int kSortRounds = 16;     // most keys per thread of a radix-sort block (256 threads)
 constexpr int kRedBlocks = 256;     // blocks of the bin reductions
 constexpr int kMaxK = 256;
 constexpr int kBucket = 4;          // particles per leaf bucket of the search tree
@@ -61,7 +61,7 @@ struct alignas(256) WsHeader {
     int32_t heavy_n;             // sampling: particles handed to the wavefront-per-particle pass
     int32_t heavy_next;          // sampling: next of them to take
     int32_t knn_fb_n;            // neighbour search: queries the tile search handed back
-    int32_t pad1;
+    uint32_t red_done;           // controller sums: blocks done (wraps to 0 at the last)
     int32_t mc_seg[kXcd];        // sampling: particles with an event, per die's segment of the list
     int32_t mc_next;             // sampling: next group of them to take
     int32_t heavy_n0;            // sampling: particles the screen sent straight to the wavefront pass (at the list's end)
@@ -74,7 +74,10 @@ struct Layout {
         snap, a, b, part, hint, heavy, mclist, stats, total;
     int64_t n;
     int32_t k;
-    int32_t nsort_blocks;
+    // radix sort: keys per thread, blocks, blocks per group of the digit
+    // counts and groups (hist: a row of 256 counts per block, then per pass a
+    // row per group)
+    int32_t sort_rounds, nsort_blocks, sort_sup, nsort_sup;
     // implicit search tree: level l holds cnt[l] boxes (padded to a multiple
     // of kFan) starting at box index off[l]; level 0 = buckets of kBucket
     // slots, node i of level l >= 1 = children kFan*i .. kFan*i+7 of level l-1;
@@ -94,7 +97,15 @@ __host__ inline Layout make_layout(int64_t n, int32_t k)
     Layout L{};
     L.n = n;
     L.k = k;
-    L.nsort_blocks = int32_t((n + kSortTile - 1) / kSortTile);
+    // few keys per thread while that leaves blocks idle (a pass over 64K keys
+    // takes as long as its longest block); about as many groups as blocks in
+    // a group, since every scatter block adds up a row of each
+    L.sort_rounds = 1;
+    while (L.sort_rounds < kSortRounds && n > int64_t(128) * 256 * L.sort_rounds) L.sort_rounds *= 2;
+    L.nsort_blocks = int32_t((n + 256 * L.sort_rounds - 1) / (256 * L.sort_rounds));
+    L.sort_sup = 8;
+    while (int64_t(L.sort_sup) * L.sort_sup < L.nsort_blocks) L.sort_sup *= 2;
+    L.nsort_sup = (L.nsort_blocks + L.sort_sup - 1) / L.sort_sup;
     size_t o = 0;
     auto take = [&](size_t bytes) { size_t at = o; o = align256(o + bytes); return at; };
     const size_t nn = size_t(n > 0 ? n : 1);
@@ -103,7 +114,7 @@ __host__ inline Layout make_layout(int64_t n, int32_t k)
     L.keys1 = take(4 * nn);
     L.vals0 = take(4 * nn);
     L.vals1 = take(4 * nn);
-    L.hist = take(4 * size_t(256) * (L.nsort_blocks + 1));
+    L.hist = take(4 * size_t(256) * (size_t(L.nsort_blocks) + 4 * size_t(L.nsort_sup)));
     L.red = take(sizeof(double) * 8 * kRedBlocks);
     L.pos4 = take(32 * nn);
     {
@@ -214,8 +225,7 @@ __global__ __launch_bounds__(K::kThreads) void k_many(const typename K::Args* __
 }
 
 // the counters a many-run interval clears before a stage (one block per run):
-// the die queues and the two fallback counts of the search, or the list
-// segment counts of sampling
+// the die queues or the fallback count of the search
 struct ClearArgs {
     int32_t* a;
     int32_t na;
@@ -355,6 +365,12 @@ __device__ inline double readlane_d(double x, int l)
                             __builtin_amdgcn_readlane(__double2loint(x), l));
 }
 
+__device__ inline uint64_t readlane_u64(uint64_t x, int l)
+{
+    return (uint64_t(uint32_t(__builtin_amdgcn_readlane(int(x >> 32), l))) << 32) |
+           uint32_t(__builtin_amdgcn_readlane(int(x), l));
+}
+
 // the double-double sum over the wavefront, in every lane: the DPP steps of
 // wave_scan_incl with dd_add, then the last lane's prefix read across
 template <int CTRL, int ROWS>
@@ -398,6 +414,36 @@ __device__ inline void wave_sum_dd3(dd& a, dd& b, dd& c)
     a = dd{readlane_d(a.hi, kWave - 1), readlane_d(a.lo, kWave - 1)};
     b = dd{readlane_d(b.hi, kWave - 1), readlane_d(b.lo, kWave - 1)};
     c = dd{readlane_d(c.hi, kWave - 1), readlane_d(c.lo, kWave - 1)};
+}
+
+// ---------------------------------------------------------------------------
+// Values that one block of a launch leaves for the block that ends last.  The
+// dies' L2 caches do not see each other's lines, so they are stored by
+// device-scope atomics, which go to the memory side.  Each wavefront waits
+// for its stores to get there (done_stores), the block's barrier follows, and
+// one thread counts the block; the last one's acquire fence drops the lines
+// its caches may hold of them, and plain loads then read them.  Plain stores
+// with a device-scope fence instead write back a whole L2: 14 us over 256
+// blocks with a fence in each block, 40 us with one in each wavefront.
+__device__ inline void put_device(double* p, double v)
+{
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+__device__ inline void put_device(uint64_t* p, uint64_t v)
+{
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+__device__ inline void done_stores() { __builtin_amdgcn_s_waitcnt(0); }
+
+// true in the last of `blocks` blocks to count itself (the counter wraps to
+// 0 there); by one thread, after the block's barrier and before another
+__device__ inline bool last_block(uint32_t* counter, int64_t blocks)
+{
+    if (atomicInc(counter, unsigned(blocks - 1)) != unsigned(blocks - 1)) return false;
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+    return true;
 }
 
 __device__ inline void set_status(void* ws, int bits)

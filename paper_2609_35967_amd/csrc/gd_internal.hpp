@@ -24,9 +24,8 @@ struct PermuteArgs {
 DevProblem to_dev(const gd_problem* p);
 void prof_mark(int which, int after, hipStream_t st);
 
-int launch_morton_sort(const gd_problem* p, const gd_particles* in, gd_particles* out, const double* hint, void* ws,
-                       const Layout& L,
-                       hipStream_t st);
+int launch_morton_sort(const gd_problem* p, const gd_particles* in, gd_particles* out, const double* hint,
+                       int32_t* na_out, void* ws, const Layout& L, hipStream_t st);
 void launch_fill_i32(int32_t* a, int64_t n, int32_t v, hipStream_t st);
 int launch_knn(const gd_problem* p, const gd_neighbors* nb, void* ws, const Layout& L, hipStream_t st);
 int launch_rates(const gd_problem* p, const gd_particles* s, const gd_neighbors* nb, gd_interval* iv, double* lam_i,
@@ -39,7 +38,6 @@ int launch_reshuffle(const gd_problem* p, const gd_neighbors* nb, uint64_t seed,
 hipError_t reshuffle_static_table(int32_t** table);
 int launch_reshuffle_static(const gd_problem* p, const gd_neighbors* nb, uint64_t seed, uint32_t refresh,
                             int32_t* table, hipStream_t st);
-int launch_audit(const gd_problem* p, const gd_particles* s, gd_interval* iv, void* ws, const Layout& L, hipStream_t st);
 size_t sample_table_bytes(int32_t nslot);
 int max_table_slots();
 int launch_sample_table(void* table, int32_t nslot, int32_t k, int32_t rates_fp32, hipStream_t st,
@@ -62,9 +60,10 @@ int launch_publish_group(const gd_particles* s, int64_t lo, int64_t hi, int64_t*
                          hipStream_t st);
 int launch_diffuse(const gd_problem* p, const gd_particles* s, double dt, uint64_t seed, uint32_t step,
                    hipStream_t st);
-const double* launch_part_fold(const double* part, void* ws, const Layout& L, hipStream_t st);
-void launch_bin_reduce(int mode, const double* msnap, const double* M, const double* va, const double* vb, int64_t n,
-                       double* part, void* ws, hipStream_t st);
+void launch_plan(const gd_problem* p, const double* msnap, const double* M, const double* a, const double* b,
+                 int64_t n, gd_interval* iv, void* ws, const Layout& L, hipStream_t st);
+void launch_audit(const gd_problem* p, const double* msnap, const double* M, const double* mnew, int64_t n,
+                  gd_interval* iv, void* ws, const Layout& L, hipStream_t st);
 
 // ---------------------------------------------------------------------------
 // Many runs stepped as one (gd_many_*): each stage of an interval is one
@@ -164,7 +163,7 @@ void many_sort(ManyBuilder& B, const std::vector<ManyRun>& R);
 void many_knn(ManyBuilder& B, const std::vector<ManyRun>& R);
 void many_rates(ManyBuilder& B, const std::vector<ManyRun>& R, bool own_snapshot = true);
 void many_sample(ManyBuilder& B, const std::vector<ManyRun>& R);
-void many_audit_sums(ManyBuilder& B, const std::vector<ManyRun>& R);
+void many_audit(ManyBuilder& B, const std::vector<ManyRun>& R);
 void many_snapshot(ManyBuilder& B, const gd_problem* p, const gd_particles* s, double4* snap);
 void many_push(ManyBuilder& B, const std::vector<ManyRun>& R);
 

@@ -929,20 +929,6 @@ __device__ __forceinline__ void KnnQuery<PER>::body(const Args& A, Blk B)
 }
 
 // ---------------------------------------------------------------------------
-struct CopyNaArgs {
-    const WsHeader* h;
-    int32_t* out;
-};
-
-struct CopyNa {
-    using Args = CopyNaArgs;
-    static constexpr int kThreads = 64;
-    static __device__ __forceinline__ void body(const Args& A, Blk)
-    {
-        if (threadIdx.x == 0) *A.out = A.h->n_active;
-    }
-};
-
 struct KnnSetup {
     TreeLevels T;
     Periodicity P;
@@ -1138,13 +1124,6 @@ void many_knn(ManyBuilder& B, const std::vector<ManyRun>& R)
             else B.add<KnnQuery<false>>(qa, nb);
         }
     }
-    // the active counts, for the runs that ask for them
-    std::vector<CopyNaArgs> na(nr);
-    for (size_t r = 0; r < nr; ++r) {
-        na[r] = CopyNaArgs{S[r].A.h, R[r].nb.n_active};
-        nb[r] = R[r].nb.n_active ? 1 : 0;
-    }
-    B.add<CopyNa>(na, nb);
 }
 
 }  // namespace gd

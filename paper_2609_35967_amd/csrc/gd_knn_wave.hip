@@ -60,12 +60,6 @@ struct WaveLds {
 __device__ inline uint64_t d2_key(double d2) { return uint64_t(__double_as_longlong(d2)); }
 __device__ inline uint64_t lanes_below(int lane) { return (uint64_t(1) << lane) - 1; }
 
-__device__ inline uint64_t readlane_u64(uint64_t x, int l)
-{
-    return (uint64_t(uint32_t(__builtin_amdgcn_readlane(int(x >> 32), l))) << 32) |
-           uint32_t(__builtin_amdgcn_readlane(int(x), l));
-}
-
 // The need-th smallest (key, slot) of the list's n >= need >= 1 pairs, whose
 // keys are d^2 <= R2: a histogram of d^2, linear over [0, R2], finds the bin
 // that holds it; that bin's pairs (about n / kSelBins of them) are ranked one

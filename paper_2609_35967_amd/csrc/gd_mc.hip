@@ -1,5 +1,5 @@
 // gd_mc.hip -- Monte Carlo sampling of collision events against the frozen
-// neighbourhood (Sect. 2.5.3) and the post-interval audit.
+// neighbourhood (Sect. 2.5.3).  The post-interval audit is in gd_rates.hip.
 //
 // One lane per particle.  The particle draws waiting times
 // dt_w = -ln(U_w)/lambda*_i (Gillespie); an event happens iff dt_w fits in the
@@ -11,10 +11,6 @@
 // (the same function of the same inputs), so particles without events never
 // evaluate their pairs here.  Random numbers: Philox4x32-10 keyed by the seed,
 // counters (id, interval, event, 0/1); every event uses both calls.
-//
-// Audit (a reading: the paper names what the audit monitors, not its rule):
-// per merged controller bin the mass-weighted mean realised |ln(s'/s)|; if the
-// largest exceeds 2 eps C, C halves (floor 0.25), else C grows by 1.25 (cap 1).
 #include "gd_common.hpp"
 #include "gd_internal.hpp"
 #include "gd_physics.hpp"
@@ -700,90 +696,6 @@ __global__ __launch_bounds__(256) void k_mc_heavy_batch(char* table, int32_t nbo
 }
 
 // ---------------------------------------------------------------------------
-constexpr int kAuditGroups = 8;  // block-partial groups summed in parallel
-
-struct AuditArgs {
-    DevProblem P;
-    const double* part;
-    int nblk;
-    gd_interval* iv;
-    WsHeader* h;
-};
-
-struct Audit {
-    using Args = AuditArgs;
-    static constexpr int kThreads = kAuditGroups * kNBin;
-    static __device__ __forceinline__ void body(const Args& A, Blk B);
-};
-
-__global__ __launch_bounds__(kAuditGroups * kNBin) void k_audit(AuditArgs A)
-{
-    Audit::body(A, Blk{0, 1});
-}
-
-__device__ __forceinline__ void Audit::body(const Args& A, Blk)
-{
-    const DevProblem& P = A.P;
-    const double* __restrict__ part = A.part;
-    const int nblk = A.nblk;
-    gd_interval* iv = A.iv;
-    WsHeader* h = A.h;
-    __shared__ double sh[kAuditGroups][kNBin], sl[kAuditGroups][kNBin];
-    __shared__ int32_t s_grp[kNBin];
-    const int t = threadIdx.x, b = t % kNBin, gq = t / kNBin;
-    {
-        dd x{0.0, 0.0};
-#pragma unroll 4
-        for (int blk = gq; blk < nblk; blk += kAuditGroups) {
-            const double* a = part + (int64_t(blk) * kNBin + b) * 8;
-            x = dd_add(x, dd{a[1], a[2]});
-        }
-        sh[gq][b] = x.hi;
-        sl[gq][b] = x.lo;
-    }
-    if (t < kNBin) s_grp[t] = h->group_of[t];
-    __syncthreads();
-    if (t < kNBin) {  // the groups combined in a fixed order
-        dd x{sh[0][t], sl[0][t]};
-        for (int g = 1; g < kAuditGroups; ++g) x = dd_add(x, dd{sh[g][t], sl[g][t]});
-        sh[0][t] = x.hi;
-        sl[0][t] = x.lo;
-    }
-    __syncthreads();
-    if (t != 0) return;
-    // groups are ascending runs of bins: one pass, each group's bins added in order
-    double worst = 0.0;
-    int g = -1;
-    dd s{0.0, 0.0};
-    auto close = [&]() {
-        if (g >= 0 && h->gM[g] > 0.0) {
-            const double r = s.hi / h->gM[g];
-            if (r > worst) worst = r;
-        }
-    };
-    for (int bb = 0; bb < kNBin; ++bb) {
-        const int gb = s_grp[bb];
-        if (gb < 0) continue;
-        if (gb != g) {
-            close();
-            g = gb;
-            s = dd{0.0, 0.0};
-        }
-        s = dd_add(s, dd{sh[0][bb], sl[0][bb]});
-    }
-    close();
-    const double Cf = iv->C;
-    const double thr = 2.0 * P.eps * Cf;
-    iv->C = (worst > thr) ? fmax(0.25, 0.5 * Cf) : fmin(1.0, 1.25 * Cf);
-    iv->audit_worst = worst;
-    int64_t tk = iv->ticks + iv->exe_ticks;
-    if (tk >= kTicks) tk = 0;
-    iv->ticks = tk;
-    iv->time = iv->time + iv->dt_exe;
-    iv->n_intervals = iv->n_intervals + 1;
-    iv->n_events = int64_t(*reinterpret_cast<const unsigned long long*>(&h->scratch[0]));
-}
-
 __global__ void k_interval_init(gd_interval* iv, double dt_coll)
 {
     if (threadIdx.x != 0) return;
@@ -851,9 +763,6 @@ static McArgs mc_args(const gd_problem* p, const gd_particles* s, const gd_neigh
 static bool launch_screen(const McArgs& A, const gd_problem* p, hipStream_t st)
 {
     const int g = int((A.P.n + 255) / 256);
-    static_assert(offsetof(WsHeader, mc_next) == offsetof(WsHeader, mc_seg) + kXcd * sizeof(int32_t),
-                  "the segment counts and the next counter are cleared together");
-    launch_fill_i32(A.list_seg, kXcd + 1, 0, st);
     if (p->k > 64) {  // no prefix registers: straight to the wavefront-per-particle pass
         hipLaunchKernelGGL(k_mc_screen<true>, dim3(g), dim3(256), 0, st, A);
         return false;
@@ -909,18 +818,6 @@ static void launch_deferred(const McArgs& A, const gd_problem* p, hipStream_t st
     else launch_heavy<false>(A, p->k, st);
 }
 
-int launch_audit(const gd_problem* p, const gd_particles* s, gd_interval* iv, void* ws, const Layout& L, hipStream_t st)
-{
-    WsHeader* h = at<WsHeader>(ws, L.hdr);
-    double* part = at<double>(ws, L.part);
-    prof_mark(GD_PROF_AUDIT, 0, st);
-    launch_bin_reduce(1, s->m[s->cur], s->M, s->m[s->cur ^ 1], nullptr, p->n, part, ws, st);
-    const double* folded = launch_part_fold(part, ws, L, st);
-    hipLaunchKernelGGL(k_audit, dim3(1), dim3(kAuditGroups * kNBin), 0, st, AuditArgs{to_dev(p), folded, 1, iv, h});
-    prof_mark(GD_PROF_AUDIT, 1, st);
-    return 0;
-}
-
 int launch_sample(const gd_problem* p, const gd_particles* s, const gd_neighbors* nb, gd_interval* iv,
                   const double* lam_i, uint64_t seed, uint32_t interval, bool interval_on_device, int32_t* n_events, int32_t* log,
                   int32_t log_cap, void* ws, const Layout& L, hipStream_t st, void* table, int32_t slot)
@@ -930,6 +827,9 @@ int launch_sample(const gd_problem* p, const gd_particles* s, const gd_neighbors
     // slot, so no chain starts early)
     if (!table) A.early_events = kEarlyEvents;
     prof_mark(GD_PROF_MC, 0, st);
+    // (the list's segment counts are cleared by the plan and by every audit;
+    // a run of the table form may sample again before its audit)
+    if (table) launch_fill_i32(A.list_seg, kXcd + 1, 0, st);
     if (p->n > 0) launch_first(A, p, st);
     if (table) {
         // deferred particles are left to the launch over the whole table
@@ -940,7 +840,8 @@ int launch_sample(const gd_problem* p, const gd_particles* s, const gd_neighbors
     }
     launch_deferred(A, p, st);
     prof_mark(GD_PROF_MC, 1, st);
-    return launch_audit(p, s, iv, ws, L, st);
+    launch_audit(p, s->m[s->cur], s->M, s->m[s->cur ^ 1], p->n, iv, ws, L, st);
+    return 0;
 }
 
 // Sampling and audit of the slots [lo, hi) only (one spatial group); the
@@ -967,15 +868,7 @@ int launch_sample_group(const gd_problem* p, const gd_particles* s, const gd_nei
     if (cnt > 0) launch_first(A, p, st);
     launch_deferred(A, p, st);
     prof_mark(GD_PROF_MC, 1, st);
-    WsHeader* h = at<WsHeader>(ws, L.hdr);
-    double* part = at<double>(ws, L.part);
-    DevProblem P = to_dev(p);
-    P.n = cnt;
-    prof_mark(GD_PROF_AUDIT, 0, st);
-    launch_bin_reduce(1, s->m[s->cur] + lo, s->M + lo, s->m[s->cur ^ 1] + lo, nullptr, cnt, part, ws, st);
-    const double* folded = launch_part_fold(part, ws, L, st);
-    hipLaunchKernelGGL(k_audit, dim3(1), dim3(kAuditGroups * kNBin), 0, st, AuditArgs{P, folded, 1, iv, h});
-    prof_mark(GD_PROF_AUDIT, 1, st);
+    launch_audit(p, s->m[s->cur] + lo, s->M + lo, s->m[s->cur ^ 1] + lo, cnt, iv, ws, L, st);
     return 0;
 }
 
@@ -1005,11 +898,9 @@ int launch_sample_table(void* table, int32_t nslot, int32_t k, int32_t rates_fp3
     return 0;
 }
 
-// Sampling and audit of every run as stages of one interval: clear the list
-// counters, the screen, the per-lane event pass (k <= 64), the pass over the
+// Sampling and audit of every run as stages of one interval: the screen, the per-lane event pass (k <= 64), the pass over the
 // deferred particles of every run (one launch through a table of the runs'
-// arguments, shaped for the largest k), then the audit's bin sums, fold and
-// rule.  Draws take the interval index from each run's interval state.
+// arguments, shaped for the largest k), then the audit.  Draws take the interval index from each run's interval state.
 static void many_table_step(char* base, const ManyStep& s, hipStream_t st)
 {
     launch_sample_table(base + s.tab, int32_t(s.a0), int32_t(s.a1 >> 1), int32_t(s.a1 & 1), st, int32_t(s.nblocks));
@@ -1019,8 +910,7 @@ void many_sample(ManyBuilder& B, const std::vector<ManyRun>& R)
 {
     const size_t nr = R.size();
     std::vector<McArgs> ma(nr);
-    std::vector<ClearArgs> clr(nr);
-    std::vector<int64_t> one(nr, 1), nb(nr), scr_d(nr), scr_l(nr);
+    std::vector<int64_t> nb(nr), scr_d(nr), scr_l(nr);
     int kmax = 1, f32 = 0;
     for (size_t r = 0; r < nr; ++r) {
         const ManyRun& x = R[r];
@@ -1029,14 +919,12 @@ void many_sample(ManyBuilder& B, const std::vector<ManyRun>& R)
         if (x.n_all >= 0) ma[r].n_all = x.n_all;
         ma[r].interval_at = x.interval_at;
         ma[r].active = B.active ? B.active + r : nullptr;
-        clr[r] = ClearArgs{ma[r].list_seg, kXcd + 1, nullptr, 0};
         nb[r] = cdiv(x.p.n, 256);
         scr_d[r] = x.p.k > 64 ? nb[r] : 0;
         scr_l[r] = x.p.k > 64 ? 0 : nb[r];
         kmax = std::max(kmax, int(x.p.k));
         f32 = x.p.rates_fp32 ? 1 : 0;
     }
-    B.add<ClearCounters>(clr, one);
     B.add<McScreen<true>>(ma, scr_d);
     B.add<McScreen<false>>(ma, scr_l);
     for (int cls = 0; cls < 2; ++cls) {
@@ -1067,13 +955,7 @@ void many_sample(ManyBuilder& B, const std::vector<ManyRun>& R)
     const size_t tab = B.put_vec(table);
     ManyStep st{&many_table_step, tab, 0, 0, B.tune.heavy_blocks, int64_t(nr), int64_t(kmax) * 2 + f32};
     B.steps.push_back(st);
-    many_audit_sums(B, R);
-    std::vector<AuditArgs> au(nr);
-    for (size_t r = 0; r < nr; ++r) {
-        const ManyRun& x = R[r];
-        au[r] = AuditArgs{to_dev(&x.p), at<double>(x.ws, x.L.red), 1, x.iv, at<WsHeader>(x.ws, x.L.hdr)};
-    }
-    B.add<Audit>(au, one);
+    many_audit(B, R);
 }
 
 }  // namespace gd

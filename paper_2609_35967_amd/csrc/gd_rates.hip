@@ -5,10 +5,11 @@
 //                count N_j = M_j/m_j (the frozen properties neighbours read)
 //  k_rates       one lane per particle: lambda*_ij over its slots in slot order,
 //                lambda*_i, controller moments a_i = sum rate <J>, b_i = sum rate <J^2>
-//  k_bin_reduce  per-block sums over ilogb(m) bins in double-double, grouped per
-//                wavefront with ballots (deterministic order)
-//  k_plan        merge bins, A_b, B_b, dt_req, dyadic dt_exe into the interval
-//                state (one block)
+//  k_reduce      per-block sums over ilogb(m) bins in double-double, grouped per
+//                wavefront with ballots (deterministic order); the block that
+//                ends last folds the blocks' sums and runs the plan (merged
+//                bins, A_b, B_b, dt_req, dyadic dt_exe into the interval
+//                state) or, after sampling, the audit
 #include "gd_common.hpp"
 #include "gd_internal.hpp"
 #include "gd_physics.hpp"
@@ -211,20 +212,26 @@ __device__ __forceinline__ void RatesF32::body(const Args& A, Blk B)
 }
 
 // ---------------------------------------------------------------------------
-// Per-block bin sums.  mode 0 (plan): count, M, M a, M b over bin(m_snap).
-// mode 1 (audit): M |ln(m_new/m_snap)|/3 over bin(m_snap).
-// part[(blk * kNBin + bin) * 8 + f]: f = 0 count, (1,2) (3,4) (5,6) dd values.
-constexpr int kRedWaves = 8;  // wavefronts per bin-reduction block
+// Bin sums of the controller.  Mode 0 (plan): count, M, M a, M b over
+// bin(m_snap).  Mode 1 (audit): M |ln(m_new/m_snap)|/3 over bin(m_snap).
+// part[(blk * kNBin + bin) * 8 + f]: f = 0 count, (1,2) (3,4) (5,6) dd values,
+// written for the bins of the block's mask (mask[2 blk], mask[2 blk + 1]).
+// One launch each: the fold over the blocks and the rule were launches of
+// their own (4.7 and 10-24 us, the rule one thread's walk over the bins).
+constexpr int kRedWaves = 8;  // wavefronts per block
 
-struct BinArgs {
-    int mode;
+struct ReduceArgs {
     const double* msnap;
     const double* M;
     const double* va;
     const double* vb;
     int64_t n;
     double* part;
-    void* ws;
+    uint64_t* mask;
+    gd_interval* iv;
+    WsHeader* h;
+    double eps, dt_fn_max;
+    int32_t nbin_min;
 };
 
 // One step of a segmented inclusive double-double scan over the wavefront:
@@ -257,27 +264,186 @@ __device__ inline void seg_scan(dd (&v)[NV], int id)
     for (int u = 0; u < NV; ++u) seg_step<0x143, 0xc>(v[u], id);
 }
 
-struct BinReduce {
-    using Args = BinArgs;
+template <int MODE>
+struct Reduce {
+    using Args = ReduceArgs;
     static constexpr int kThreads = kRedWaves * kWave;
     static __device__ __forceinline__ void body(const Args& A, Blk B);
 };
 
-__global__ __launch_bounds__(kRedWaves * kWave) void k_bin_reduce(BinArgs A)
+template <int MODE>
+__global__ __launch_bounds__(kRedWaves * kWave) void k_reduce(ReduceArgs A)
 {
-    BinReduce::body(A, Blk{int64_t(blockIdx.x), int64_t(gridDim.x)});
+    Reduce<MODE>::body(A, Blk{int64_t(blockIdx.x), int64_t(gridDim.x)});
 }
 
-__device__ __forceinline__ void BinReduce::body(const Args& A, Blk B)
+// the folded sums of a bin, and the bins that hold particles
+using BinRow = double[7];
+
+__device__ inline bool in_mask(uint64_t m0, uint64_t m1, int b) { return ((b < 64 ? m0 : m1) >> (b & 63)) & 1u; }
+
+// Plan (Sect. 2.5.3): bins merged in ascending order until each group holds
+// >= nbin_min particles (a short last group joins the previous one);
+// A_b = sum M a/sum M, B_b = sum M b/sum M;
+// dt_req = min(dt_remain, dt_fn_max, eps C/A_b, (eps C)^2/B_b);
+// dt_exe = dt_coll 2^-n, the largest aligned dyadic fraction <= dt_req.
+// One wavefront: the merge walks the bins that hold particles, their counts
+// in registers; then each lane sums its groups' bins in ascending order.
+__device__ inline void plan_rule(const ReduceArgs& A, const BinRow* row, uint64_t m0, uint64_t m1, int lane,
+                                 int32_t (&s_first)[kNBin], int32_t (&s_last)[kNBin])
 {
-    const int mode = A.mode;
+    gd_interval* iv = A.iv;
+    WsHeader* h = A.h;
+    const double dt_coll = iv->dt_coll;
+    const double Cf = iv->C;
+    const int64_t ticks = iv->ticks;
+    const double c0 = row[lane][0], c1 = row[lane + 64][0];
+    int ng = 0, last = -1;
+    double acc = 0.0;
+    bool open = false;
+    int g0 = -1, g1 = -1;  // the groups of bins lane and lane + 64
+    for (int half = 0; half < 2; ++half) {
+        for (uint64_t m = half ? m1 : m0; m; m &= m - 1) {
+            const int l = __ffsll((unsigned long long)m) - 1, bb = l + 64 * half;
+            const double c = readlane_d(half ? c1 : c0, l);
+            if (!open) {
+                open = true;
+                acc = 0.0;
+                if (lane == 0) s_first[ng] = bb;
+            }
+            last = bb;
+            acc = acc + c;
+            if (half == 0 && lane == l) g0 = ng;
+            if (half == 1 && lane == l) g1 = ng;
+            if (acc >= double(A.nbin_min)) {
+                if (lane == 0) s_last[ng] = bb;
+                ++ng;
+                open = false;
+            }
+        }
+    }
+    if (open) {  // a short tail joins the previous group, or is the only one
+        if (ng > 0) {
+            g0 = g0 == ng ? ng - 1 : g0;
+            g1 = g1 == ng ? ng - 1 : g1;
+        } else {
+            ng = 1;
+        }
+        if (lane == 0) s_last[ng - 1] = last;
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
+    const double eC = A.eps * Cf;
+    double req = INFINITY;
+    for (int g = lane; g < kNBin; g += kWave) {
+        double gM = 0.0;
+        if (g < ng) {
+            dd x[3] = {dd{0.0, 0.0}, dd{0.0, 0.0}, dd{0.0, 0.0}};
+            for (int bb = s_first[g]; bb <= s_last[g]; ++bb) {
+                if (!in_mask(m0, m1, bb)) continue;
+#pragma unroll
+                for (int v = 0; v < 3; ++v) x[v] = dd_add(x[v], dd{row[bb][1 + 2 * v], row[bb][2 + 2 * v]});
+            }
+            gM = x[0].hi;
+            const double A_ = gM > 0.0 ? x[1].hi / gM : 0.0;
+            const double B_ = gM > 0.0 ? x[2].hi / gM : 0.0;
+            if (A_ > 0.0) {
+                const double tt = eC / A_;
+                if (tt < req) req = tt;
+            }
+            if (B_ > 0.0) {
+                const double tt = (eC * eC) / B_;
+                if (tt < req) req = tt;
+            }
+        }
+        h->gM[g] = gM;
+    }
+    h->group_of[lane] = g0;
+    h->group_of[lane + 64] = g1;
+    req = wave_min_d(req);
+    const double tick = ldexp(dt_coll, -30);
+    const double rem = double(kTicks - ticks) * tick;
+    // (rem first: a comparison with a NaN on either side keeps the other)
+    double r = rem;
+    if (A.dt_fn_max < r) r = A.dt_fn_max;
+    if (req < r) r = req;
+    // lane nh tests the fraction 2^-nh; the first that fits is the largest
+    const int64_t mine = kTicks >> (lane <= 30 ? lane : 30);
+    const uint64_t fits = __ballot(lane <= 30 && double(mine) * tick <= r && (ticks & (mine - 1)) == 0);
+    if (lane != 0) return;
+    if (!fits) atomicOr(&h->status, GD_DEV_TICK_FLOOR);
+    const int64_t size = fits ? kTicks >> (__ffsll((unsigned long long)fits) - 1) : 1;
+    h->n_groups = ng;
+    iv->dt_req = r;
+    iv->dt_exe = double(size) * tick;
+    iv->exe_ticks = size;
+    iv->n_groups = ng;
+    h->scratch[0] = 0.0;  // event counter of the coming interval
+    h->heavy_n = 0;       // and the sampling's deferred particles
+    h->heavy_next = 0;
+    h->heavy_n0 = 0;
+    h->heavy_next0 = 0;
+}
+
+// Audit (a reading: the paper names what the audit monitors, not its rule):
+// per merged controller bin the mass-weighted mean realised |ln(s'/s)|; if the
+// largest exceeds 2 eps C, C halves (floor 0.25), else C grows by 1.25 (cap 1).
+// The groups are the plan's, ascending runs of bins.
+__device__ inline void audit_rule(const ReduceArgs& A, const BinRow* row, uint64_t m0, uint64_t m1, int lane,
+                                  int32_t (&s_first)[kNBin], int32_t (&s_last)[kNBin])
+{
+    gd_interval* iv = A.iv;
+    WsHeader* h = A.h;
+    const int32_t g0 = h->group_of[lane], g1 = h->group_of[lane + 64];
+    for (int g = lane; g < kNBin; g += kWave) {
+        s_first[g] = kNBin;
+        s_last[g] = -1;
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
+    if (g0 >= 0) {
+        atomicMin(&s_first[g0], lane);
+        atomicMax(&s_last[g0], lane);
+    }
+    if (g1 >= 0) {
+        atomicMin(&s_first[g1], lane + 64);
+        atomicMax(&s_last[g1], lane + 64);
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
+    double worst = 0.0;
+    for (int g = lane; g < kNBin; g += kWave) {
+        const double gM = h->gM[g];
+        dd x{0.0, 0.0};
+        for (int bb = s_first[g]; bb <= s_last[g]; ++bb)
+            if (in_mask(m0, m1, bb)) x = dd_add(x, dd{row[bb][1], row[bb][2]});
+        if (s_last[g] >= 0 && gM > 0.0) {
+            const double r = x.hi / gM;
+            if (r > worst) worst = r;
+        }
+    }
+    worst = wave_max_d(worst);
+    if (lane != 0) return;
+    const double Cf = iv->C;
+    const double thr = 2.0 * A.eps * Cf;
+    iv->C = (worst > thr) ? fmax(0.25, 0.5 * Cf) : fmin(1.0, 1.25 * Cf);
+    iv->audit_worst = worst;
+    int64_t tk = iv->ticks + iv->exe_ticks;
+    if (tk >= kTicks) tk = 0;
+    iv->ticks = tk;
+    iv->time = iv->time + iv->dt_exe;
+    iv->n_intervals = iv->n_intervals + 1;
+    iv->n_events = int64_t(*reinterpret_cast<const unsigned long long*>(&h->scratch[0]));
+}
+
+template <int MODE>
+__device__ __forceinline__ void Reduce<MODE>::body(const Args& A, Blk B)
+{
+    constexpr int mode = MODE;
     const double* __restrict__ msnap = A.msnap;
     const double* __restrict__ M = A.M;
     const double* __restrict__ va = A.va;
     const double* __restrict__ vb = A.vb;
     const int64_t n = A.n;
-    double* __restrict__ part = A.part;
-    void* ws = A.ws;
+    double* part = A.part;
+    WsHeader* h = A.h;
     __shared__ double acc[kRedWaves][kNBin][7];
     // a row of many bins in bin order: bin, run length and the three values
     // of each lane, per wavefront
@@ -406,272 +572,162 @@ __device__ __forceinline__ void BinReduce::body(const Args& A, Blk B)
         }
         cur = nxt;
     }
-    if (__ballot(range_bad) && lane == 0) set_status(ws, GD_DEV_MASS_RANGE);
+    if (__ballot(range_bad) && lane == 0) atomicOr(&h->status, GD_DEV_MASS_RANGE);
     __syncthreads();
-    for (int bin = t; bin < kNBin; bin += kRedWaves * kWave) {
-        double* out = part + (B.id * kNBin + bin) * 8;
+    // the block's sums per bin, in acc[0][bin], and the bins that hold some
+    __shared__ uint64_t s_m[2];
+    __shared__ int32_t s_last_blk;
+    BinRow* row = acc[0];
+    if (t < kNBin) {
         double cnt = 0.0;
         dd x0{0.0, 0.0}, x1{0.0, 0.0}, x2{0.0, 0.0};
         for (int ww = 0; ww < kRedWaves; ++ww) {
-            const double* a = acc[ww][bin];
+            const double* a = acc[ww][t];
             cnt += a[0];
             x0 = dd_add(x0, dd{a[1], a[2]});
-            x1 = dd_add(x1, dd{a[3], a[4]});
-            x2 = dd_add(x2, dd{a[5], a[6]});
-        }
-        out[0] = cnt;
-        out[1] = x0.hi;
-        out[2] = x0.lo;
-        out[3] = x1.hi;
-        out[4] = x1.lo;
-        out[5] = x2.hi;
-        out[6] = x2.lo;
-    }
-}
-
-// ---------------------------------------------------------------------------
-// Plan (Sect. 2.5.3): bins merged in ascending order until each holds >=
-// nbin_min particles (a short last group joins the previous one);
-// A_b = sum M a/sum M, B_b = sum M b/sum M;
-// dt_req = min(dt_remain, dt_fn_max, eps C/A_b, (eps C)^2/B_b);
-// dt_exe = dt_coll 2^-n, the largest aligned dyadic fraction <= dt_req.
-constexpr int kPlanGroups = 8;  // block-partial groups summed in parallel
-
-struct PlanArgs {
-    DevProblem P;
-    const double* part;
-    int nblk;
-    gd_interval* iv;
-    WsHeader* h;
-    void* ws;
-};
-
-struct Plan {
-    using Args = PlanArgs;
-    static constexpr int kThreads = kPlanGroups * kNBin;
-    static __device__ __forceinline__ void body(const Args& A, Blk B);
-};
-
-__global__ __launch_bounds__(kPlanGroups * kNBin) void k_plan(PlanArgs A)
-{
-    Plan::body(A, Blk{0, 1});
-}
-
-__device__ __forceinline__ void Plan::body(const Args& A, Blk)
-{
-    const DevProblem& P = A.P;
-    const double* __restrict__ part = A.part;
-    const int nblk = A.nblk;
-    gd_interval* iv = A.iv;
-    WsHeader* h = A.h;
-    __shared__ double pc[kPlanGroups][kNBin];
-    __shared__ double ph[kPlanGroups][3][kNBin], pl[kPlanGroups][3][kNBin];
-    __shared__ int32_t s_grp[kNBin];
-    __shared__ int32_t s_ng;
-    const int t = threadIdx.x, b = t % kNBin, gq = t / kNBin;
-    {
-        double c = 0.0;
-        dd x0{0.0, 0.0}, x1{0.0, 0.0}, x2{0.0, 0.0};
-#pragma unroll 4
-        for (int blk = gq; blk < nblk; blk += kPlanGroups) {
-            const double* a = part + (int64_t(blk) * kNBin + b) * 8;
-            c += a[0];
-            x0 = dd_add(x0, dd{a[1], a[2]});
-            x1 = dd_add(x1, dd{a[3], a[4]});
-            x2 = dd_add(x2, dd{a[5], a[6]});
-        }
-        pc[gq][b] = c;
-        ph[gq][0][b] = x0.hi;
-        pl[gq][0][b] = x0.lo;
-        ph[gq][1][b] = x1.hi;
-        pl[gq][1][b] = x1.lo;
-        ph[gq][2][b] = x2.hi;
-        pl[gq][2][b] = x2.lo;
-    }
-    __syncthreads();
-    if (t < kNBin) {  // the groups combined in a fixed order: row 0 holds the bin totals
-        double c = pc[0][t];
-        dd x[3];
-        for (int v = 0; v < 3; ++v) x[v] = dd{ph[0][v][t], pl[0][v][t]};
-        for (int g = 1; g < kPlanGroups; ++g) {
-            c += pc[g][t];
-            for (int v = 0; v < 3; ++v) x[v] = dd_add(x[v], dd{ph[g][v][t], pl[g][v][t]});
-        }
-        pc[0][t] = c;
-        for (int v = 0; v < 3; ++v) {
-            ph[0][v][t] = x[v].hi;
-            pl[0][v][t] = x[v].lo;
-        }
-    }
-    __syncthreads();
-    if (t == 0) {
-        // merge rule in one ascending pass: a group opens at a non-empty bin
-        // and closes once it holds nbin_min particles; a short open tail
-        // joins the previous group (or is the only group).  Each group's sums
-        // add its bins in ascending order.
-        const double dt_coll = iv->dt_coll;
-        const double Cf = iv->C;
-        const int64_t ticks = iv->ticks;
-        const double tick = ldexp(dt_coll, -30);
-        double req = double(kTicks - ticks) * tick;
-        if (P.dt_fn_max < req) req = P.dt_fn_max;
-        const double eC = P.eps * Cf;
-        auto finalize = [&](const dd (&x)[3], int g) {
-            h->gM[g] = x[0].hi;
-            const double A_ = x[0].hi > 0.0 ? x[1].hi / x[0].hi : 0.0;
-            const double B_ = x[0].hi > 0.0 ? x[2].hi / x[0].hi : 0.0;
-            if (A_ > 0.0) {
-                const double tt = eC / A_;
-                if (tt < req) req = tt;
-            }
-            if (B_ > 0.0) {
-                const double tt = (eC * eC) / B_;
-                if (tt < req) req = tt;
-            }
-        };
-        int ng = 0, tail = -1;
-        double acc = 0.0;
-        bool open = false, has_pend = false;
-        dd cur[3], pend[3];
-        for (int bb = 0; bb < kNBin; ++bb) {
-            s_grp[bb] = -1;
-            if (pc[0][bb] == 0.0) continue;
-            if (!open) {
-                open = true;
-                acc = 0.0;
-                tail = bb;
-                for (int v = 0; v < 3; ++v) cur[v] = dd{0.0, 0.0};
-            }
-            s_grp[bb] = ng;
-            acc += pc[0][bb];
-            for (int v = 0; v < 3; ++v) cur[v] = dd_add(cur[v], dd{ph[0][v][bb], pl[0][v][bb]});
-            if (acc >= double(P.nbin_min)) {
-                if (has_pend) finalize(pend, ng - 1);
-                for (int v = 0; v < 3; ++v) pend[v] = cur[v];
-                has_pend = true;
-                ++ng;
-                open = false;
+            if (mode == 0) {
+                x1 = dd_add(x1, dd{a[3], a[4]});
+                x2 = dd_add(x2, dd{a[5], a[6]});
             }
         }
-        if (open) {
-            if (has_pend) {
-                for (int bb = tail; bb < kNBin; ++bb) {
-                    if (pc[0][bb] == 0.0) continue;
-                    s_grp[bb] = ng - 1;
-                    for (int v = 0; v < 3; ++v) pend[v] = dd_add(pend[v], dd{ph[0][v][bb], pl[0][v][bb]});
-                }
-            } else {
-                for (int v = 0; v < 3; ++v) pend[v] = cur[v];
-                has_pend = true;
-                ng = 1;
-            }
-        }
-        if (has_pend) finalize(pend, ng - 1);
-        int64_t size = kTicks;
-        int nh = 0;
-        for (nh = 0; nh <= 30; ++nh) {
-            size = kTicks >> nh;
-            if (double(size) * tick <= req && (ticks % size) == 0) break;
-        }
-        if (nh > 30) {
-            size = 1;
-            atomicOr(&h->status, GD_DEV_TICK_FLOOR);
-        }
-        h->n_groups = ng;
-        iv->dt_req = req;
-        iv->dt_exe = double(size) * tick;
-        iv->exe_ticks = size;
-        iv->n_groups = ng;
-        h->scratch[0] = 0.0;  // event counter of the coming interval
-        h->heavy_n = 0;       // and the sampling's deferred particles
-        h->heavy_next = 0;
-        h->heavy_n0 = 0;
-        h->heavy_next0 = 0;
-        s_ng = ng;
-    }
-    __syncthreads();
-    if (t < kNBin) {
-        h->group_of[t] = s_grp[t];
-        if (t >= s_ng) h->gM[t] = 0.0;
-    }
-}
-
-// The kRedBlocks block partials of each bin summed as a tree, one block per
-// bin, into one row per bin (same layout as a block's partials): the plan and
-// the audit then read a single row instead of looping over the blocks.
-struct FoldArgs {
-    const double* part;
-    double* out;
-    int nblk;  // partial rows written (the rest count as zero)
-};
-
-struct PartFold {
-    using Args = FoldArgs;
-    static constexpr int kThreads = kRedBlocks;
-    static __device__ __forceinline__ void body(const Args& A, Blk B);
-};
-
-__global__ __launch_bounds__(kRedBlocks) void k_part_fold(FoldArgs A)
-{
-    PartFold::body(A, Blk{int64_t(blockIdx.x), int64_t(gridDim.x)});
-}
-
-__device__ __forceinline__ void PartFold::body(const Args& A, Blk B)
-{
-    __shared__ double c[kRedBlocks];
-    __shared__ double hi[3][kRedBlocks], lo[3][kRedBlocks];
-    const int b = int(B.id), t = threadIdx.x;
-    double* __restrict__ out = A.out;
-    const bool have = t < A.nblk;
-    const double* a = A.part + (int64_t(have ? t : 0) * kNBin + b) * 8;
-    c[t] = have ? a[0] : 0.0;
+        const double v[7] = {cnt, x0.hi, x0.lo, x1.hi, x1.lo, x2.hi, x2.lo};
+        double* out = part + (B.id * kNBin + t) * 8;
 #pragma unroll
-    for (int v = 0; v < 3; ++v) {
-        hi[v][t] = have ? a[1 + 2 * v] : 0.0;
-        lo[v][t] = have ? a[2 + 2 * v] : 0.0;
-    }
-    __syncthreads();
-    for (int w = kRedBlocks / 2; w > 0; w >>= 1) {
-        if (t < w) {
-            c[t] += c[t + w];
-#pragma unroll
-            for (int v = 0; v < 3; ++v) {
-                const dd x = dd_add(dd{hi[v][t], lo[v][t]}, dd{hi[v][t + w], lo[v][t + w]});
-                hi[v][t] = x.hi;
-                lo[v][t] = x.lo;
-            }
+        for (int f = 0; f < 7; ++f) {
+            row[t][f] = v[f];
+            if (B.n > 1 && cnt > 0.0) put_device(out + f, v[f]);
         }
+        const uint64_t m = __ballot(cnt > 0.0);
+        if (lane == 0) {
+            s_m[w] = m;
+            if (B.n > 1) put_device(A.mask + 2 * B.id + w, m);
+        }
+    }
+    if (B.n > 1) {
+        done_stores();
         __syncthreads();
-    }
-    if (t == 0) {
-        double* o = out + int64_t(b) * 8;
-        o[0] = c[0];
+        if (t == 0) s_last_blk = last_block(&h->red_done, B.n) ? 1 : 0;
+        __syncthreads();
+        if (!s_last_blk) return;
+        // fold: wavefront w takes the bins w, w + kRedWaves, ... of the union
+        // of the masks, its lanes the blocks
+        constexpr int NR = kRedBlocks / kWave;
+        uint64_t b0[NR], b1[NR], u0 = 0, u1 = 0;
 #pragma unroll
-        for (int v = 0; v < 3; ++v) {
-            o[1 + 2 * v] = hi[v][0];
-            o[2 + 2 * v] = lo[v][0];
+        for (int r = 0; r < NR; ++r) {
+            const int blk = r * kWave + lane;
+            b0[r] = blk < B.n ? A.mask[2 * blk] : 0;
+            b1[r] = blk < B.n ? A.mask[2 * blk + 1] : 0;
+            u0 |= b0[r];
+            u1 |= b1[r];
         }
-        o[7] = 0.0;
+#pragma unroll
+        for (int o = 1; o < kWave; o <<= 1) {
+            u0 |= __shfl_xor((unsigned long long)u0, o, kWave);
+            u1 |= __shfl_xor((unsigned long long)u1, o, kWave);
+        }
+        u0 = readlane_u64(u0, 0);
+        u1 = readlane_u64(u1, 0);
+        int turn = 0;
+        uint64_t left0 = u0, left1 = u1;
+        while (left0 | left1) {
+            const int bin = left0 ? __ffsll((unsigned long long)left0) - 1 : 63 + __ffsll((unsigned long long)left1);
+            if (left0) left0 &= left0 - 1;
+            else left1 &= left1 - 1;
+            const bool mine = turn == w;
+            turn = (turn + 1) & (kRedWaves - 1);
+            if (!mine) continue;
+            double cnt = 0.0;
+            dd x0{0.0, 0.0}, x1{0.0, 0.0}, x2{0.0, 0.0};
+            double v[NR][8];
+#pragma unroll
+            for (int r = 0; r < NR; ++r) {
+                const bool have = in_mask(b0[r], b1[r], bin);
+                const double2* a =
+                    reinterpret_cast<const double2*>(part + (int64_t(have ? r * kWave + lane : 0) * kNBin + bin) * 8);
+#pragma unroll
+                for (int f = 0; f < (mode == 0 ? 4 : 2); ++f) {
+                    const double2 p = a[f];
+                    v[r][2 * f] = have ? p.x : 0.0;
+                    v[r][2 * f + 1] = have ? p.y : 0.0;
+                }
+            }
+#pragma unroll
+            for (int r = 0; r < NR; ++r) {
+                cnt += v[r][0];
+                x0 = dd_add(x0, dd{v[r][1], v[r][2]});
+                if (mode == 0) {
+                    x1 = dd_add(x1, dd{v[r][3], v[r][4]});
+                    x2 = dd_add(x2, dd{v[r][5], v[r][6]});
+                }
+            }
+            if (mode == 0) wave_sum_dd3(x0, x1, x2);
+            else x0 = wave_sum_dd(x0);
+#pragma unroll
+            for (int o = 1; o < kWave; o <<= 1) cnt += shfl_xor_d(cnt, o);
+            if (lane == 0) {
+                const double o[7] = {cnt, x0.hi, x0.lo, x1.hi, x1.lo, x2.hi, x2.lo};
+#pragma unroll
+                for (int f = 0; f < 7; ++f) row[bin][f] = o[f];
+            }
+        }
+        if (t == 0) {
+            s_m[0] = u0;
+            s_m[1] = u1;
+        }
     }
+    __syncthreads();
+    if (w != 0) return;
+    __shared__ int32_t s_first[kNBin], s_last[kNBin];
+    if (mode == 0) plan_rule(A, row, s_m[0], s_m[1], lane, s_first, s_last);
+    else audit_rule(A, row, s_m[0], s_m[1], lane, s_first, s_last);
+    // the coming sampling's list of particles with events starts empty
+    if (lane <= kXcd) h->mc_seg[lane] = 0;  // (and mc_next, which follows)
 }
 
-static_assert(kNBin * 8 <= 8 * kRedBlocks, "the folded rows fit the reduction scratch");
+static_assert(offsetof(WsHeader, mc_next) == offsetof(WsHeader, mc_seg) + kXcd * sizeof(int32_t),
+              "the segment counts and the next counter are cleared together");
 
-// fold the block partials `part` into the reduction scratch of the workspace
-// (free outside the neighbour build); returns the folded rows
-const double* launch_part_fold(const double* part, void* ws, const Layout& L, hipStream_t st)
+static ReduceArgs reduce_args(const gd_problem* p, const double* msnap, const double* M, const double* va,
+                              const double* vb, int64_t n, gd_interval* iv, void* ws, const Layout& L)
 {
-    double* out = at<double>(ws, L.red);
-    hipLaunchKernelGGL(k_part_fold, dim3(kNBin), dim3(kRedBlocks), 0, st, FoldArgs{part, out, kRedBlocks});
-    return out;
+    const DevProblem P = to_dev(p);
+    ReduceArgs A{};
+    A.msnap = msnap;
+    A.M = M;
+    A.va = va;
+    A.vb = vb;
+    A.n = n;
+    A.part = at<double>(ws, L.part);
+    A.mask = at<uint64_t>(ws, L.red);  // (free outside the neighbour build)
+    A.iv = iv;
+    A.h = at<WsHeader>(ws, L.hdr);
+    A.eps = P.eps;
+    A.dt_fn_max = P.dt_fn_max;
+    A.nbin_min = P.nbin_min;
+    return A;
 }
 
-// ---------------------------------------------------------------------------
-void launch_bin_reduce(int mode, const double* msnap, const double* M, const double* va, const double* vb, int64_t n,
-                       double* part, void* ws, hipStream_t st)
+// a row of 64 particles per wavefront and block up to kRedBlocks blocks
+static int64_t reduce_blocks(int64_t n)
 {
-    hipLaunchKernelGGL(k_bin_reduce, dim3(kRedBlocks), dim3(kRedWaves * kWave), 0, st,
-                       BinArgs{mode, msnap, M, va, vb, n, part, ws});
+    return std::min<int64_t>(kRedBlocks, std::max<int64_t>(1, cdiv(n, kRedWaves * kWave)));
+}
+
+void launch_plan(const gd_problem* p, const double* msnap, const double* M, const double* a, const double* b,
+                 int64_t n, gd_interval* iv, void* ws, const Layout& L, hipStream_t st)
+{
+    hipLaunchKernelGGL(k_reduce<0>, dim3(unsigned(reduce_blocks(n))), dim3(kRedWaves * kWave), 0, st,
+                       reduce_args(p, msnap, M, a, b, n, iv, ws, L));
+}
+
+void launch_audit(const gd_problem* p, const double* msnap, const double* M, const double* mnew, int64_t n,
+                  gd_interval* iv, void* ws, const Layout& L, hipStream_t st)
+{
+    prof_mark(GD_PROF_AUDIT, 0, st);
+    hipLaunchKernelGGL(k_reduce<1>, dim3(unsigned(reduce_blocks(n))), dim3(kRedWaves * kWave), 0, st,
+                       reduce_args(p, msnap, M, mnew, nullptr, n, iv, ws, L));
+    prof_mark(GD_PROF_AUDIT, 1, st);
 }
 
 int launch_rates(const gd_problem* p, const gd_particles* s, const gd_neighbors* nb, gd_interval* iv, double* lam_i,
@@ -703,11 +759,7 @@ int launch_rates(const gd_problem* p, const gd_particles* s, const gd_neighbors*
     A.snap_own = snap;
     if (p->rates_fp32) hipLaunchKernelGGL(k_rates_f32, dim3(g), dim3(256), 0, st, A);
     else hipLaunchKernelGGL(k_rates, dim3(g), dim3(256), 0, st, A);
-    double* part = at<double>(ws, L.part);
-    launch_bin_reduce(0, m, s->M, A.a, A.b, n, part, ws, st);
-    const double* folded = launch_part_fold(part, ws, L, st);
-    hipLaunchKernelGGL(k_plan, dim3(1), dim3(kPlanGroups * kNBin), 0, st,
-                       PlanArgs{P, folded, 1, iv, at<WsHeader>(ws, L.hdr), ws});
+    launch_plan(p, m, s->M, A.a, A.b, n, iv, ws, L, st);
     prof_mark(GD_PROF_RATES, 1, st);
     return 0;
 }
@@ -774,11 +826,7 @@ int launch_rates_group(const gd_problem* p, const gd_particles* s, const gd_neig
         if (p->rates_fp32) hipLaunchKernelGGL(k_rates_f32, dim3(g), dim3(256), 0, st, A);
         else hipLaunchKernelGGL(k_rates, dim3(g), dim3(256), 0, st, A);
     }
-    double* part = at<double>(ws, L.part);
-    launch_bin_reduce(0, m + lo, s->M + lo, A.a, A.b, cnt, part, ws, st);
-    const double* folded = launch_part_fold(part, ws, L, st);
-    hipLaunchKernelGGL(k_plan, dim3(1), dim3(kPlanGroups * kNBin), 0, st,
-                       PlanArgs{P, folded, 1, iv, at<WsHeader>(ws, L.hdr), ws});
+    launch_plan(p, m + lo, s->M + lo, A.a, A.b, cnt, iv, ws, L, st);
     hipLaunchKernelGGL(k_group_clamp, dim3(1), dim3(64), 0, st, iv, int(group), int(n_groups),
                        reinterpret_cast<const unsigned long long*>(rows), sched);
     prof_mark(GD_PROF_RATES, 1, st);
@@ -786,17 +834,15 @@ int launch_rates_group(const gd_problem* p, const gd_particles* s, const gd_neig
 }
 
 // Rates and plan of every run as stages of one interval: snapshot, rates,
-// the bin sums over n / red_div blocks per run (at most kRedBlocks), their
-// fold and the plan.
+// the bin sums over n / red_div blocks per run (at most kRedBlocks) with the
+// plan.
 void many_rates(ManyBuilder& B, const std::vector<ManyRun>& R, bool own_snapshot)
 {
     const size_t nr = R.size();
     std::vector<SnapArgs> sn(nr);
     std::vector<RatesArgs> ra(nr);
-    std::vector<BinArgs> bi(nr);
-    std::vector<FoldArgs> fo(nr);
-    std::vector<PlanArgs> pl(nr);
-    std::vector<int64_t> nb(nr), nred(nr), nbin(nr, kNBin), one(nr, 1), f64(nr), f32(nr);
+    std::vector<ReduceArgs> pl(nr);
+    std::vector<int64_t> nb(nr), nred(nr), f64(nr), f32(nr);
     for (size_t r = 0; r < nr; ++r) {
         const ManyRun& x = R[r];
         const gd_problem* p = &x.p;
@@ -828,18 +874,12 @@ void many_rates(ManyBuilder& B, const std::vector<ManyRun>& R, bool own_snapshot
         f64[r] = p->rates_fp32 ? 0 : nb[r];
         f32[r] = p->rates_fp32 ? nb[r] : 0;
         nred[r] = std::min<int64_t>(kRedBlocks, std::max<int64_t>(1, cdiv(n, B.tune.red_div)));
-        double* part = at<double>(x.ws, x.L.part);
-        double* folded = at<double>(x.ws, x.L.red);
-        bi[r] = BinArgs{0, m, s->M, A.a, A.b, n, part, x.ws};
-        fo[r] = FoldArgs{part, folded, int(nred[r])};
-        pl[r] = PlanArgs{P, folded, 1, x.iv, at<WsHeader>(x.ws, x.L.hdr), x.ws};
+        pl[r] = reduce_args(p, m, s->M, A.a, A.b, n, x.iv, x.ws, x.L);
     }
     if (own_snapshot) B.add<Snapshot>(sn, nb);
     B.add<Rates>(ra, f64);
     B.add<RatesF32>(ra, f32);
-    B.add<BinReduce>(bi, nred);
-    B.add<PartFold>(fo, nbin);
-    B.add<Plan>(pl, one);
+    B.add<Reduce<0>>(pl, nred);
 }
 
 // the snapshot of a whole particle set as one step (one run; predicated by
@@ -850,25 +890,20 @@ void many_snapshot(ManyBuilder& B, const gd_problem* p, const gd_particles* s, d
     B.add<Snapshot>(sn, std::vector<int64_t>{cdiv(p->n, 256)});
 }
 
-// the audit's bin sums and their fold (mode 1 over m_snap, M, m_new), for
-// the sampling stage's audit
-void many_audit_sums(ManyBuilder& B, const std::vector<ManyRun>& R)
+// the audit of every run
+void many_audit(ManyBuilder& B, const std::vector<ManyRun>& R)
 {
     const size_t nr = R.size();
-    std::vector<BinArgs> bi(nr);
-    std::vector<FoldArgs> fo(nr);
-    std::vector<int64_t> nred(nr), nbin(nr, kNBin);
+    std::vector<ReduceArgs> au(nr);
+    std::vector<int64_t> nred(nr);
     for (size_t r = 0; r < nr; ++r) {
         const ManyRun& x = R[r];
         const gd_particles* s = &x.out;
         const int64_t n = x.p.n;
         nred[r] = std::min<int64_t>(kRedBlocks, std::max<int64_t>(1, cdiv(n, B.tune.red_div)));
-        double* part = at<double>(x.ws, x.L.part);
-        bi[r] = BinArgs{1, s->m[s->cur], s->M, s->m[s->cur ^ 1], nullptr, n, part, x.ws};
-        fo[r] = FoldArgs{part, at<double>(x.ws, x.L.red), int(nred[r])};
+        au[r] = reduce_args(&x.p, s->m[s->cur], s->M, s->m[s->cur ^ 1], nullptr, n, x.iv, x.ws, x.L);
     }
-    B.add<BinReduce>(bi, nred);
-    B.add<PartFold>(fo, nbin);
+    B.add<Reduce<1>>(au, nred);
 }
 
 }  // namespace gd

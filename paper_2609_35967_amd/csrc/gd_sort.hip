@@ -1,7 +1,7 @@
 // gd_sort.hip -- Morton order of the active particles (Sect. 2.5.1: the
 // neighbour search runs on an adaptive spatial hierarchy over the Morton
-// order).  Bounding box reduction, 30-bit keys, stable LSD radix sort of
-// (key, slot) pairs with 8-bit digits, and the gather of every state array
+// order).  Bounding box, 30-bit keys with the first digit's counts, stable
+// LSD radix sort of (key, slot) pairs with 8-bit digits, and the gather of every state array
 // into the sorted order.  All kernels are bandwidth-bound streaming passes:
 // coalesced loads of the SoA arrays, one 4-byte key and value per particle.
 #include "gd_common.hpp"
@@ -13,25 +13,32 @@
 namespace gd {
 
 // ---------------------------------------------------------------------------
-// Bounding box and active count: per-block partials, then one block combines.
+// Bounding box and active count: per-block partials, combined by the block
+// that ends last (a launch of its own took 4.6 us).  Clears the sort's
+// counts.
 struct BboxArgs {
     const double *x, *y, *z, *M;
     int64_t n;
     double* red;
+    WsHeader* h;
+    int32_t* na_out;  // the caller's copy of the active count, or null
+    uint32_t* zero;   // counts cleared for the sort
+    int64_t nzero;
 };
 
-struct BboxPartial {
+struct Bbox {
     using Args = BboxArgs;
     static constexpr int kThreads = 256;
     static __device__ __forceinline__ void body(const Args& A, Blk B);
 };
 
-__device__ __forceinline__ void BboxPartial::body(const Args& A, Blk B)
+__device__ __forceinline__ void Bbox::body(const Args& A, Blk B)
 {
     const double *x = A.x, *y = A.y, *z = A.z, *M = A.M;
     const int64_t n = A.n;
     double lo[3] = {INFINITY, INFINITY, INFINITY}, hi[3] = {-INFINITY, -INFINITY, -INFINITY};
     double cnt = 0.0;
+    for (int64_t i = B.id * int64_t(blockDim.x) + threadIdx.x; i < A.nzero; i += B.n * blockDim.x) A.zero[i] = 0u;
     // the four arrays are read for every slot (an inactive one is then left
     // out), so that the unrolled iterations' loads are in flight together
 #pragma unroll 4
@@ -46,6 +53,7 @@ __device__ __forceinline__ void BboxPartial::body(const Args& A, Blk B)
         cnt += act ? 1.0 : 0.0;
     }
     __shared__ double s[4][7];
+    __shared__ int32_t s_last;
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     double v[7] = {lo[0], lo[1], lo[2], hi[0], hi[1], hi[2], cnt};
 #pragma unroll
@@ -63,42 +71,32 @@ __device__ __forceinline__ void BboxPartial::body(const Args& A, Blk B)
             for (int d = 3; d < 6; ++d) s[0][d] = fmax(s[0][d], s[ww][d]);
             s[0][6] += s[ww][6];
         }
-        for (int d = 0; d < 7; ++d) A.red[B.id * 8 + d] = s[0][d];
+        for (int d = 0; d < 7; ++d) put_device(A.red + B.id * 8 + d, s[0][d]);
+        done_stores();
+        s_last = last_block(&A.h->red_done, B.n) ? 1 : 0;
     }
-}
-
-__global__ __launch_bounds__(256) void k_bbox_partial(BboxArgs A)
-{
-    BboxPartial::body(A, Blk{int64_t(blockIdx.x), int64_t(gridDim.x)});
-}
-
-// one wavefront combines the per-block partials
-struct BboxFinalArgs {
-    const double* red;
-    int nblk;
-    WsHeader* h;
-};
-
-struct BboxFinal {
-    using Args = BboxFinalArgs;
-    static constexpr int kThreads = 64;
-    static __device__ __forceinline__ void body(const Args& A, Blk B);
-};
-
-__device__ __forceinline__ void BboxFinal::body(const Args& A, Blk)
-{
+    __syncthreads();
+    if (!s_last || threadIdx.x >= kWave) return;
     const double* red = A.red;
-    const int nblk = A.nblk;
+    const int nblk = int(B.n);
     WsHeader* h = A.h;
-    const int lane = threadIdx.x;
-    double v[7] = {INFINITY, INFINITY, INFINITY, -INFINITY, -INFINITY, -INFINITY, 0.0};
-    for (int b = lane; b < nblk; b += 64) {
+#pragma unroll
+    for (int d = 0; d < 3; ++d) {
+        v[d] = INFINITY;
+        v[3 + d] = -INFINITY;
+    }
+    v[6] = 0.0;
+#pragma unroll
+    for (int r = 0; r < kRedBlocks / kWave; ++r) {
+        const int b = r * kWave + lane;
+        const bool have = b < nblk;
+        const double* p = red + (have ? b : 0) * 8;
 #pragma unroll
         for (int d = 0; d < 3; ++d) {
-            v[d] = fmin(v[d], red[b * 8 + d]);
-            v[3 + d] = fmax(v[3 + d], red[b * 8 + 3 + d]);
+            v[d] = fmin(v[d], p[d]);
+            v[3 + d] = fmax(v[3 + d], p[3 + d]);
         }
-        v[6] += red[b * 8 + 6];
+        v[6] += have ? p[6] : 0.0;
     }
 #pragma unroll
     for (int d = 0; d < 3; ++d) {
@@ -117,11 +115,12 @@ __device__ __forceinline__ void BboxFinal::body(const Args& A, Blk)
     }
     h->inv = ext > 0.0 ? 1024.0 / ext : 0.0;
     h->n_active = int32_t(v[6]);
+    if (A.na_out) *A.na_out = int32_t(v[6]);
 }
 
-__global__ __launch_bounds__(64) void k_bbox_final(BboxFinalArgs A)
+__global__ __launch_bounds__(256) void k_bbox(BboxArgs A)
 {
-    BboxFinal::body(A, Blk{0, 1});
+    Bbox::body(A, Blk{int64_t(blockIdx.x), int64_t(gridDim.x)});
 }
 
 // ---------------------------------------------------------------------------
@@ -143,12 +142,38 @@ __device__ inline uint32_t quant(double c, double lo, double inv)
     return q > 1023u ? 1023u : q;
 }
 
+// ---------------------------------------------------------------------------
+// LSD radix sort, 8-bit digits.  Block b owns the keys [b T, (b + 1) T), T =
+// 256 rounds, wavefront w of it the w-th quarter.  A pass is a count (row b
+// of hist, and added to the row of b's group of `sup` blocks) and a scatter,
+// whose blocks add up the group rows and their own group's block rows
+// themselves (a scan kernel between the two took 4.7 us a pass).
+struct RadixArgs {
+    const uint32_t *kin, *vin;
+    uint32_t *kout, *vout;
+    int64_t n;
+    int shift, rounds;
+    uint32_t* hist;
+    uint32_t* sums;  // this pass's group rows
+    int nblk, sup;
+};
+
+// the block's digit counts h (LDS) to its row, and onto its group's
+__device__ inline void put_counts(const RadixArgs& A, Blk B, const uint32_t* h)
+{
+    const int t = threadIdx.x;
+    const uint32_t c = h[t];
+    A.hist[B.id * 256 + t] = c;
+    if (c) atomicAdd(&A.sums[(B.id / A.sup) * 256 + t], c);
+}
+
+// the keys (and slots) of every particle, and the first pass's counts
 struct MortonArgs {
     const double *x, *y, *z, *M;
-    int64_t n;
     const WsHeader* h;
     uint32_t* keys;
     uint32_t* vals;
+    RadixArgs r;
 };
 
 struct Morton {
@@ -156,17 +181,27 @@ struct Morton {
     static constexpr int kThreads = 256;
     static __device__ __forceinline__ void body(const Args& A, Blk B)
     {
-        const int64_t i = B.id * int64_t(blockDim.x) + threadIdx.x;
-        if (i >= A.n) return;
-        uint32_t key = 0xFFFFFFFFu;
-        if (A.M[i] > 0.0) {
-            const WsHeader* h = A.h;
-            const double inv = h->inv;
-            key = spread3(quant(A.x[i], h->lo[0], inv)) | (spread3(quant(A.y[i], h->lo[1], inv)) << 1) |
-                  (spread3(quant(A.z[i], h->lo[2], inv)) << 2);
+        __shared__ uint32_t cnt[256];
+        cnt[threadIdx.x] = 0;
+        __syncthreads();
+        const WsHeader* h = A.h;
+        const double inv = h->inv;
+        const double lo[3] = {h->lo[0], h->lo[1], h->lo[2]};
+        const int64_t base = B.id * int64_t(256 * A.r.rounds) + threadIdx.x;
+#pragma unroll 4
+        for (int r = 0; r < A.r.rounds; ++r) {
+            const int64_t i = base + r * 256;
+            if (i >= A.r.n) break;
+            uint32_t key = 0xFFFFFFFFu;
+            if (A.M[i] > 0.0)
+                key = spread3(quant(A.x[i], lo[0], inv)) | (spread3(quant(A.y[i], lo[1], inv)) << 1) |
+                      (spread3(quant(A.z[i], lo[2], inv)) << 2);
+            A.keys[i] = key;
+            A.vals[i] = uint32_t(i);
+            atomicAdd(&cnt[key & 0xFFu], 1u);
         }
-        A.keys[i] = key;
-        A.vals[i] = uint32_t(i);
+        __syncthreads();
+        put_counts(A.r, B, cnt);
     }
 };
 
@@ -174,21 +209,6 @@ __global__ __launch_bounds__(256) void k_morton(MortonArgs A)
 {
     Morton::body(A, Blk{int64_t(blockIdx.x), int64_t(gridDim.x)});
 }
-
-// ---------------------------------------------------------------------------
-// LSD radix sort, 8-bit digits.  Block b owns keys [b*4096, (b+1)*4096).
-// hist is digit-major: hist[d * nblk + b]; each digit's row is exclusive-
-// scanned in place by its own block, and the scatter adds the exclusive scan
-// of the digit totals.
-struct RadixArgs {
-    const uint32_t *kin, *vin;
-    uint32_t *kout, *vout;
-    int64_t n;
-    int shift;
-    uint32_t* hist;
-    int nblk;
-    uint32_t* tot;
-};
 
 struct RadixHist {
     using Args = RadixArgs;
@@ -198,21 +218,17 @@ struct RadixHist {
         __shared__ uint32_t h[256];
         h[threadIdx.x] = 0;
         __syncthreads();
-        const int64_t base = B.id * kSortTile;
+        const int64_t base = B.id * int64_t(256 * A.rounds) + threadIdx.x;
         const int shift = A.shift;
         // the tile's keys are loaded first, all in flight together
-        constexpr int R = kSortTile / 256;
-        uint32_t kr[R];
+        uint32_t kr[kSortRounds];
 #pragma unroll
-        for (int r = 0; r < R; ++r) {
-            const int64_t i = base + r * 256 + threadIdx.x;
-            kr[r] = i < A.n ? A.kin[i] : 0u;
-        }
+        for (int r = 0; r < kSortRounds; ++r) kr[r] = r < A.rounds && base + r * 256 < A.n ? A.kin[base + r * 256] : 0u;
 #pragma unroll
-        for (int r = 0; r < R; ++r)
-            if (base + r * 256 + threadIdx.x < A.n) atomicAdd(&h[(kr[r] >> shift) & 0xFFu], 1u);
+        for (int r = 0; r < kSortRounds; ++r)
+            if (r < A.rounds && base + r * 256 < A.n) atomicAdd(&h[(kr[r] >> shift) & 0xFFu], 1u);
         __syncthreads();
-        A.hist[int64_t(threadIdx.x) * A.nblk + B.id] = h[threadIdx.x];
+        put_counts(A, B, h);
     }
 };
 
@@ -222,8 +238,8 @@ __global__ __launch_bounds__(256) void k_radix_hist(RadixArgs A)
 }
 
 // Exclusive scan of 256 values held one per thread of a 256-thread block;
-// returns this thread's prefix, and the total in *total.
-__device__ inline uint32_t block_scan_excl_256(uint32_t v, uint32_t* s_w, uint32_t* total)
+// returns this thread's prefix.
+__device__ inline uint32_t block_scan_excl_256(uint32_t v, uint32_t* s_w)
 {
     const int t = threadIdx.x, lane = t & 63, w = t >> 6;
     uint32_t x = v;
@@ -236,39 +252,13 @@ __device__ inline uint32_t block_scan_excl_256(uint32_t v, uint32_t* s_w, uint32
     __syncthreads();
     uint32_t before = 0;
     for (int ww = 0; ww < w; ++ww) before += s_w[ww];
-    *total = s_w[0] + s_w[1] + s_w[2] + s_w[3];
-    __syncthreads();
     return before + x - v;
 }
 
-// Row d of the digit-major histogram (the counts of digit d in every block)
-// becomes its exclusive prefix; the row total goes to tot[d].
-struct ScanRows {
-    using Args = RadixArgs;
-    static constexpr int kThreads = 256;
-    static __device__ __forceinline__ void body(const Args& A, Blk B)
-    {
-        __shared__ uint32_t s_w[4];
-        const int nblk = A.nblk;
-        uint32_t* row = A.hist + B.id * nblk;
-        uint32_t carry = 0;
-        for (int c = 0; c < nblk; c += 256) {
-            const int i = c + int(threadIdx.x);
-            const uint32_t v = i < nblk ? row[i] : 0u;
-            uint32_t chunk;
-            const uint32_t pre = block_scan_excl_256(v, s_w, &chunk);
-            if (i < nblk) row[i] = carry + pre;
-            carry += chunk;
-        }
-        if (threadIdx.x == 0) A.tot[B.id] = carry;
-    }
-};
-
-__global__ __launch_bounds__(256) void k_scan_rows(RadixArgs A)
-{
-    ScanRows::body(A, Blk{int64_t(blockIdx.x), int64_t(gridDim.x)});
-}
-
+// The wavefronts rank their quarters of the tile on their own: each counts
+// its digits first, the four counts become places, and then every round of
+// 64 keys takes its places from the wavefront's own row, with no barrier
+// (four barriers a round, shared rows: 12.7 us a pass on 10,000 keys).
 struct RadixScatter {
     using Args = RadixArgs;
     static constexpr int kThreads = 256;
@@ -277,44 +267,55 @@ struct RadixScatter {
 
 __device__ __forceinline__ void RadixScatter::body(const Args& A, Blk B)
 {
-    const uint32_t* __restrict__ kin = A.kin;
-    const uint32_t* __restrict__ vin = A.vin;
-    uint32_t* __restrict__ kout = A.kout;
-    uint32_t* __restrict__ vout = A.vout;
     const int64_t n = A.n;
-    const int shift = A.shift;
-    const uint32_t* __restrict__ hist = A.hist;
-    const int nblk = A.nblk;
-    const uint32_t* __restrict__ tot = A.tot;
-    __shared__ uint32_t goff[256];   // global offset of each digit for this block
-    __shared__ uint32_t run[256];    // items of each digit placed in earlier rounds
-    __shared__ uint32_t wcnt[4][256];
+    const int shift = A.shift, rounds = A.rounds;
+    __shared__ uint32_t at[4][256];  // per wavefront: counts, then the next place of each digit
     __shared__ uint32_t s_w[4];
     const int t = threadIdx.x, lane = t & 63, w = t >> 6;
-    uint32_t all;
-    const uint32_t below = block_scan_excl_256(tot[t], s_w, &all);  // keys of smaller digits
-    goff[t] = below + hist[int64_t(t) * nblk + B.id];
-    run[t] = 0;
-    const int64_t base = B.id * kSortTile;
-    const uint64_t lt = (uint64_t(1) << lane) - 1;
-    // the tile's keys and values are loaded first, all in flight together;
-    // the rounds then take them from registers
-    constexpr int R = kSortTile / 256;
-    uint32_t kr[R], vr[R];
+    // the tile's keys and values are loaded first, all in flight together
+    const int64_t base = B.id * int64_t(256 * rounds) + int64_t(w) * (64 * rounds) + lane;
+    uint32_t kr[kSortRounds], vr[kSortRounds];
 #pragma unroll
-    for (int r = 0; r < R; ++r) {
-        const int64_t i = base + r * 256 + t;
-        kr[r] = i < n ? kin[i] : 0u;
-        vr[r] = i < n ? vin[i] : 0u;
+    for (int r = 0; r < kSortRounds; ++r) {
+        const bool in = r < rounds && base + r * 64 < n;
+        kr[r] = in ? A.kin[base + r * 64] : 0u;
+        vr[r] = in ? A.vin[base + r * 64] : 0u;
     }
+    // digit t: the keys of it in all blocks, and in the blocks before this one
+    const int grp = int(B.id / A.sup), ngrp = (A.nblk + A.sup - 1) / A.sup;
+    uint32_t total = 0, before = 0;
+#pragma unroll 8
+    for (int g = 0; g < ngrp; ++g) {
+        const uint32_t c = A.sums[g * 256 + t];
+        total += c;
+        before += g < grp ? c : 0u;
+    }
+    const int b0 = grp * A.sup;
+#pragma unroll 8
+    for (int b = b0; b < int(B.id); ++b) before += A.hist[b * 256 + t];
 #pragma unroll
-    for (int r = 0; r < R; ++r) {
-        for (int ww = 0; ww < 4; ++ww) wcnt[ww][t] = 0;
-        __syncthreads();
-        const int64_t i = base + r * 256 + t;
-        const bool valid = i < n;
-        const uint32_t key = kr[r], val = vr[r];
-        const uint32_t dig = valid ? (key >> shift) & 0xFFu : 0u;
+    for (int ww = 0; ww < 4; ++ww) at[ww][t] = 0;
+    const uint32_t goff = block_scan_excl_256(total, s_w) + before;  // (holds a barrier)
+#pragma unroll
+    for (int r = 0; r < kSortRounds; ++r)
+        if (r < rounds && base + r * 64 < n) atomicAdd(&at[w][(kr[r] >> shift) & 0xFFu], 1u);
+    __syncthreads();
+    {
+        uint32_t p = goff;
+#pragma unroll
+        for (int ww = 0; ww < 4; ++ww) {
+            const uint32_t c = at[ww][t];
+            at[ww][t] = p;
+            p += c;
+        }
+    }
+    __syncthreads();
+    const uint64_t lt = (uint64_t(1) << lane) - 1;
+#pragma unroll
+    for (int r = 0; r < kSortRounds; ++r) {
+        if (r >= rounds) break;
+        const bool valid = base + r * 64 < n;
+        const uint32_t dig = (kr[r] >> shift) & 0xFFu;
         uint64_t peers = __ballot(valid);
 #pragma unroll
         for (int bit = 0; bit < 8; ++bit) {
@@ -322,18 +323,16 @@ __device__ __forceinline__ void RadixScatter::body(const Args& A, Blk B)
             const uint64_t bs = __ballot(set);
             peers &= set ? bs : ~bs;
         }
-        const uint32_t rank = __popcll(peers & lt);
-        if (valid && rank == 0) wcnt[w][dig] = __popcll(peers);
-        __syncthreads();
+        const uint32_t rank = uint32_t(__popcll(peers & lt));
         if (valid) {
-            uint32_t off = goff[dig] + run[dig];
-            for (int ww = 0; ww < w; ++ww) off += wcnt[ww][dig];
-            kout[off + rank] = key;
-            vout[off + rank] = val;
+            const uint32_t off = at[w][dig] + rank;
+            A.kout[off] = kr[r];
+            A.vout[off] = vr[r];
+            // (the wavefront's LDS operations run in order: every peer has
+            // read its place when the last of them moves it on)
+            if (rank + 1 == uint32_t(__popcll(peers))) at[w][dig] = off + 1;
         }
-        __syncthreads();
-        run[t] += wcnt[0][t] + wcnt[1][t] + wcnt[2][t] + wcnt[3][t];
-        __syncthreads();
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     }
 }
 
@@ -386,33 +385,33 @@ __global__ void k_fill_i32(int32_t* __restrict__ a, int64_t n, int32_t v)
 // alternate between (keys0, vals0) and (keys1, vals1)
 struct SortArgs {
     BboxArgs bbox;
-    BboxFinalArgs fin;
     MortonArgs morton;
     RadixArgs pass[4];
     PermuteArgs perm;
 };
 
-static SortArgs sort_args(const gd_problem* p, const gd_particles* in, gd_particles* out, const double* hint, void* ws,
-                          const Layout& L, int nblk_bbox)
+static SortArgs sort_args(const gd_problem* p, const gd_particles* in, gd_particles* out, const double* hint,
+                          int32_t* na_out, void* ws, const Layout& L)
 {
     const int64_t n = p->n;
     WsHeader* h = at<WsHeader>(ws, L.hdr);
     double* red = at<double>(ws, L.red);
     SortArgs S{};
-    S.bbox = BboxArgs{in->x, in->y, in->z, in->M, n, red};
-    S.fin = BboxFinalArgs{red, nblk_bbox, h};
     uint32_t* k0 = at<uint32_t>(ws, L.keys0);
     uint32_t* k1 = at<uint32_t>(ws, L.keys1);
     uint32_t* v0 = at<uint32_t>(ws, L.vals0);
     uint32_t* v1 = at<uint32_t>(ws, L.vals1);
     uint32_t* hist = at<uint32_t>(ws, L.hist);
-    S.morton = MortonArgs{in->x, in->y, in->z, in->M, n, h, k0, v0};
     const int nsb = L.nsort_blocks;
-    uint32_t* tot = hist + int64_t(256) * nsb;  // per-digit totals (the spare row of hist)
+    uint32_t* sums = hist + int64_t(256) * nsb;  // per pass: the group rows
+    const int64_t row = int64_t(256) * L.nsort_sup;
+    S.bbox = BboxArgs{in->x, in->y, in->z, in->M, n, red, h, na_out, sums, 4 * row};
     for (int pass = 0; pass < 4; ++pass) {
         const bool odd = pass & 1;
-        S.pass[pass] = RadixArgs{odd ? k1 : k0, odd ? v1 : v0, odd ? k0 : k1, odd ? v0 : v1, n, 8 * pass, hist, nsb, tot};
+        S.pass[pass] = RadixArgs{odd ? k1 : k0, odd ? v1 : v0, odd ? k0 : k1, odd ? v0 : v1, n, 8 * pass,
+                                 L.sort_rounds, hist, sums + pass * row, nsb, L.sort_sup};
     }
+    S.morton = MortonArgs{in->x, in->y, in->z, in->M, h, k0, v0, S.pass[0]};
     // sorted (key, slot) pairs are back in (k0, v0)
     PermuteArgs& A = S.perm;
     A.n = n;
@@ -447,20 +446,21 @@ static SortArgs sort_args(const gd_problem* p, const gd_particles* in, gd_partic
     return S;
 }
 
-int launch_morton_sort(const gd_problem* p, const gd_particles* in, gd_particles* out, const double* hint, void* ws,
-                       const Layout& L, hipStream_t st)
+// blocks of the bounding box: at most kRedBlocks, four slots or more a thread
+static int64_t bbox_blocks(int64_t n) { return std::min<int64_t>(kRedBlocks, std::max<int64_t>(1, cdiv(n, 1024))); }
+
+int launch_morton_sort(const gd_problem* p, const gd_particles* in, gd_particles* out, const double* hint,
+                       int32_t* na_out, void* ws, const Layout& L, hipStream_t st)
 {
     const int64_t n = p->n;
-    const SortArgs S = sort_args(p, in, out, hint, ws, L, kRedBlocks);
+    const SortArgs S = sort_args(p, in, out, hint, na_out, ws, L);
     prof_mark(GD_PROF_SORT, 0, st);
-    hipLaunchKernelGGL(k_bbox_partial, dim3(kRedBlocks), dim3(256), 0, st, S.bbox);
-    hipLaunchKernelGGL(k_bbox_final, dim3(1), dim3(64), 0, st, S.fin);
+    hipLaunchKernelGGL(k_bbox, dim3(unsigned(bbox_blocks(n))), dim3(256), 0, st, S.bbox);
     const int nb = int((n + 255) / 256);
-    hipLaunchKernelGGL(k_morton, dim3(nb), dim3(256), 0, st, S.morton);
     const int nsb = L.nsort_blocks;
+    hipLaunchKernelGGL(k_morton, dim3(nsb), dim3(256), 0, st, S.morton);
     for (int pass = 0; pass < 4; ++pass) {
-        hipLaunchKernelGGL(k_radix_hist, dim3(nsb), dim3(256), 0, st, S.pass[pass]);
-        hipLaunchKernelGGL(k_scan_rows, dim3(256), dim3(256), 0, st, S.pass[pass]);
+        if (pass > 0) hipLaunchKernelGGL(k_radix_hist, dim3(nsb), dim3(256), 0, st, S.pass[pass]);
         hipLaunchKernelGGL(k_radix_scatter, dim3(nsb), dim3(256), 0, st, S.pass[pass]);
     }
     hipLaunchKernelGGL(k_permute, dim3(nb), dim3(256), 0, st, S.perm);
@@ -473,17 +473,15 @@ void many_sort(ManyBuilder& B, const std::vector<ManyRun>& R)
 {
     const size_t nr = R.size();
     std::vector<SortArgs> S(nr);
-    std::vector<int64_t> nbb(nr), one(nr, 1), nb(nr), nsb(nr), digits(nr, 256);
+    std::vector<int64_t> nbb(nr), nb(nr), nsb(nr);
     for (size_t r = 0; r < nr; ++r) {
         const ManyRun& x = R[r];
         const int64_t n = x.p.n;
         nbb[r] = n > 0 ? std::min<int64_t>(kRedBlocks, std::max<int64_t>(1, cdiv(n, B.tune.red_div))) : 0;
         gd_particles out = x.out;
-        S[r] = sort_args(&x.p, &x.in, &out, x.nb.dmax, x.ws, x.L, int(nbb[r]));
-        one[r] = n > 0 ? 1 : 0;
+        S[r] = sort_args(&x.p, &x.in, &out, x.nb.dmax, x.nb.n_active, x.ws, x.L);
         nb[r] = cdiv(n, 256);
         nsb[r] = n > 0 ? x.L.nsort_blocks : 0;
-        if (n == 0) digits[r] = 0;
     }
     auto pick = [&](auto f) {
         using A = std::remove_reference_t<decltype(f(S[0]))>;
@@ -491,13 +489,11 @@ void many_sort(ManyBuilder& B, const std::vector<ManyRun>& R)
         for (size_t r = 0; r < nr; ++r) v[r] = f(S[r]);
         return v;
     };
-    B.add<BboxPartial>(pick([](SortArgs& a) -> BboxArgs& { return a.bbox; }), nbb);
-    B.add<BboxFinal>(pick([](SortArgs& a) -> BboxFinalArgs& { return a.fin; }), one);
-    B.add<Morton>(pick([](SortArgs& a) -> MortonArgs& { return a.morton; }), nb);
+    B.add<Bbox>(pick([](SortArgs& a) -> BboxArgs& { return a.bbox; }), nbb);
+    B.add<Morton>(pick([](SortArgs& a) -> MortonArgs& { return a.morton; }), nsb);
     for (int pass = 0; pass < 4; ++pass) {
         auto tab = pick([pass](SortArgs& a) -> RadixArgs& { return a.pass[pass]; });
-        B.add<RadixHist>(tab, nsb);
-        B.add<ScanRows>(tab, digits);
+        if (pass > 0) B.add<RadixHist>(tab, nsb);
         B.add<RadixScatter>(tab, nsb);
     }
     B.add<Permute>(pick([](SortArgs& a) -> PermuteArgs& { return a.perm; }), nb);
