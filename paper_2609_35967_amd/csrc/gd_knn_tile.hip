@@ -37,6 +37,8 @@
 #include "gd_internal.hpp"
 #include "gd_knn.hpp"
 
+#include <type_traits>
+
 namespace gd {
 
 constexpr int kTG = 8;               // lanes (queries) per group
@@ -76,6 +78,7 @@ struct TileLds {
     } u;
     uint32_t glist[kNGrp][kGList];
     float gbox[kNGrp][6];            // group boxes: lo[3], hi[3]
+    float gimg[PER ? kNGrp : 1][3][4];  // their images' spans per axis: lo and hi at +L, at -L
 };
 
 // 32 per-lane 8-bit bin counters in 8 registers
@@ -96,24 +99,48 @@ struct Hist8 {
 
 __device__ inline bool span_meets(float lo, float hi, float blo, float bhi) { return (blo <= hi) & (lo <= bhi); }
 
-// does box b meet group box g (with its periodic images)?
-template <bool PER>
-__device__ inline bool group_meets(const KnnArgs& A, const float (&g)[6], const FBox& b)
+// The periodic images a wavefront's spheres can meet: on axis a, the spheres
+// moved by +L (p) or -L (m) reach into the particles' box.  Without one no
+// particle lies within a sphere through that image, and every |dx| within the
+// radius is the minimum image already, so a wavefront without any (about half
+// of them at 65,536 particles in a unit box) searches as in an open box.
+struct Images {
+    bool p[3], m[3];
+};
+
+// does box b meet group box g, or, on the axes of `im`, its image?  (the
+// images' spans, rounded outward, are in gi: lo and hi of +L, then of -L)
+template <bool IMG>
+__device__ inline bool group_meets(const Images& im, const float (&g)[6], const float (*gi)[4], const FBox& b)
 {
     bool ok = true;
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
         bool m = span_meets(g[a], g[3 + a], b.lo[a], b.hi[a]);
-        if (PER && A.per[a]) {
-            const double L = A.L[a];
-            m = m | span_meets(__double2float_rd(double(g[a]) + L), __double2float_ru(double(g[3 + a]) + L), b.lo[a],
-                               b.hi[a]);
-            m = m | span_meets(__double2float_rd(double(g[a]) - L), __double2float_ru(double(g[3 + a]) - L), b.lo[a],
-                               b.hi[a]);
+        if (IMG) {
+            if (im.p[a]) m = m | span_meets(gi[a][0], gi[a][1], b.lo[a], b.hi[a]);
+            if (im.m[a]) m = m | span_meets(gi[a][2], gi[a][3], b.lo[a], b.hi[a]);
         }
         ok = ok & m;
     }
     return ok;
+}
+
+// box2f of gd_knn.hpp over the images of `im`
+template <bool IMG>
+__device__ inline float sphere2f(const Images& im, const QF& f, const FBox& b)
+{
+    float g[3];
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        float v = gapf(f.c[a], b.lo[a], b.hi[a]);
+        if (IMG) {
+            if (im.p[a]) v = fminf(v, gapf(f.p[a], b.lo[a], b.hi[a]));
+            if (im.m[a]) v = fminf(v, gapf(f.m[a], b.lo[a], b.hi[a]));
+        }
+        g[a] = v;
+    }
+    return fmaf(g[2], g[2], fmaf(g[1], g[1], g[0] * g[0]));
 }
 
 // The first radius (squared) of lanes without a previous distance: of the
@@ -297,6 +324,7 @@ __device__ __forceinline__ void KnnTile<PER>::body(const Args& TA, Blk B)
     }
     reinterpret_cast<uint4*>(&L.u.t.gm[0][0])[lane] = make_uint4(0u, 0u, 0u, 0u);
     static_assert(sizeof(L.u.t.gm) == kWave * sizeof(uint4), "one 16-byte store per lane clears the lane masks");
+    Images im{};
     // the group boxes: each sphere's box, widened far beyond the rounding of
     // q +- R in double and rounded outward to single precision
     {
@@ -320,13 +348,39 @@ __device__ __forceinline__ void KnnTile<PER>::body(const Args& TA, Blk B)
 #pragma unroll
             for (int a = 0; a < 6; ++a) L.gbox[lane / kTG][a] = g[a];
         }
+        if (PER) {
+            const FBox* tb = A.boxes + A.T.off[A.T.levels - 1];
+#pragma unroll
+            for (int a = 0; a < 3; ++a) {
+                if (!A.per[a]) continue;
+                float lo = INFINITY, hi = -INFINITY;  // the particles' box
+#pragma unroll
+                for (int c = 0; c < kFan; ++c) {
+                    lo = fminf(lo, tb[c].lo[a]);
+                    hi = fmaxf(hi, tb[c].hi[a]);
+                }
+                const double Lp = A.L[a];
+                const float s[4] = {__double2float_rd(double(g[a]) + Lp), __double2float_ru(double(g[3 + a]) + Lp),
+                                    __double2float_rd(double(g[a]) - Lp), __double2float_ru(double(g[3 + a]) - Lp)};
+                im.p[a] = __ballot(s[0] <= hi) != 0;
+                im.m[a] = __ballot(s[3] >= lo) != 0;
+                if ((lane & (kTG - 1)) == 0) {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) L.gimg[lane / kTG][a][e] = s[e];
+                }
+            }
+        }
     }
+    const bool imaged = im.p[0] | im.p[1] | im.p[2] | im.m[0] | im.m[1] | im.m[2];
     const uint64_t okmask = __ballot(ok);
     uint32_t gall = 0;  // groups with at least one searching lane
 #pragma unroll
     for (int g = 0; g < kNGrp; ++g) gall |= ((okmask >> (kTG * g)) & 0xFFu) ? (1u << g) : 0u;
     __syncthreads();
 
+    // the rest of the search, with or without periodic images
+    auto rest = [&](auto with_images) __attribute__((always_inline)) {
+    constexpr bool IMG = decltype(with_images)::value;
     bool wave_ok = gall != 0;
     int npairs = 0;  // pairs waiting (uniform over the wavefront)
 #ifdef GD_KNN_STATS
@@ -369,8 +423,8 @@ __device__ __forceinline__ void KnnTile<PER>::body(const Args& TA, Blk B)
                     f.c[0] = sq.x;
                     f.c[1] = sq.y;
                     f.c[2] = sq.z;
-                    if (PER) {
-                        const float4 sp = L.u.t.sp[g * kTG + t], sm = L.u.t.sm[g * kTG + t];
+                    if (IMG) {
+                        const float4 sp = L.u.t.sp[PER ? g * kTG + t : 0], sm = L.u.t.sm[PER ? g * kTG + t : 0];
                         f.p[0] = sp.x;
                         f.p[1] = sp.y;
                         f.p[2] = sp.z;
@@ -379,7 +433,7 @@ __device__ __forceinline__ void KnnTile<PER>::body(const Args& TA, Blk B)
                         f.m[2] = sm.z;
                     }
                     // (a lane without a search has a negative threshold, below any box2f)
-                    hit |= uint32_t(box2f<PER>(A, f, bx) <= sq.w) << t;
+                    hit |= uint32_t(sphere2f<IMG>(im, f, bx) <= sq.w) << t;
                 }
             }
             // places in the groups' lists: per group, after the lanes below
@@ -448,7 +502,7 @@ __device__ __forceinline__ void KnnTile<PER>::body(const Args& TA, Blk B)
                             float gb[6];
 #pragma unroll
                             for (int a = 0; a < 6; ++a) gb[a] = L.gbox[g][a];
-                            cm |= (((pm[u] >> g) & 1u) & uint32_t(group_meets<PER>(A, gb, bx[u]))) << g;
+                            cm |= (((pm[u] >> g) & 1u) & uint32_t(group_meets<IMG>(im, gb, L.gimg[PER ? g : 0], bx[u]))) << g;
                         }
                     }
                     if (lv > 1) {
@@ -613,7 +667,7 @@ __device__ __forceinline__ void KnnTile<PER>::body(const Args& TA, Blk B)
         if (len > kTList - kBucket && !ovf) cut_list();  // room for a whole bucket
 #pragma unroll
         for (int s = 0; s < kBucket; ++s) {
-            const double d2 = sep2<PER>(A, qp, c.x[s], c.y[s], c.z[s]);
+            const double d2 = sep2<IMG>(A, qp, c.x[s], c.y[s], c.z[s]);
             const int j = c.j0 + s;
             if (j < na && d2 <= R2cut && j != q && !ovf) {
                 const int b = log_bin(d2 * sA);
@@ -706,7 +760,7 @@ __device__ __forceinline__ void KnnTile<PER>::body(const Args& TA, Blk B)
         for (int e = 0; e < kC1; ++e) {
             bw[e] = e < nb ? bnd(e) : uint16_t(0);
             bj[e] = e < nb ? slot_of(bw[e]) : INT32_MAX;
-            bd[e] = e < nb ? sep2_slot<PER>(A, qp, bj[e]) : INFINITY;
+            bd[e] = e < nb ? sep2_slot<IMG>(A, qp, bj[e]) : INFINITY;
         }
 #pragma unroll
         for (int e = 0; e < kC1; ++e) {
@@ -770,6 +824,9 @@ __device__ __forceinline__ void KnnTile<PER>::body(const Args& TA, Blk B)
     if (lane == 0 && fbm) base = atomicAdd(TA.fb_n, int32_t(__popcll(fbm)));
     base = __builtin_amdgcn_readfirstlane(base);
     if (fb) TA.fb[base + int(__popcll(fbm & ((uint64_t(1) << lane) - 1)))] = q;
+    };
+    if (PER && imaged) rest(std::true_type{});
+    else rest(std::false_type{});
 }
 
 // fb receives the handed-back queries (n entries), counted by *fb_n
