@@ -52,7 +52,11 @@ namespace gd {
 constexpr int kDMax = 3;  // levels of the nested bin chain
 constexpr int kRescales = 4;  // restarts of pass A on a finer distance scale
 constexpr int kQBlock = 128;
-constexpr int kFallbackBlocks = 8192;  // one-wavefront workgroups that take the handed-back queries (about one each)
+// one-wavefront workgroups for the handed-back queries: most leave at once
+// when few were (a million-particle interval takes as long with 7168, as many
+// as are resident), and a run's first search, all of it handed back, balances
+// over them (300,007 particles: 0.86 ms against 0.98 with 7168)
+constexpr int kFallbackBlocks = 32768;
 constexpr int kQueue = 4;  // level-1 bucket masks a walk keeps queued
 static_assert(kQueue >= 1 && kQueue <= 4, "the queue keeps its masks in the bytes of one word");
 
@@ -554,20 +558,7 @@ __device__ __forceinline__ void KnnQuery<PER>::body(const Args& A, Blk B)
         const double hv = A.hint[q] * kHintSlack;
         if (hv > 0.0 && hv < INFINITY) {
             // a radius beyond the diagonal of the active set's box is no hint
-            const FBox* tb = A.boxes + A.T.off[A.T.levels - 1];
-            double e2 = 0.0;
-#pragma unroll
-            for (int a = 0; a < 3; ++a) {
-                float lo = INFINITY, hi = -INFINITY;
-#pragma unroll
-                for (int c = 0; c < kFan; ++c) {
-                    lo = fminf(lo, tb[c].lo[a]);
-                    hi = fmaxf(hi, tb[c].hi[a]);
-                }
-                const double ext = double(hi) - double(lo);
-                e2 += ext * ext;
-            }
-            if (hv * hv <= e2) R2hint = hv * hv;
+            if (hv * hv <= diagonal2(A.h)) R2hint = hv * hv;
         }
     }
     bool use_hint = R2hint < INFINITY;
@@ -953,6 +944,7 @@ static KnnSetup knn_setup(const gd_problem* p, const gd_neighbors* nb, void* ws,
     }
     T.off1 = int32_t(L.off1);
     T.stride1 = int32_t(L.stride1);
+    while (L.lvl_cnt[T.start] > kWave) ++T.start;  // (the top level has at most 8 nodes)
     S.per = false;
     for (int a = 0; a < 3; ++a) {
         S.P.per[a] = p->periodic[a] ? 1 : 0;
@@ -983,6 +975,20 @@ static KnnSetup knn_setup(const gd_problem* p, const gd_neighbors* nb, void* ws,
     A.ws = ws;
     A.xq = at<WsHeader>(ws, L.hdr)->xq[kQueueKnn];
     return S;
+}
+
+// Shared tiles (64 queries per wavefront) or a wavefront per query.  The
+// tiles hold k <= 33.  They do the least work per query, but a set of up to
+// 64K queries gives each SIMD one wavefront or none, and one tile takes up to
+// 0.28 ms; a wavefront per query keeps 7 on each SIMD.  Measured intervals at
+// k = 32, tiles against wavefronts: open disks 360 / 311 us at 100,003
+// particles, 432 / 426 at 150,001, 498 / 529 at 200,003; periodic columns
+// 611 / 388 at 131,072, 847 / 678 at 262,144, 1022 / 998 at 400,000.
+constexpr int64_t kTileOpen = 160000, kTilePeriodic = 400000;
+
+static bool use_tiles(int32_t k, int64_t n, bool per)
+{
+    return k <= 33 && n > (per ? kTilePeriodic : kTileOpen);
 }
 
 int launch_knn(const gd_problem* p, const gd_neighbors* nb, void* ws, const Layout& L, hipStream_t st)
@@ -1020,28 +1026,27 @@ int launch_knn(const gd_problem* p, const gd_neighbors* nb, void* ws, const Layo
     launch_fill_i32(A.stats, 8 * n, 0, st);
 #endif
     prof_mark(GD_PROF_KNN_QUERY, 0, st);
-    // one wavefront per query beyond the shared lists' 33 (at k = 48 on a
-    // 200K disk 0.86 ms per interval with the per-lane walk, 0.77 with this)
-    if (p->k > 33) {
+    if (!use_tiles(p->k, n, per)) {
         launch_knn_wave(A, per, nullptr, nullptr, n, st);
         prof_mark(GD_PROF_KNN_QUERY, 1, st);
         return 0;
     }
     // shared candidate tiles first; the queries they cannot complete (usually
-    // well under 1%: sparse regions with many candidates; some 15% in a
+    // well under 1%: sparse regions with many candidates; all of them in a
     // run's first search) take a wavefront each
     int32_t* fb = at<int32_t>(ws, L.vals1);  // n entries, free after the sort
     if (L.levels == 1) launch_fill_i32(&hw->knn_fb_n, 1, 0, st);  // (else cleared by the tree's first pass)
     launch_knn_tile(A, per, fb, &hw->knn_fb_n, st);
-    launch_knn_wave(A, per, fb, &hw->knn_fb_n, kFallbackBlocks, st);
+    launch_knn_wave(A, per, fb, &hw->knn_fb_n, std::min<int64_t>(kFallbackBlocks, n), st);
     prof_mark(GD_PROF_KNN_QUERY, 1, st);
     return 0;
 }
 
 // The search of every run as stages of one interval: the bucket boxes, each
-// tree level over the runs that have it, then the queries: k > 33 one
-// wavefront per query; k <= 33 (with tiles) the tile search and its fallback
-// wavefronts; otherwise the per-lane search over every query.  Runs are grouped by periodicity and
+// tree level over the runs that have it, then the queries: k > 33, or few
+// particles in all, one wavefront per query; k <= 33 (with tiles) the tile
+// search and its fallback wavefronts; otherwise the per-lane search over
+// every query.  Runs are grouped by periodicity and
 // k class, a launch per group and stage.
 void many_knn(ManyBuilder& B, const std::vector<ManyRun>& R)
 {
@@ -1075,14 +1080,16 @@ void many_knn(ManyBuilder& B, const std::vector<ManyRun>& R)
         for (int cls = 0; cls < 2; ++cls) {
             std::vector<int64_t> mine(nr, 0);
             bool any = false;
+            int64_t total = 0;  // the launch fills the chip over all runs of the class
             for (size_t r = 0; r < nr; ++r) {
                 const int k = R[r].p.k;
                 const int c = k <= 33 ? 0 : 1;
                 mine[r] = (int(S[r].per) == per && c == cls) ? 1 : 0;
                 any = any || mine[r];
+                total += mine[r] ? R[r].p.n : 0;
             }
             if (!any) continue;
-            if (cls == 1) {
+            if (cls == 1 || (B.tune.knn_tile && !use_tiles(2, total, per))) {
                 std::vector<WaveArgs> tab(nr);
                 for (size_t r = 0; r < nr; ++r) {
                     tab[r] = WaveArgs{S[r].A, nullptr, nullptr};

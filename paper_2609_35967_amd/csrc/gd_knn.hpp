@@ -19,6 +19,7 @@ struct TreeLevels {
     int64_t off[kMaxTreeLevels];
     int64_t cap[kMaxTreeLevels];  // padded capacity of each level
     int32_t off1, stride1;        // off[l] = off1 + (l - 1) stride1 for l >= 1
+    int32_t start;                // lowest level of at most 64 nodes
 };
 
 // first box of level l (arithmetic, no table lookup on the walk's path)
@@ -31,6 +32,15 @@ struct Periodicity {
     int32_t per[3];
     double L[3];
 };
+
+// squared diagonal of the active set's box
+__device__ inline double diagonal2(const WsHeader* h)
+{
+    double e2 = 0.0;
+#pragma unroll
+    for (int a = 0; a < 3; ++a) e2 += (h->hi[a] - h->lo[a]) * (h->hi[a] - h->lo[a]);
+    return e2;
+}
 
 // Margin of the single-precision box tests on axis a: 2^-21 (M + L), M the
 // largest coordinate magnitude of the active set, L the period on periodic
@@ -61,7 +71,7 @@ struct KnnArgs {
     double* dmax;
     int32_t row_vec;  // nbr is 16-byte aligned
     int32_t* xq;      // per-die work queue counters
-    double* hint;  // previous neighbour distance per slot (search hint only)
+    const double* hint;  // previous neighbour distance per slot (search hint only)
     void* ws;
 };
 

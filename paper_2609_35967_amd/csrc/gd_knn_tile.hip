@@ -6,9 +6,8 @@
 // its instructions go to box tests and walk bookkeeping, not to distances.
 // Here the wavefront's queries share the walk:
 //   1. each lane's radius is its particle's distance from the previous search
-//      widened by kHintSlack; a lane without a usable one (a run's first
-//      search) takes the k-th distance within the kGuess slots around the
-//      wavefront's, a guaranteed bound (guess_radius); eight groups of eight Morton-consecutive lanes each bound their
+//      widened by kHintSlack (a lane without a usable one is handed back, see
+//      6); eight groups of eight Morton-consecutive lanes each bound their
 //      spheres by one box, rounded outward to single precision;
 //   2. the box tree is traversed breadth first, eight nodes (64 child boxes)
 //      at a time, testing each child against the boxes of the groups its
@@ -26,7 +25,7 @@
 //   5. the bin holding the (k-1)-th other splits the list into sure entries
 //      and a boundary bin ranked by (d^2, slot); the row is written once, in
 //      slot order;
-//   6. lanes whose radius held fewer than k-1 others, whose list or group
+//   6. lanes without a usable previous distance, whose radius held fewer than k-1 others, whose list or group
 //      list overflowed, or whose boundary bin is over-full, go to a list that
 //      the wavefront-per-query search then completes.  The result never
 //      depends on which lanes go there.
@@ -48,7 +47,6 @@ constexpr int kFront = 512;          // traversal frontier (nodes of one level)
 constexpr int kPairs = 512;          // (bucket, group) pairs awaiting their sphere tests
 constexpr int kGList = 128;          // buckets per group after the sphere tests
 constexpr int kMaskW = kGList / 32;  // words of a lane's bucket mask
-constexpr int kGuess = 256;          // slots a first radius is guessed from
 static_assert(kGList * kBucket <= 2048, "a list entry keeps the bucket's place and slot in 11 bits");
 
 template <bool PER>
@@ -69,12 +67,6 @@ struct TileLds {
         struct {
             uint16_t list[kTList][kWave];
         } d;
-        // first radius: the slots' positions from the wavefront's first
-        // query, and per-lane bin counters (halves of a word: bins 2w, 2w + 1)
-        struct {
-            float4 p[kGuess];
-            uint32_t cnt[kNB / 2][kWave];
-        } g;
     } u;
     uint32_t glist[kNGrp][kGList];
     float gbox[kNGrp][6];            // group boxes: lo[3], hi[3]
@@ -143,80 +135,6 @@ __device__ inline float sphere2f(const Images& im, const QF& f, const FBox& b)
     return fmaf(g[2], g[2], fmaf(g[1], g[1], g[0] * g[0]));
 }
 
-// The first radius (squared) of lanes without a previous distance: of the
-// kGuess slots around the wavefront's queries, the distance within which
-// k - 1 others lie, to the upper edge of a bin of 2^(1/8) in d^2.  On a 3D
-// disk and a uniform box it is 1.15 times the true k-th distance at the
-// median and 2 times at the 99th percentile (the k slots about the query
-// alone give several times it).  Single precision about the first query; the
-// rounding up leaves room for it, and a radius that still falls short only
-// sends its lane to the list.  Returns -1 without one.
-template <bool PER>
-__device__ inline double guess_radius(const KnnArgs& A, TileLds<PER>& L, int64_t q0, int q, bool mine,
-                                      const double (&qp)[3], int na, int k, int lane)
-{
-    int lo = int(q0) + kWave / 2 - kGuess / 2;
-    lo = lo + kGuess > na ? na - kGuess : lo;
-    lo = lo < 0 ? 0 : lo;
-    const int m = na - lo < kGuess ? na - lo : kGuess;  // slots taken (> k: the caller has na > k)
-    const double4 b = A.pos[q0];
-    const double base[3] = {b.x, b.y, b.z};
-    float Lf[3], rL[3];
-#pragma unroll
-    for (int a = 0; a < 3; ++a) {
-        Lf[a] = PER && A.per[a] ? float(A.L[a]) : 0.0f;
-        rL[a] = PER && A.per[a] ? 1.0f / float(A.L[a]) : 0.0f;
-    }
-#pragma unroll
-    for (int t = 0; t < kGuess / kWave; ++t) {
-        const int s = t * kWave + lane;
-        const double4 p = A.pos[lo + (s < m ? s : 0)];
-        L.u.g.p[s] = make_float4(float(p.x - base[0]), float(p.y - base[1]), float(p.z - base[2]), 0.0f);
-    }
-#pragma unroll
-    for (int w = 0; w < kNB / 2; ++w) L.u.g.cnt[w][lane] = 0;
-    __syncthreads();
-    const float f[3] = {float(qp[0] - base[0]), float(qp[1] - base[1]), float(qp[2] - base[2])};
-    auto d2_of = [&](int s) {
-        const float4 p = L.u.g.p[s];
-        float d[3] = {p.x - f[0], p.y - f[1], p.z - f[2]};
-#pragma unroll
-        for (int a = 0; a < 3; ++a)
-            if (PER) d[a] = d[a] - Lf[a] * rintf(d[a] * rL[a]);
-        return fmaf(d[2], d[2], fmaf(d[1], d[1], d[0] * d[0]));
-    };
-    // the scale: the largest distance to the k slots about the query
-    int f0 = (mine ? q : int(q0)) - lo - k / 2;
-    f0 = f0 + k > m ? m - k : f0;
-    f0 = f0 < 0 ? 0 : f0;
-    float R0 = 0.0f;
-    for (int s = 0; s < k; ++s) R0 = fmaxf(R0, d2_of(f0 + s));
-    const float sc = R0 > 0.0f ? 1.0f / R0 : 0.0f;
-    for (int s = 0; s < m; ++s) {
-        const float x = d2_of(s) * sc;
-        // 8 bins per octave below 1 (the bits of the float: 20 below the
-        // bin's three), bin 0 also everything smaller
-        const int bn = (__float_as_int(x) >> 20) - (127 * 8 - kNB);
-        const int bc = min(max(bn, 0), kNB - 1);
-        if (x < 1.0f) atomicAdd(&L.u.g.cnt[bc >> 1][lane], 1u << (16 * (bc & 1)));
-    }
-    __syncthreads();
-    // bins up to the one that completes the particle and k - 1 others
-    int cum = 0, bs = kNB;
-#pragma unroll
-    for (int w = 0; w < kNB / 2; ++w) {
-        const uint32_t c = L.u.g.cnt[w][lane];
-        cum += int(c & 0xFFFFu);
-        bs = (bs == kNB && cum >= k) ? 2 * w : bs;
-        cum += int(c >> 16);
-        bs = (bs == kNB && cum >= k) ? 2 * w + 1 : bs;
-    }
-    __syncthreads();
-    const float edge = bs < kNB - 1 ? __int_as_float((bs + 1 + 127 * 8 - kNB) << 20) : 1.0f;
-    const double R2 = double(R0) * double(edge) * (1.0 + 1e-5);
-    return mine && sc > 0.0f && sc < INFINITY && R2 < INFINITY ? R2 : -1.0;
-}
-
 template <bool PER>
 struct KnnTile {
     using Args = TileArgs;
@@ -275,41 +193,13 @@ __device__ __forceinline__ void KnnTile<PER>::body(const Args& TA, Blk B)
         }
     }
     // 1. radius from the previous distance: positive, finite, within the
-    //    diagonal of the active set's box and below the maximum search scale;
-    //    else guessed from the slots around (and kept as the distance that
-    //    the wavefront-per-query search of a handed-back lane starts from)
+    //    diagonal of the active set's box and below the maximum search scale
     double R2 = 0.0;
-    const bool may = ok;
     if (ok) {
         const double hv = A.hint[q] * kHintSlack;
-        ok = hv > 0.0 && hv < INFINITY;
-        if (ok) {
-            const FBox* tb = A.boxes + A.T.off[A.T.levels - 1];
-            double e2 = 0.0;
-#pragma unroll
-            for (int a = 0; a < 3; ++a) {
-                float lo = INFINITY, hi = -INFINITY;
-#pragma unroll
-                for (int c = 0; c < kFan; ++c) {
-                    lo = fminf(lo, tb[c].lo[a]);
-                    hi = fmaxf(hi, tb[c].hi[a]);
-                }
-                const double ext = double(hi) - double(lo);
-                e2 += ext * ext;
-            }
-            R2 = hv * hv;
-            ok = R2 <= e2;
-        }
+        R2 = hv * hv;
+        ok = hv > 0.0 && hv < INFINITY && R2 <= diagonal2(A.h) && R2 < A.rmax2;
     }
-    if (__ballot(may && !ok)) {
-        const double g2 = guess_radius<PER>(A, L, item * kWave, q, may, qp, na, k, lane);
-        if (may && !ok) {
-            ok = g2 > 0.0;
-            R2 = ok ? g2 : 0.0;
-            A.hint[q] = ok ? sqrt(g2) * (1.0 / kHintSlack) : 0.0;
-        }
-    }
-    ok = ok && R2 < A.rmax2;
     QF qf;
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
@@ -349,16 +239,10 @@ __device__ __forceinline__ void KnnTile<PER>::body(const Args& TA, Blk B)
             for (int a = 0; a < 6; ++a) L.gbox[lane / kTG][a] = g[a];
         }
         if (PER) {
-            const FBox* tb = A.boxes + A.T.off[A.T.levels - 1];
 #pragma unroll
             for (int a = 0; a < 3; ++a) {
                 if (!A.per[a]) continue;
-                float lo = INFINITY, hi = -INFINITY;  // the particles' box
-#pragma unroll
-                for (int c = 0; c < kFan; ++c) {
-                    lo = fminf(lo, tb[c].lo[a]);
-                    hi = fmaxf(hi, tb[c].hi[a]);
-                }
+                const float lo = __double2float_rd(A.h->lo[a]), hi = __double2float_ru(A.h->hi[a]);
                 const double Lp = A.L[a];
                 const float s[4] = {__double2float_rd(double(g[a]) + Lp), __double2float_ru(double(g[3 + a]) + Lp),
                                     __double2float_rd(double(g[a]) - Lp), __double2float_ru(double(g[3 + a]) - Lp)};

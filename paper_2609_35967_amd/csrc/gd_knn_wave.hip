@@ -5,10 +5,9 @@
 //
 // Per query (one 64-lane wavefront):
 //   1. the search radius: the particle's distance from the previous search
-//      widened by kHintSlack when that is usable, else the smallest, over
-//      three windows of k consecutive Morton slots holding the query, of the
-//      window's largest d^2 (each window holds k-1 others, so that is an upper
-//      bound of the (k-1)-th d^2), capped by the maximum search scale;
+//      widened by kHintSlack when that is usable, else the (k-1)-th distance
+//      to the others in a window of Morton slots about the query (an upper
+//      bound of the one sought), capped by the maximum search scale;
 //   2. a depth-first traversal of the box tree in Morton order, kPop nodes at
 //      a time: each lane tests child boxes against the query's sphere (the
 //      conservative single-precision test of gd_knn.hpp); passing internal
@@ -16,7 +15,7 @@
 //      bucket buffer.  Levels grow from the top of the stack down, so the
 //      level-1 nodes of a batch lie left of its other nodes and the buckets
 //      come out in ascending order;
-//   3. the buffered buckets' slots are evaluated four per lane: every other
+//   3. the buffered buckets' slots are evaluated kEval per lane: every other
 //      at or below the cut (d^2, slot) <= (R2, J) joins an LDS list of
 //      (d^2, slot) pairs, compacted across the wavefront in ascending slot
 //      order.  When the list would overflow, it is cut in place to its k-1
@@ -39,7 +38,7 @@ namespace gd {
 
 constexpr int kPop = 8;          // nodes expanded at a time, eight lanes each
 constexpr int kWBuf = 128;       // buckets waiting for evaluation: flushed from 64 on
-constexpr int kSelBins = 256;    // bins of the selection's distance histogram
+constexpr int kEval = 2;         // slots a lane evaluates at a time
 
 // A level's nodes join the stack only when fewer than kPop nodes of lower
 // levels were on it (a batch takes them all), so each level has at most
@@ -49,11 +48,12 @@ constexpr int kWStack = (kMaxTreeLevels - 1) * kPop * kFan;
 // NL: (d^2, slot) pairs a query keeps
 template <int NL>
 struct WaveLds {
+    static constexpr int kBins = NL > 192 ? 256 : 64;  // of the selection's distance histogram
     uint64_t key[NL];        // d^2 as its bit pattern
     int32_t slot[NL];        // ascending
     int32_t stack[kWStack];  // node: level << 27 | index
     int32_t buf[kWBuf];      // bucket indices, ascending
-    uint32_t hist[kSelBins];
+    uint32_t hist[kBins];
     int32_t bnd[kWave];      // list places of the boundary bin's pairs
 };
 
@@ -62,7 +62,7 @@ __device__ inline uint64_t lanes_below(int lane) { return (uint64_t(1) << lane) 
 
 // The need-th smallest (key, slot) of the list's n >= need >= 1 pairs, whose
 // keys are d^2 <= R2: a histogram of d^2, linear over [0, R2], finds the bin
-// that holds it; that bin's pairs (about n / kSelBins of them) are ranked one
+// that holds it; that bin's pairs (one or two as a rule) are ranked one
 // against all.  A bin of more than 64 pairs (many equal distances) is
 // resolved by bisection on the key's bits instead, and equal keys by their
 // order in the list, which is the slot order.  Sorting
@@ -73,7 +73,7 @@ template <int NL>
 __device__ __forceinline__ void select_pair(WaveLds<NL>& L, int n, int need, double R2, int lane, uint64_t& T, int32_t& J)
 {
     constexpr int NP = NL / kWave;
-    constexpr int NB = kSelBins / kWave;
+    constexpr int kSelBins = WaveLds<NL>::kBins, NB = kSelBins / kWave;
     uint64_t key[NP];
 #pragma unroll
     for (int b = 0; b < NB; ++b) L.hist[b * kWave + lane] = 0;
@@ -221,44 +221,48 @@ __device__ __forceinline__ void knn_wave_query(const KnnArgs& A, int q, WaveLds<
     {
         const double hv = A.hint[q] * kHintSlack;
         if (hv > 0.0 && hv < INFINITY) {
-            const FBox* tb = A.boxes + A.T.off[A.T.levels - 1];
-            double e2 = 0.0;
-#pragma unroll
-            for (int a = 0; a < 3; ++a) {
-                float lo = INFINITY, hi = -INFINITY;
-#pragma unroll
-                for (int c = 0; c < kFan; ++c) {
-                    lo = fminf(lo, tb[c].lo[a]);
-                    hi = fmaxf(hi, tb[c].hi[a]);
-                }
-                const double ext = double(hi) - double(lo);
-                e2 += ext * ext;
-            }
-            if (hv * hv <= e2) R2hint = hv * hv;
+            if (hv * hv <= diagonal2(A.h)) R2hint = hv * hv;
         }
     }
-    // the window bound (computed only when needed)
-    auto window_bound = [&]() {
-        const int span = na < k ? na : k;
-        const int fmaxs = na - span;
-        int f[3] = {q - span + 1, q - span / 2 + 1, q};
-        double w[3] = {0.0, 0.0, 0.0};
+    // without one, the (k-1)-th distance to the others among the NL slots
+    // about the query: an upper bound of the distance sought, some 1.15 times
+    // it at the median in a disk or a uniform box
+    auto window_bound = [&]() __attribute__((always_inline)) {
+        int lo = q - NL / 2;
+        lo = lo + NL > na ? na - NL : lo;
+        lo = lo < 0 ? 0 : lo;
+        int m = 0;
+        double far = 0.0;
 #pragma unroll
-        for (int t = 0; t < 3; ++t) {
-            f[t] = f[t] < 0 ? 0 : (f[t] > fmaxs ? fmaxs : f[t]);
-            for (int j = f[t] + lane; j < f[t] + span; j += kWave) w[t] = fmax(w[t], sep2_slot<PER>(A, qp, j));
-            w[t] = wave_max_d(w[t]);
+        for (int p = 0; p < NP; ++p) {
+            const int j = lo + p * kWave + lane;
+            const bool ok = j < na && j != q;
+            const double d2 = sep2_slot<PER>(A, qp, ok ? j : q);
+            const bool in = ok && d2 < INFINITY;
+            const uint64_t bal = __ballot(in);
+            if (in) {
+                const int at = m + int(__popcll(bal & lanes_below(lane)));
+                L.key[at] = d2_key(d2);
+                L.slot[at] = j;
+                far = fmax(far, d2);
+            }
+            m += int(__popcll(bal));
         }
-        return fmin(w[0], fmin(w[1], w[2]));
+        __syncthreads();
+        if (m < need) return double(INFINITY);  // (fewer than k slots: every other is a neighbour)
+        uint64_t T;
+        int32_t J;
+        select_pair<NL>(L, m, need, wave_max_d(far), lane, T, J);
+        return __longlong_as_double((long long)T);
     };
 
     bool use_hint = R2hint < INFINITY;
-    double R2cap = use_hint ? A.rmax2 : fmin(window_bound(), A.rmax2);
+    double R2cap = A.rmax2;
     int n = 0;
     double R2 = 0.0;
     int32_t Jc = INT32_MAX;
-    const int top = A.T.levels - 1;  // the root's children: the boxes of the top stored level
     for (;;) {
+        if (!use_hint) R2cap = fmin(window_bound(), A.rmax2);
         R2 = use_hint ? fmin(R2hint, R2cap) : R2cap;
         Jc = INT32_MAX;
         n = 0;
@@ -298,39 +302,39 @@ __device__ __forceinline__ void knn_wave_query(const KnnArgs& A, int q, WaveLds<
             n = kept;
             __syncthreads();
         };
-        // evaluate the buffered buckets in order, 64 at a time, four slots per lane
+        // evaluate the buffered buckets in order, kEval slots per lane at a time
         auto flush = [&]() __attribute__((always_inline)) {
-            for (int b0 = 0; b0 < nbuf; b0 += kWave) {
-                const int nb = nbuf - b0 < kWave ? nbuf - b0 : kWave;
-                double d2[4];
-                int32_t jj[4];
-                bool acc[4];
+            constexpr int kStep = kWave * kEval / kBucket;  // buckets
+            for (int b0 = 0; b0 < nbuf; b0 += kStep) {
+                double d2[kEval];
+                int32_t jj[kEval];
+                bool acc[kEval];
                 int total = 0;
 #pragma unroll
-                for (int t = 0; t < 4; ++t) {
+                for (int t = 0; t < kEval; ++t) {
                     const int p = lane + kWave * t;
-                    const int b = p >> 2;
-                    const int j = b < nb ? L.buf[b0 + b] * kBucket + (p & 3) : -1;
+                    const int b = b0 + (p >> 2);
+                    const int j = b < nbuf ? L.buf[b] * kBucket + (p & 3) : -1;
                     const bool ok = j >= 0 && j < na && j != q;
                     jj[t] = ok ? j : -1;
                 }
                 // every lane reads a slot (a lane without one its own query)
-                // so that the four loads are in flight together
+                // so that the loads are in flight together
 #pragma unroll
-                for (int t = 0; t < 4; ++t) d2[t] = sep2_slot<PER>(A, qp, jj[t] >= 0 ? jj[t] : q);
+                for (int t = 0; t < kEval; ++t) d2[t] = sep2_slot<PER>(A, qp, jj[t] >= 0 ? jj[t] : q);
 #pragma unroll
-                for (int t = 0; t < 4; ++t) {
+                for (int t = 0; t < kEval; ++t) {
                     acc[t] = jj[t] >= 0 && (d2[t] < R2 || (d2[t] == R2 && jj[t] <= Jc));
                     total += int(__popcll(__ballot(acc[t])));
                 }
                 if (n + total > NL) {
                     cut_list();
 #pragma unroll
-                    for (int t = 0; t < 4; ++t)
+                    for (int t = 0; t < kEval; ++t)
                         acc[t] = acc[t] && (d2[t] < R2 || (d2[t] == R2 && jj[t] <= Jc));
                 }
 #pragma unroll
-                for (int t = 0; t < 4; ++t) {
+                for (int t = 0; t < kEval; ++t) {
                     const uint64_t bal = __ballot(acc[t]);
                     if (acc[t]) {
                         const int at = n + int(__popcll(bal & lanes_below(lane)));
@@ -343,11 +347,10 @@ __device__ __forceinline__ void knn_wave_query(const KnnArgs& A, int q, WaveLds<
             nbuf = 0;
             __syncthreads();
         };
-        // the root's children
+        // the walk starts on the lowest level of at most 64 nodes, a lane each
         {
-            const int lv = top;
-            const bool valid = lane < kFan && (uint32_t(lane) < uint32_t(A.T.cap[top])) &&
-                               ((live_children(na, top + 1, 0) >> lane) & 1u);
+            const int lv = A.T.start;
+            const bool valid = (int64_t(lane) << (2 + 3 * lv)) < na;  // the node holds active slots
             bool pass = false;
             if (valid) pass = box2f<PER>(A, qf, A.boxes[level_off(A.T, lv) + lane]) <= R2f;
             const uint64_t bal = __ballot(pass);
@@ -387,7 +390,6 @@ __device__ __forceinline__ void knn_wave_query(const KnnArgs& A, int q, WaveLds<
         }
         if (use_hint && n < need && R2hint < R2cap) {
             use_hint = false;  // the previous distance held too few others: again on the bound
-            R2cap = fmin(window_bound(), A.rmax2);
             continue;
         }
         break;
@@ -440,8 +442,13 @@ struct KnnWave {
         __shared__ WaveLds<NL> L;
         const int lane = threadIdx.x;
         if (W.list) {
+            // each die's workgroups take a contiguous range of the list, which
+            // is in Morton order where it is long (a run's first search)
             const int32_t nl = *W.count;
-            for (int64_t t = B.id; t < nl; t += B.n) knn_wave_query<PER, NL>(W.A, W.list[t], L, lane);
+            const int x = int(B.id % kXcd);
+            const int32_t hi = xcd_range_lo(x + 1, nl), step = int32_t((B.n - x + kXcd - 1) / kXcd);
+            for (int32_t t = xcd_range_lo(x, nl) + int32_t(B.id / kXcd); t < hi; t += step)
+                knn_wave_query<PER, NL>(W.A, W.list[t], L, lane);
         } else {
             const int64_t q = B.id;
             if (q < W.A.n) knn_wave_query<PER, NL>(W.A, int(q), L, lane);
@@ -450,16 +457,16 @@ struct KnnWave {
 };
 
 template <bool PER, int NL>
-__global__ __launch_bounds__(kWave) void k_knn_wave(WaveArgs W)
+__global__ __launch_bounds__(kWave, NL == 192 ? 7 : 5) void k_knn_wave(WaveArgs W)
 {
     KnnWave<PER, NL>::body(W, Blk{W.list ? int64_t(blockIdx.x) : xcd_block(), int64_t(gridDim.x)});
 }
 
-// the list's length for neighbourhoods of k: k - 1 pairs kept by a cut and a
-// flush of 4 * kWave more always fit
-constexpr int kListSmall = 384, kListLarge = 512;
-constexpr int kSmallK = kListSmall - 4 * kWave + 1;
-static_assert(kListLarge >= (kMaxK - 1) + 4 * kWave, "a flush after a cut must fit the list");
+// the list's length for neighbourhoods of k: the k - 1 pairs a cut keeps and
+// an evaluation step of 64 kEval more always fit
+constexpr int kListSmall = 192, kListLarge = 384;
+constexpr int kSmallK = kListSmall - kEval * kWave + 1;
+static_assert(kListLarge >= (kMaxK - 1) + kEval * kWave, "a step after a cut must fit the list");
 
 void launch_knn_wave(const KnnArgs& A, bool per, const int32_t* list, const int32_t* count, int64_t nblocks,
                      hipStream_t st)
