@@ -65,33 +65,69 @@ struct RatesArgs {
     int64_t n_all;  // length of the snapshot: neighbour indices lie in [0, n_all)
 };
 
-constexpr int kGather = 4;  // neighbours whose slot and record loads are in flight together
+constexpr int kGather = 4;  // neighbours whose slot and record loads a lane has in flight together
 
-// slots row[s0 .. s0+kGather) (those below cmax) and the snapshot records of
-// the valid ones; invalid slots are left for the caller to flag
-__device__ inline void gather_neighbours(const int32_t* row, int s0, int cmax, int64_t n, const double4* snap,
+// A particle's pairs are shared by LANES = 1, 2 or 4 neighbouring lanes: lane
+// `sub` takes the slots sub, sub + LANES, ...  The kGather slots of the lane
+// from s0 on (those below cmax) and the snapshot records of the valid ones;
+// invalid slots are left for the caller to flag.
+template <int LANES>
+__device__ inline void gather_neighbours(const int32_t* row, int s0, int sub, int cmax, int64_t n, const double4* snap,
                                          int (&jj)[kGather], double4 (&rec)[kGather])
 {
 #pragma unroll
-    for (int t = 0; t < kGather; ++t) jj[t] = s0 + t < cmax ? row[s0 + t] : -1;
+    for (int t = 0; t < kGather; ++t) {
+        const int s = s0 + t * LANES + sub;
+        jj[t] = s < cmax ? row[s] : -1;
+    }
 #pragma unroll
     for (int t = 0; t < kGather; ++t) rec[t] = (jj[t] >= 0 && jj[t] < n) ? snap[jj[t]] : make_double4(0.0, 0.0, 0.0, 0.0);
 }
 
+// lane l of every group of LANES lanes read by the whole group (DPP quad
+// permutation, no LDS)
+template <int LANES, int l>
+__device__ inline double group_lane(double x)
+{
+    constexpr int c = LANES == 4 ? l * 0x55 : (LANES == 2 ? (l | (l << 2) | ((l + 2) << 4) | ((l + 2) << 6)) : 0xE4);
+    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(x), c, 0xf, 0xf, true);
+    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(x), c, 0xf, 0xf, true);
+    return __hiloint2double(hi, lo);
+}
+
+// sum + the group's values in lane order, that is in slot order: the same
+// additions as one lane's over the slots (a lane without a slot adds +0)
+template <int LANES>
+__device__ inline double add_in_order(double sum, double v)
+{
+    if (LANES == 1) return sum + v;
+    sum = sum + group_lane<LANES, 0>(v);
+    sum = sum + group_lane<LANES, 1>(v);
+    if (LANES == 4) {
+        sum = sum + group_lane<LANES, LANES == 4 ? 2 : 0>(v);
+        sum = sum + group_lane<LANES, LANES == 4 ? 3 : 0>(v);
+    }
+    return sum;
+}
+
+template <int LANES>
 struct Rates {
     using Args = RatesArgs;
     static constexpr int kThreads = 256;
     static __device__ __forceinline__ void body(const Args& A, Blk B);
 };
 
+template <int LANES>
 __global__ __launch_bounds__(256) void k_rates(RatesArgs A)
 {
-    Rates::body(A, Blk{xcd_block(), int64_t(gridDim.x)});
+    Rates<LANES>::body(A, Blk{xcd_block(), int64_t(gridDim.x)});
 }
 
-__device__ __forceinline__ void Rates::body(const Args& A, Blk B)
+template <int LANES>
+__device__ __forceinline__ void Rates<LANES>::body(const Args& A, Blk B)
 {
-    const int64_t i = B.id * int64_t(blockDim.x) + threadIdx.x;
+    const int64_t i = (B.id * int64_t(blockDim.x) + threadIdx.x) / LANES;
+    const int sub = int(threadIdx.x) % LANES;
     if (i >= A.P.n) return;
     const int k = A.P.k;
     const bool phys = A.P.kernel == GD_KERNEL_PHYSICAL;
@@ -105,34 +141,38 @@ __device__ __forceinline__ void Rates::body(const Args& A, Blk B)
         own_terms(A.P, q, mi, phys ? A.snap_own[i].y : 0.0, true, w);
         if (!(mi > 0.0) || !isfinite(mi)) set_status(A.ws, GD_DEV_NONFINITE);
         const int cmax = c < k ? c : k;
-        // neighbours four at a time: their slots, then their records, in flight
-        // together; the pairs are then taken in slot order as before
-        for (int s0 = 0; s0 < cmax; s0 += kGather) {
+        // neighbours kGather at a time: their slots, then their records, in
+        // flight together; the pairs are then taken in slot order
+        for (int s0 = 0; s0 < cmax; s0 += kGather * LANES) {
             int jj[kGather];
             double4 rec[kGather];
-            gather_neighbours(A.nbr + i * k, s0, cmax, A.n_all, A.snap, jj, rec);
+            gather_neighbours<LANES>(A.nbr + i * k, s0, sub, cmax, A.n_all, A.snap, jj, rec);
 #pragma unroll
             for (int t = 0; t < kGather; ++t) {
-            const int s = s0 + t;
-            if (s >= cmax) break;
-            const int j = jj[t];
-            if (j < 0 || j >= A.n_all) {
-                set_status(A.ws, GD_DEV_INTERNAL);
-                continue;
-            }
-            const double4 sn = rec[t];
-            const double mj = sn.x;
-            Pair o;
-            pair_eval<true>(A.P, q, w, mj, phys ? sn.y : 0.0, phys ? sn.z : 0.0, sn.w, o);
-            lam = lam + o.lam_star;
-            if (A.lam_pair) A.lam_pair[i * k + s] = o.lam_star;
-            double pa, pb;
-            pair_moments(o, w, mj, pa, pb);
-            sa = sa + pa;
-            sb = sb + pb;
+                if (s0 + t * LANES >= cmax) break;  // the same in the particle's lanes
+                const int s = s0 + t * LANES + sub;
+                const int j = jj[t];
+                double pl = 0.0, pa = 0.0, pb = 0.0;
+                if (LANES == 1 || s < cmax) {
+                    if (j < 0 || j >= A.n_all) {
+                        set_status(A.ws, GD_DEV_INTERNAL);
+                        if (LANES == 1) continue;
+                    } else {
+                        const double4 sn = rec[t];
+                        Pair o;
+                        pair_eval<true>(A.P, q, w, sn.x, phys ? sn.y : 0.0, phys ? sn.z : 0.0, sn.w, o);
+                        pl = o.lam_star;
+                        if (A.lam_pair) A.lam_pair[i * k + s] = pl;
+                        pair_moments(o, w, sn.x, pa, pb);
+                    }
+                }
+                lam = add_in_order<LANES>(lam, pl);
+                sa = add_in_order<LANES>(sa, pa);
+                sb = add_in_order<LANES>(sb, pb);
             }
         }
     }
+    if (sub != 0) return;
     if (A.lam_pair)
         for (int s = (c > 1 ? c : 0); s < k; ++s) A.lam_pair[i * k + s] = 0.0;
     A.lam[i] = lam;
@@ -142,20 +182,24 @@ __device__ __forceinline__ void Rates::body(const Args& A, Blk B)
 
 // The same pass with the single-precision pair form (gd_problem.rates_fp32):
 // float pair terms, summed in FP64 in slot order.
+template <int LANES>
 struct RatesF32 {
     using Args = RatesArgs;
     static constexpr int kThreads = 256;
     static __device__ __forceinline__ void body(const Args& A, Blk B);
 };
 
+template <int LANES>
 __global__ __launch_bounds__(256) void k_rates_f32(RatesArgs A)
 {
-    RatesF32::body(A, Blk{xcd_block(), int64_t(gridDim.x)});
+    RatesF32<LANES>::body(A, Blk{xcd_block(), int64_t(gridDim.x)});
 }
 
-__device__ __forceinline__ void RatesF32::body(const Args& A, Blk B)
+template <int LANES>
+__device__ __forceinline__ void RatesF32<LANES>::body(const Args& A, Blk B)
 {
-    const int64_t i = B.id * int64_t(blockDim.x) + threadIdx.x;
+    const int64_t i = (B.id * int64_t(blockDim.x) + threadIdx.x) / LANES;
+    const int sub = int(threadIdx.x) % LANES;
     if (i >= A.P.n) return;
     const int k = A.P.k;
     const bool phys = A.P.kernel == GD_KERNEL_PHYSICAL;
@@ -179,36 +223,69 @@ __device__ __forceinline__ void RatesF32::body(const Args& A, Blk B)
         }
         if (!(mi > 0.0) || !isfinite(mi)) set_status(A.ws, GD_DEV_NONFINITE);
         const int cmax = c < k ? c : k;
-        for (int s0 = 0; s0 < cmax; s0 += kGather) {
+        for (int s0 = 0; s0 < cmax; s0 += kGather * LANES) {
             int jj[kGather];
             double4 rec[kGather];
-            gather_neighbours(A.nbr + i * k, s0, cmax, A.n_all, A.snap, jj, rec);
+            gather_neighbours<LANES>(A.nbr + i * k, s0, sub, cmax, A.n_all, A.snap, jj, rec);
 #pragma unroll
             for (int t = 0; t < kGather; ++t) {
-            const int s = s0 + t;
-            if (s >= cmax) break;
-            const int j = jj[t];
-            if (j < 0 || j >= A.n_all) {
-                set_status(A.ws, GD_DEV_INTERNAL);
-                continue;
-            }
-            const double4 sn = rec[t];
-            PairF o;
-            pair_eval_f32(A.P, qf, mi, rmi, si, Sti, sn.x, phys ? float(sn.y) : 0.0f, phys ? sn.z : 0.0, o);
-            lam = lam + double(o.lam_star);
-            if (A.lam_pair) A.lam_pair[i * k + s] = double(o.lam_star);
-            float pa, pb;
-            pair_moments_f32(o, mJf, mJ2f, pa, pb);
-            sa = sa + double(pa);
-            sb = sb + double(pb);
+                if (s0 + t * LANES >= cmax) break;
+                const int s = s0 + t * LANES + sub;
+                const int j = jj[t];
+                double pl = 0.0;
+                float pa = 0.0f, pb = 0.0f;
+                if (LANES == 1 || s < cmax) {
+                    if (j < 0 || j >= A.n_all) {
+                        set_status(A.ws, GD_DEV_INTERNAL);
+                        if (LANES == 1) continue;
+                    } else {
+                        const double4 sn = rec[t];
+                        PairF o;
+                        pair_eval_f32(A.P, qf, mi, rmi, si, Sti, sn.x, phys ? float(sn.y) : 0.0f, phys ? sn.z : 0.0, o);
+                        pl = double(o.lam_star);
+                        if (A.lam_pair) A.lam_pair[i * k + s] = pl;
+                        pair_moments_f32(o, mJf, mJ2f, pa, pb);
+                    }
+                }
+                lam = add_in_order<LANES>(lam, pl);
+                sa = add_in_order<LANES>(sa, double(pa));
+                sb = add_in_order<LANES>(sb, double(pb));
             }
         }
     }
+    if (sub != 0) return;
     if (A.lam_pair)
         for (int s = (c > 1 ? c : 0); s < k; ++s) A.lam_pair[i * k + s] = 0.0;
     A.lam[i] = lam;
     A.a[i] = sa;
     A.b[i] = sb;
+}
+
+// Lanes a particle's pairs are shared by: a set that leaves the SIMDs with a
+// wavefront or two waits on one lane's chain of pairs.  n counts all particles
+// of the launch.  Measured intervals with 1, 2 and 4 lanes: boxes without a
+// search 59 / 50 / 44 us at 4096 particles, 65 / 56 / 52 at 32,768, 73 / 66 /
+// 66 at 65,536, 98 / 99 / 96 at 131,072; disks 148 / 135 / 127 us at 10,007,
+// 179 / 166 / 161 at 32,768, 235 / 226 / 228 at 65,536, 305 / 306 / 305 at
+// 100,003, 550 / 553 / 565 at 262,144 (each lane repeats the particle's own
+// terms).
+constexpr int64_t kRates4 = 49152, kRates2 = 98304;
+
+static int rates_lanes(int64_t n) { return n <= kRates4 ? 4 : (n <= kRates2 ? 2 : 1); }
+
+static void launch_rates_pass(const RatesArgs& A, bool f32, hipStream_t st)
+{
+    const int lanes = rates_lanes(A.P.n);
+    const dim3 g(unsigned(cdiv(A.P.n * lanes, 256))), b(256);
+    if (f32) {
+        if (lanes == 4) hipLaunchKernelGGL(k_rates_f32<4>, g, b, 0, st, A);
+        else if (lanes == 2) hipLaunchKernelGGL(k_rates_f32<2>, g, b, 0, st, A);
+        else hipLaunchKernelGGL(k_rates_f32<1>, g, b, 0, st, A);
+    } else {
+        if (lanes == 4) hipLaunchKernelGGL(k_rates<4>, g, b, 0, st, A);
+        else if (lanes == 2) hipLaunchKernelGGL(k_rates<2>, g, b, 0, st, A);
+        else hipLaunchKernelGGL(k_rates<1>, g, b, 0, st, A);
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -757,8 +834,7 @@ int launch_rates(const gd_problem* p, const gd_particles* s, const gd_neighbors*
     A.ws = ws;
     A.n_all = n;
     A.snap_own = snap;
-    if (p->rates_fp32) hipLaunchKernelGGL(k_rates_f32, dim3(g), dim3(256), 0, st, A);
-    else hipLaunchKernelGGL(k_rates, dim3(g), dim3(256), 0, st, A);
+    launch_rates_pass(A, p->rates_fp32 != 0, st);
     launch_plan(p, m, s->M, A.a, A.b, n, iv, ws, L, st);
     prof_mark(GD_PROF_RATES, 1, st);
     return 0;
@@ -821,11 +897,7 @@ int launch_rates_group(const gd_problem* p, const gd_particles* s, const gd_neig
     A.b = at<double>(ws, L.b) + lo;
     A.ws = ws;
     A.n_all = n;
-    const int g = int((cnt + 255) / 256);
-    if (cnt > 0) {
-        if (p->rates_fp32) hipLaunchKernelGGL(k_rates_f32, dim3(g), dim3(256), 0, st, A);
-        else hipLaunchKernelGGL(k_rates, dim3(g), dim3(256), 0, st, A);
-    }
+    if (cnt > 0) launch_rates_pass(A, p->rates_fp32 != 0, st);
     launch_plan(p, m + lo, s->M + lo, A.a, A.b, cnt, iv, ws, L, st);
     hipLaunchKernelGGL(k_group_clamp, dim3(1), dim3(64), 0, st, iv, int(group), int(n_groups),
                        reinterpret_cast<const unsigned long long*>(rows), sched);
@@ -843,6 +915,9 @@ void many_rates(ManyBuilder& B, const std::vector<ManyRun>& R, bool own_snapshot
     std::vector<RatesArgs> ra(nr);
     std::vector<ReduceArgs> pl(nr);
     std::vector<int64_t> nb(nr), nred(nr), f64(nr), f32(nr);
+    int64_t total = 0;
+    for (size_t r = 0; r < nr; ++r) total += R[r].p.n;
+    const int lanes = rates_lanes(total);
     for (size_t r = 0; r < nr; ++r) {
         const ManyRun& x = R[r];
         const gd_problem* p = &x.p;
@@ -871,14 +946,22 @@ void many_rates(ManyBuilder& B, const std::vector<ManyRun>& R, bool own_snapshot
         A.ws = x.ws;
         A.n_all = x.n_all >= 0 ? x.n_all : n;
         nb[r] = cdiv(n, 256);
-        f64[r] = p->rates_fp32 ? 0 : nb[r];
-        f32[r] = p->rates_fp32 ? nb[r] : 0;
+        f64[r] = p->rates_fp32 ? 0 : cdiv(n * lanes, 256);
+        f32[r] = p->rates_fp32 ? cdiv(n * lanes, 256) : 0;
         nred[r] = std::min<int64_t>(kRedBlocks, std::max<int64_t>(1, cdiv(n, B.tune.red_div)));
         pl[r] = reduce_args(p, m, s->M, A.a, A.b, n, x.iv, x.ws, x.L);
     }
     if (own_snapshot) B.add<Snapshot>(sn, nb);
-    B.add<Rates>(ra, f64);
-    B.add<RatesF32>(ra, f32);
+    if (lanes == 4) {
+        B.add<Rates<4>>(ra, f64);
+        B.add<RatesF32<4>>(ra, f32);
+    } else if (lanes == 2) {
+        B.add<Rates<2>>(ra, f64);
+        B.add<RatesF32<2>>(ra, f32);
+    } else {
+        B.add<Rates<1>>(ra, f64);
+        B.add<RatesF32<1>>(ra, f32);
+    }
     B.add<Reduce<0>>(pl, nred);
 }
 
