@@ -255,13 +255,13 @@ int32_t gd_reshuffle_neighbors_static(const gd_problem* p, const gd_neighbors* n
                                       void* stream);
 
 /* Sampling over many independent runs (boxes) at once.  gd_sample_collisions
- * is, in order: the per-lane pass (each particle's first events; a particle
- * with more is recorded in the workspace at that event boundary), the pass
- * that runs the rest of every recorded particle with one wavefront each, and
- * the audit.  The three calls below make the same passes with the second
- * one shared by many runs, so that the recorded particles of every run are
- * sampled in one launch.  Results are those of gd_sample_collisions, bit for
- * bit.
+ * is, in order: the screen (the particles with an event in the interval are
+ * listed in the workspace, the others keep their mass), the pass that runs
+ * the interval of every listed particle with half a wavefront or a whole one
+ * each, and the audit.  The three calls below make the same passes with the
+ * second one shared by many runs, so that the listed particles of every run
+ * are sampled in one launch.  Results are those of gd_sample_collisions, bit
+ * for bit.
  *
  * The table is device memory owned by the caller, gd_sample_table_size(nslot)
  * bytes (1 <= nslot <= 4096).  Per interval, for each run r in [0, nslot):
@@ -325,8 +325,8 @@ int32_t gd_transport_dt(const gd_problem* p, const gd_particles* st, const gd_ne
  * gd_push make; Sect. 4.3.1: many small independent domains on one device).
  * Every stage of the interval -- bounding box, Morton keys and radix sort,
  * permutation, search tree, neighbour search, snapshot and rates, bin sums and
- * plan, sampling (the per-lane pass, then one pass over the deferred
- * particles of all runs), audit, push -- is one launch over all runs: the
+ * plan, sampling (the screen, then one pass over the listed particles of
+ * all runs), audit, push -- is one launch over all runs: the
  * runs' blocks follow one another in one grid, and a block finds its run and
  * that run's arguments through tables the library keeps in device memory.
  * A run's results are those of its own calls, bit for bit, except that the
@@ -347,12 +347,13 @@ int32_t gd_transport_dt(const gd_problem* p, const gd_particles* st, const gd_ne
  * (gd_many_create allocates them with hipMalloc on the current device).
  *
  * gd_many_tuning holds launch shapes only; no choice changes a result:
- *   knn_tile      1: the shared-candidate-tile search first (k <= 33), 0: the
- *                 per-lane search for every query;
+ *   knn_tile      1: the search the library picks by the runs' total size
+ *                 (k <= 33: shared candidate tiles or a wavefront per query),
+ *                 0: the per-lane search for every query;
  *   fallback_div  wavefronts of the tile search's fallback pass: n / fallback_div per run;
- *   event_div     workgroups of the per-lane sampling pass: n / event_div per run (<= 512);
+ *   event_div     accepted, without effect (the sampling has one pass);
  *   red_div       workgroups of each bin sum: n / red_div per run (<= 256);
- *   heavy_blocks  workgroups (4 wavefronts each) of the pass over the deferred particles.
+ *   heavy_blocks  workgroups (4 wavefronts each) of the pass over the listed particles.
  * Zero fields take the defaults (1, 256, 512, 2048, 768).
  *
  * gd_many_interval enqueues one interval of every run on `stream`; the host

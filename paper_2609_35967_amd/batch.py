@@ -12,12 +12,12 @@ workspace, and its own adaptive interval.  Three forms step every box:
   by timing candidates on the batch itself (from a saved device state, so
   every candidate runs the same intervals) and records what it measured;
 * ``replay`` -- one HIP graph holding two intervals of every box.  Per
-  interval: each box's neighbour search, rates and per-lane sampling pass on
-  its stream (boxes dealt to a few streams, largest first, each to the stream
+  interval: each box's neighbour search, rates and sampling screen on its
+  stream (boxes dealt to a few streams, largest first, each to the stream
   with the least work so far, so that the small launches of different boxes
   overlap), its sampling arguments written to a slot of a shared table; then
-  one launch samples the particles that outlast the per-lane pass in every
-  box (gd_sample_table_run), and each box's audit follows on its stream.
+  one launch samples the listed particles of every box
+  (gd_sample_table_run), and each box's audit follows on its stream.
   Two intervals per graph: the Morton permutation alternates between a box's
   two state buffers and the sampling between its two mass buffers, so after
   two intervals every buffer is back in its place and the graph can be
@@ -118,7 +118,6 @@ class BoxBatch:
         torch.cuda.synchronize()
 
     SPACE = dict(sets=(1, 2, 4, 8), knn_tile=(1, 0), heavy_blocks=(256, 512, 768, 1024, 1536),
-                 event_div=(256, 512, 1024, 2048),
                  fallback_div=(64, 256, 1024), red_div=(512, 2048, 8192))
 
     def tune(self, intervals: int = 2, space: dict | None = None) -> dict:

@@ -352,7 +352,7 @@ class Engine:
                                                      self._s()))
 
     def sample_deferred(self, table, table_bytes: int, slot: int):
-        """The per-lane pass of sampling; the run's arguments go to table slot `slot`
+        """The screen of sampling; the run's arguments go to table slot `slot`
         (the rest runs in gd_sample_table_run, then sample_audit)."""
         s = self.A.struct()
         check(self.lib.gd_sample_collisions_deferred(

@@ -58,20 +58,16 @@ struct alignas(256) WsHeader {
     double gM[kNBin];            // plan: sum of M per merged group
     double scratch[16];
     int32_t xq[4][8];            // per-die work queues of the gather-heavy kernels
-    int32_t heavy_n;             // sampling: particles handed to the wavefront-per-particle pass
-    int32_t heavy_next;          // sampling: next of them to take
     int32_t knn_fb_n;            // neighbour search: queries the tile search handed back
     uint32_t red_done;           // controller sums: blocks done (wraps to 0 at the last)
-    int32_t mc_seg[kXcd];        // sampling: particles with an event, per die's segment of the list
-    int32_t mc_next;             // sampling: next group of them to take
-    int32_t heavy_n0;            // sampling: particles the screen sent straight to the wavefront pass (at the list's end)
-    int32_t heavy_next0;         // sampling: next of those to take
+    int32_t mc_n, mc_early_n;    // sampling: particles with events, from the list's start and from its end
+    int32_t mc_next;             // sampling: next chunk of them to take
 };
 
 // Workspace layout (byte offsets), identical on host and device.
 struct Layout {
     size_t hdr, keys0, keys1, vals0, vals1, hist, red, pos4, boxes,
-        snap, a, b, part, hint, heavy, mclist, stats, total;
+        snap, a, b, part, hint, mclist, stats, total;
     int64_t n;
     int32_t k;
     // radix sort: keys per thread, blocks, blocks per group of the digit
@@ -139,8 +135,7 @@ __host__ inline Layout make_layout(int64_t n, int32_t k)
     L.b = take(8 * nn);
     L.part = take(sizeof(double) * 8 * kNBin * kRedBlocks);
     L.hint = take(8 * nn);
-    L.heavy = take(24 * nn);  // sampling: (slot, events, time, mass) of deferred particles
-    L.mclist = take(4 * ((nn + 255) / 256) * 256);  // sampling: particles with an event, a segment per die
+    L.mclist = take(4 * nn);  // sampling: particles with an event
 #ifdef GD_KNN_STATS
     L.stats = take(32 * nn);
 #endif

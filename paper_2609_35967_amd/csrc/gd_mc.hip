@@ -1,9 +1,8 @@
 // gd_mc.hip -- Monte Carlo sampling of collision events against the frozen
 // neighbourhood (Sect. 2.5.3).  The post-interval audit is in gd_rates.hip.
 //
-// One lane per particle.  The particle draws waiting times
-// dt_w = -ln(U_w)/lambda*_i (Gillespie); an event happens iff dt_w fits in the
-// rest of the interval.  Its partner is the first slot whose inclusive prefix of
+// A particle draws waiting times dt_w = -ln(U_w)/lambda*_i (Gillespie); an
+// event happens iff dt_w fits in the rest of the interval.  Its partner is the first slot whose inclusive prefix of
 // lambda*_ij exceeds U_p lambda*_i, its channel the first whose cumulative rate
 // exceeds U_c lambda*_ij; the outcome (Sect. 2.5.2) updates only this particle,
 // after which every lambda*_ij is recomputed from the new mass against the
@@ -41,26 +40,18 @@ struct McArgs {
     int32_t interval_on_device;  // take the index from iv->n_intervals
     void* ws;
     unsigned long long* ev_counter;
-    // particles still sampling after `budget` events are handed, at that
-    // event boundary, to a pass that runs one wavefront per particle
-    int32_t budget;
-    struct Deferred* heavy;
-    int32_t* heavy_n;
-    int32_t* heavy_next;
-    int64_t n_all;  // length of the snapshot: neighbour indices lie in [0, n_all)
-    int32_t* list;       // particles with an event (screen -> event pass), a segment per die
-    int32_t* list_seg;   // the segments' counts
-    int32_t* list_next;  // the event pass's next group
-    const int64_t* interval_at;  // when set: the interval index (a spatial group's number in planning order)
-    const int32_t* active;       // when set and 0: the run has no interval now (its deferred list is skipped)
-    // the screen sends a particle whose expected events lambda*_i dt_exe reach
-    // early_events (0: none) straight to the wavefront-per-particle pass, to
-    // entries n - 1, n - 2, ... of `heavy` (the event pass defers to entries
-    // 0, 1, ...; no particle is in both), counted by heavy_n0, taken by
-    // heavy_next0
+    // the particles with an event, from the screen: entry e < n in list[e],
+    // and those that expect many (early_events or more; 0: none apart) in
+    // list[n - 1 - e], counted by list_n and early_n; next is the sampling's
+    // next chunk
+    int32_t* list;
+    int32_t* list_n;
+    int32_t* early_n;
+    int32_t* next;
     double early_events;
-    int32_t* heavy_n0;
-    int32_t* heavy_next0;
+    int64_t n_all;  // length of the snapshot: neighbour indices lie in [0, n_all)
+    const int64_t* interval_at;  // when set: the interval index (a spatial group's number in planning order)
+    const int32_t* active;       // when set and 0: the run has no interval now (its list is skipped)
 };
 
 __device__ inline uint32_t mc_interval(const McArgs& A)
@@ -69,430 +60,220 @@ __device__ inline uint32_t mc_interval(const McArgs& A)
     return A.interval_on_device ? uint32_t(A.iv->n_intervals) : A.interval;
 }
 
-// a particle handed over after e events, at time t of the interval, with mass m
-struct Deferred {
-    int32_t i;
-    int32_t e;
-    double t;
-    double m;
-};
-
 constexpr int kEventCap = 1 << 24;  // safety stop per particle and interval (status-flagged)
-constexpr int kLaneEvents = 4;      // events a lane samples before handing its particle over
-constexpr int kHeavyBlocks = 768;   // blocks (4 wavefronts each) of the wavefront-per-particle pass: 3 per SIMD
-constexpr int kEventBlocks = 512;   // blocks (4 wavefronts each) of the event pass: two per SIMD
-constexpr int kSmallList = 3072;    // at most this many particles with events: all to the wavefront pass
-constexpr double kEarlyEvents = 64.0;  // expected events from which the screen sends a particle straight to that pass
-constexpr int kEarlyBlocks = 256;      // blocks (4 wavefronts each) for those particles beside the event pass
+constexpr int kSampleBlocks = 1024;  // blocks (4 wavefronts each) of the sampling pass: 4 per SIMD
+// Expected events from which a particle is sampled first, and the most
+// particles a wavefront takes at a time.  On the warm 1M disk (362K particles
+// with events, 2.26M events, the longest chain 1.4K) an interval takes 3.66 ms
+// with 64 and 32, 3.50 with 32 and 32, 3.34 with 32 and 8, 3.31 with 16 and 8,
+// 3.39 with 8 and 16: later starts and larger chunks leave a longer tail.
+constexpr double kEarlyEvents = 16.0;
+constexpr int kChunk = 8;
 
-template <int KP2>
-__device__ inline double prefix_rates_f32(const McArgs& A, const QCtxF& q, const int32_t* row, int c, double mi,
-                                          float si, float Sti, double (&pre)[KP2])
-{
-    const bool phys = A.P.kernel == GD_KERNEL_PHYSICAL;
-    double li = 0.0;
-#pragma unroll
-    for (int s = 0; s < KP2; ++s) {
-        if (s < c) {
-            int j = row[s];
-            if (j < 0 || j >= A.n_all) {
-                set_status(A.ws, GD_DEV_INTERNAL);
-                j = 0;
-            }
-            const double4 sn = A.snap[j];
-            PairF o;
-            pair_eval_f32(A.P, q, mi, 1.0 / mi, si, Sti, sn.x, phys ? float(sn.y) : 0.0f, phys ? sn.z : 0.0, o);
-            li = li + double(o.lam_star);
-        }
-        pre[s] = li;
-    }
-    return li;
-}
-
-template <int KP2>
-__device__ inline double prefix_rates(const McArgs& A, const QCtx& q, const int32_t* row, int c, const Own& w,
-                                      double (&pre)[KP2])
-{
-    const bool phys = A.P.kernel == GD_KERNEL_PHYSICAL;
-    double li = 0.0;
-#pragma unroll
-    for (int s = 0; s < KP2; ++s) {
-        if (s < c) {
-            int j = row[s];
-            if (j < 0 || j >= A.n_all) {
-                set_status(A.ws, GD_DEV_INTERNAL);
-                j = 0;
-            }
-            const double4 sn = A.snap[j];
-            Pair o;
-            pair_eval(A.P, q, w, sn.x, phys ? sn.y : 0.0, phys ? sn.z : 0.0, sn.w, o);
-            li = li + o.lam_star;
-        }
-        pre[s] = li;
-    }
-    return li;
-}
-
-// Sampling runs in two steps.  The screen (one lane per particle, few
+// Sampling runs in two passes.  The screen (one lane per particle, few
 // registers) draws each particle's first waiting time against lambda*_i of
 // the rates pass: a particle without an event in the interval keeps its mass
-// and is done; the others go, compacted, to a list.  The event pass then
-// samples the listed particles, one lane each (up to kLaneEvents events,
-// then the wavefront-per-particle pass), from a grid that strides over the
-// list, so lanes without events never hold a wavefront's registers.  Its
-// lanes redraw the first event's numbers (the same counters, so the same
-// numbers).  For neighbourhoods beyond 64 (no prefix registers) the screen
-// hands its particles straight to the wavefront-per-particle pass.
-// The list has a segment per die: the blocks dealt to die x (block b with
-// b % 8 == x, 256 particles each) fill segment x, which starts after the
-// blocks of the dies before it, so that the count adds of one die go to its
-// own counter.  One add per block.
-__device__ inline int64_t seg_base(int x, int64_t nblocks)
-{
-    return ((nblocks / kXcd) * x + (x < nblocks % kXcd ? x : nblocks % kXcd)) * 256;
-}
-
-template <bool DIRECT_HEAVY>
+// and is done; the others go, compacted, to a list, those that expect many
+// events to its far end.  The sampling pass then runs the whole interval of
+// each listed particle in half a wavefront (k <= 32) or a whole one, the long
+// ones first, and redraws the first event's numbers (the same counters, so
+// the same numbers).  One atomic per workgroup and list end.
 struct McScreen {
     using Args = McArgs;
     static constexpr int kThreads = 256;
-    static __device__ __forceinline__ void body(const Args& A, Blk B);
+    static __device__ __forceinline__ void body(const Args& A, Blk B)
+    {
+        __shared__ int32_t s_w[2][4], s_base[2];
+        const int64_t i = B.id * int64_t(blockDim.x) + threadIdx.x;
+        const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+        bool ev = false, early = false;
+        if (i < A.P.n) {
+            const int c = A.cnt[i];
+            const double m = A.m[i];
+            const double li = A.lam_i[i];
+            if (c > 1 && li > 0.0) {
+                const uint32_t interval = mc_interval(A);
+                double u[4];
+                event_uniforms(A.seed, A.id[i], interval, 0u, u);
+                ev = !(-log(u[0]) / li > A.iv->dt_exe);
+                early = ev && A.early_events > 0.0 && li * A.iv->dt_exe >= A.early_events;
+            }
+            if (!ev) {
+                A.m_out[i] = m;
+                if (A.n_events) A.n_events[i] = 0;
+            }
+            if (A.log)
+                for (int f = 0; f < A.log_cap; ++f) A.log[i * A.log_cap + f] = -1;
+        }
+        const uint64_t bl = __ballot(ev && !early), be = __ballot(early);
+        if (lane == 0) {
+            s_w[0][wv] = int32_t(__popcll(bl));
+            s_w[1][wv] = int32_t(__popcll(be));
+        }
+        __syncthreads();
+        if (threadIdx.x < 2) {
+            const int32_t* w = s_w[threadIdx.x];
+            const int32_t tot = w[0] + w[1] + w[2] + w[3];
+            s_base[threadIdx.x] = tot ? atomicAdd(threadIdx.x == 0 ? A.list_n : A.early_n, tot) : 0;
+        }
+        __syncthreads();
+        if (!ev) return;
+        const int e = early ? 1 : 0;
+        int32_t at = s_base[e] + int32_t(__popcll((early ? be : bl) & ((uint64_t(1) << lane) - 1)));
+        for (int w = 0; w < wv; ++w) at += s_w[e][w];
+        A.list[early ? A.P.n - 1 - at : at] = int32_t(i);
+    }
 };
 
-template <bool DIRECT_HEAVY>
 __global__ __launch_bounds__(256) void k_mc_screen(McArgs A)
 {
-    McScreen<DIRECT_HEAVY>::body(A, Blk{int64_t(blockIdx.x), int64_t(gridDim.x)});
-}
-
-template <bool DIRECT_HEAVY>
-__device__ __forceinline__ void McScreen<DIRECT_HEAVY>::body(const Args& A, Blk B)
-{
-    __shared__ int32_t s_w[4];
-    __shared__ int32_t s_base;
-    const int64_t i = B.id * int64_t(blockDim.x) + threadIdx.x;
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    bool ev = false, early = false;
-    if (i < A.P.n) {
-        const int c = A.cnt[i];
-        const double m = A.m[i];
-        const double li = A.lam_i[i];
-        if (c > 1 && li > 0.0) {
-            const uint32_t interval = mc_interval(A);
-            double u[4];
-            event_uniforms(A.seed, A.id[i], interval, 0u, u);
-            ev = !(-log(u[0]) / li > A.iv->dt_exe);
-            // many expected events: the whole interval in the wavefront pass
-            // (the result is the same whichever pass samples a particle)
-            early = !DIRECT_HEAVY && ev && A.early_events > 0.0 && li * A.iv->dt_exe >= A.early_events;
-        }
-        if (!ev) {
-            A.m_out[i] = m;
-            if (A.n_events) A.n_events[i] = 0;
-            if (A.log)
-                for (int f = 0; f < A.log_cap; ++f) A.log[i * A.log_cap + f] = -1;
-        } else if ((DIRECT_HEAVY || early) && A.log) {
-            for (int f = 0; f < A.log_cap; ++f) A.log[i * A.log_cap + f] = -1;
-        }
-    }
-    if (!DIRECT_HEAVY) {  // the early ones, one add per wavefront that has any
-        const uint64_t eb = __ballot(early);
-        int32_t base = 0;
-        if (lane == 0 && eb) base = atomicAdd(A.heavy_n0, int32_t(__popcll(eb)));
-        base = __builtin_amdgcn_readfirstlane(base);
-        if (early)
-            A.heavy[A.P.n - 1 - (base + int32_t(__popcll(eb & ((uint64_t(1) << lane) - 1))))] =
-                Deferred{int32_t(i), 0, 0.0, A.m[i]};
-        ev = ev && !early;
-    }
-    const uint64_t bal = __ballot(ev);
-    if (lane == 0) s_w[wv] = int32_t(__popcll(bal));
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        const int32_t tot = s_w[0] + s_w[1] + s_w[2] + s_w[3];
-        int32_t b = 0;
-        if (tot) b = atomicAdd(DIRECT_HEAVY ? A.heavy_n : &A.list_seg[B.id % kXcd], tot);
-        s_base = b;
-    }
-    __syncthreads();
-    if (ev) {
-        int32_t at = s_base + int32_t(__popcll(bal & ((uint64_t(1) << lane) - 1)));
-        for (int w = 0; w < wv; ++w) at += s_w[w];
-        if (DIRECT_HEAVY) A.heavy[at] = Deferred{int32_t(i), 0, 0.0, A.m[i]};
-        else A.list[seg_base(int(B.id % kXcd), B.n) + at] = int32_t(i);
-    }
-}
-
-template <int KP2, bool F32>
-__device__ inline int mc_particle(const McArgs& A, int64_t i)
-{
-    constexpr int KR = KP2;  // prefix registers
-    int e = 0;
-    if (i < A.P.n) {
-        const int k = A.P.k;
-        const bool phys = A.P.kernel == GD_KERNEL_PHYSICAL;
-        const int c = A.cnt[i];
-        double m = A.m[i];
-        double li = A.lam_i[i];
-        const double dt_exe = A.iv->dt_exe;
-        const uint32_t interval = mc_interval(A);
-        if (c > 1 && li > 0.0) {
-            const uint32_t pid = A.id[i];
-            const int32_t* row = A.nbr + i * k;
-            QCtx q{};
-            QCtxF qf{};
-            Own own{};
-            bool have_ctx = false, have_pre = false;
-            double si = 0.0, Sti = 0.0;
-            double pre[KR];
-            double t = 0.0;
-            for (;;) {
-                if (!(li > 0.0)) break;
-                if (e >= A.budget) {
-                    // many events: the rest of this particle's interval runs
-                    // in the wavefront-per-particle pass (li equals the prefix
-                    // of the current mass, which that pass recomputes)
-                    const int32_t slot = atomicAdd(A.heavy_n, 1);
-                    A.heavy[slot] = Deferred{int32_t(i), e, t, m};
-                    break;
-                }
-                if (e >= kEventCap) {
-                    set_status(A.ws, GD_DEV_EVENT_CAP);
-                    break;
-                }
-                double u[4];
-                event_uniforms(A.seed, pid, interval, uint32_t(e), u);
-                const double dtw = -log(u[0]) / li;
-                if (dtw > dt_exe - t) break;
-                t = t + dtw;
-                if (!have_ctx) {
-                    query_ctx(A.P, A.x[i], A.y[i], A.z[i], A.dmax[i], q);
-                    if (F32) query_ctx_f32(A.P, q, qf);
-                    have_ctx = true;
-                }
-                if (!have_pre) {
-                    if (phys) {
-                        si = grain_size(A.P, m);
-                        Sti = F32 ? double(qf.stfac * float(si)) : q.stfac * si;
-                    }
-                    if (!F32) own_terms(A.P, q, m, si, false, own);
-                    li = F32 ? prefix_rates_f32<KR>(A, qf, row, c, m, float(si), float(Sti), pre)
-                             : prefix_rates<KR>(A, q, row, c, own, pre);
-                    have_pre = true;
-                }
-                const double target = u[1] * li;
-                int sel = c - 1;
-                bool found = false;
-#pragma unroll
-                for (int s = 0; s < KR; ++s) {
-                    const bool hit = !found && s < c - 1 && pre[s] > target;
-                    sel = hit ? s : sel;
-                    found = found || hit;
-                }
-                int j = row[sel];
-                if (j < 0 || j >= A.n_all) j = 0;
-                const double4 sn = A.snap[j];
-                const double mj = sn.x;
-                const double sj = phys ? sn.y : 0.0;
-                Pair o;
-                if (F32) {
-                    PairF of;
-                    pair_eval_f32(A.P, qf, m, 1.0 / m, float(si), float(Sti), mj, float(sj), phys ? sn.z : 0.0, of);
-                    o.type = of.type;
-                    o.r0 = of.r0;
-                    o.r1 = of.r1;
-                    o.lam_star = double(of.r0) + double(of.r1);
-                    o.Ng = of.Ng;
-                } else {
-                    pair_eval(A.P, q, own, mj, sj, phys ? sn.z : 0.0, sn.w, o);
-                }
-                int ch = 0;
-                if (o.type == kErosion) ch = (o.r0 > u[2] * o.lam_star) ? 0 : 1;
-                double mnew;
-                if (o.type == kStick) {
-                    mnew = m + o.Ng * mj;
-                } else if (o.type == kErosion) {
-                    mnew = (ch == 0) ? m - o.Ng * mj : mj;
-                } else {
-                    const double a = sqrt(A.P.s_min);
-                    const double w = a + u[3] * (sqrt(si) - a);
-                    const double sn = w * w;
-                    mnew = div_nr(kPi * A.P.rho_s * sn * sn * sn, 6.0);
-                }
-                if (A.log) {
-                    if (e < A.log_cap) A.log[i * A.log_cap + e] = sel | (ch << 16) | (o.type << 24);
-                    else set_status(A.ws, GD_DEV_LOG_OVERFLOW);
-                }
-                ++e;
-                if (mnew != m) {
-                    m = mnew;
-                    have_pre = false;
-                    if (phys) {
-                        si = grain_size(A.P, m);
-                        Sti = F32 ? double(qf.stfac * float(si)) : q.stfac * si;
-                    }
-                    if (!F32) own_terms(A.P, q, m, si, false, own);
-                    li = F32 ? prefix_rates_f32<KR>(A, qf, row, c, m, float(si), float(Sti), pre)
-                             : prefix_rates<KR>(A, q, row, c, own, pre);
-                    have_pre = true;
-                }
-            }
-        }
-        A.m_out[i] = m;
-        if (A.n_events) A.n_events[i] = e;
-        if (A.log)
-            for (int f = e; f < A.log_cap; ++f) A.log[i * A.log_cap + f] = -1;
-    }
-    return e;
-}
-
-// the listed particles, one lane each: the segments are read as one list;
-// wavefront w takes entries 64 w .. 64 w + 63 first, then further groups of
-// 64 from a counter until the list is exhausted (a wavefront with no first
-// group touches no counter)
-// the event pass's arguments: the sampling's and the screen's block count
-// (the list's segments are laid out by it)
-struct EventArgs {
-    McArgs A;
-    int64_t screen_blocks;
-};
-
-template <int KP2, bool F32>
-struct McEvents {
-    using Args = EventArgs;
-    static constexpr int kThreads = 256;
-    static __device__ __forceinline__ void body(const Args& E, Blk B);
-};
-
-template <int KP2, bool F32>
-__global__ __launch_bounds__(256) void k_mc(EventArgs E)
-{
-    McEvents<KP2, F32>::body(E, Blk{int64_t(blockIdx.x), int64_t(gridDim.x)});
-}
-
-template <int KP2, bool F32>
-__device__ __forceinline__ void McEvents<KP2, F32>::body(const Args& E, Blk B)
-{
-    const McArgs& A = E.A;
-    const int64_t screen_blocks = E.screen_blocks;
-    const int lane = threadIdx.x & 63;
-    int32_t pre[kXcd + 1];
-    pre[0] = 0;
-#pragma unroll
-    for (int x = 0; x < kXcd; ++x) pre[x + 1] = pre[x] + A.list_seg[x];
-    const int32_t nl = pre[kXcd];
-    const int32_t nw = int32_t(B.n * (blockDim.x / kWave));
-    int32_t b = int32_t(B.id * (blockDim.x / kWave) + threadIdx.x / kWave) * kWave;
-    if (nl <= kSmallList) {
-        // few particles with events (a cold disk): each takes a wavefront of
-        // the wavefront-per-particle pass at once, where its pairs are
-        // evaluated side by side instead of one after another in a lane.
-        // The grid strides over the list (a small grid covers less than it).
-        for (int32_t t = b + lane; t < nl; t += nw * kWave) {
-            int x = 0;
-#pragma unroll
-            for (int y = 1; y < kXcd; ++y) x += t >= pre[y] ? 1 : 0;
-            const int32_t i = A.list[seg_base(x, screen_blocks) + (t - pre[x])];
-            if (A.log)
-                for (int f = 0; f < A.log_cap; ++f) A.log[i * A.log_cap + f] = -1;
-            A.heavy[atomicAdd(A.heavy_n, 1)] = Deferred{i, 0, 0.0, A.m[i]};
-        }
-        return;
-    }
-    unsigned long long ev = 0;
-    while (b < nl) {
-        const int32_t t = b + lane;
-        if (t < nl) {
-            int x = 0;
-#pragma unroll
-            for (int y = 1; y < kXcd; ++y) x += t >= pre[y] ? 1 : 0;
-            ev += (unsigned long long)mc_particle<KP2, F32>(A, A.list[seg_base(x, screen_blocks) + (t - pre[x])]);
-        }
-        int32_t nx = 0;
-        if (lane == 0) nx = atomicAdd(A.list_next, kWave);
-        b = nw * kWave + __builtin_amdgcn_readfirstlane(nx);
-    }    // events of the interval, one atomic per wavefront
-#pragma unroll
-    for (int mk = 1; mk < 64; mk <<= 1) ev += __shfl_xor(ev, mk, 64);
-    if (lane == 0 && ev) atomicAdd(A.ev_counter, ev);
+    McScreen::body(A, Blk{int64_t(blockIdx.x), int64_t(gridDim.x)});
 }
 
 // ---------------------------------------------------------------------------
-// The rest of the interval of each deferred particle, one wavefront per
-// particle.  Lane s < c holds neighbour slot s: the neighbour's terms that
-// the frozen snapshot fixes for the whole interval are computed once, and
-// per event the lane evaluates its pair for the particle's current mass and
-// the outcome the event would have with that partner.  The prefix over the
-// slots is a wavefront scan; the selection (first slot whose prefix exceeds
-// the target) is a ballot, and the chosen lane's outcome is read across.
-// The draws do not depend on the mass: lane L draws the numbers of event
-// e0 + L, 64 events at a time, and each event reads its own from that lane.
-// Wavefronts take particles from a counter until the list is exhausted.
+// The interval of the listed particles.  A particle takes a group of W lanes
+// (W = 32, two particles per wavefront, for k <= 32; else the wavefront).
+// Lane s < c of the group holds neighbour slot s (and s + 64, ... beyond 64):
+// the neighbour's terms that the frozen snapshot fixes for the whole interval
+// are computed once, and per event the lane evaluates its pair for the
+// particle's current mass and the outcome the event would have with that
+// partner.  The prefix over the slots is a scan over the group; the selection
+// (first slot whose prefix exceeds the target) is a ballot, and the chosen
+// lane's outcome is read across.  The draws do not depend on the mass: lane L
+// of the group draws the numbers of event e0 + L, W events at a time, and
+// each event reads its own from that lane.  A group whose particle is done
+// takes the next of the wavefront's chunk while the other goes on.  The
+// pass is bound by the instructions of the pairs: on the warm 1M disk a lane
+// per particle for its first events and then a whole wavefront for the rest
+// took 2.72 ms an interval, half a wavefront for all of them 1.7 ms, and the
+// interval went from 4.39 to 3.31 ms.  128 registers (4 wavefronts per SIMD,
+// a few spilled) against 167: 3.70 against 3.83 ms at that step.
 
-// the numbers of events e0 .. e0 + 63 (lane L: event e0 + L): -ln U_w, U_p, U_c, U_f
+// the numbers of events e0 .. e0 + W - 1 (lane L: event e0 + L): -ln U_w, U_p, U_c, U_f
 struct Draws {
     double lw, up, uc, uf;
 };
 
-__device__ inline void draw64(const McArgs& A, uint32_t pid, uint32_t interval, uint32_t e0, int lane, Draws& d)
+__device__ inline void draw_events(const McArgs& A, uint32_t pid, uint32_t interval, uint32_t e0, int s, Draws& d)
 {
     double u[4];
-    event_uniforms(A.seed, pid, interval, e0 + uint32_t(lane), u);
+    event_uniforms(A.seed, pid, interval, e0 + uint32_t(s), u);
     d.lw = -log(u[0]);
     d.up = u[1];
     d.uc = u[2];
     d.uf = u[3];
 }
 
-// the rest of deferred particle `hidx` of the run described by A; returns the
-// events it adds.  Lane s holds the pairs of slots s, s + 64, ... (R of
-// them for neighbourhoods beyond 64).
+// x of lane l0 in the first group, of lane W + l1 in the second (l0, l1
+// uniform)
+template <int G>
+__device__ inline double group_read(double x, int l0, int l1, bool second)
+{
+    const double a = readlane_d(x, l0);
+    if (G == 1) return a;
+    const double b = readlane_d(x, 32 + l1);
+    return second ? b : a;
+}
+
+// inclusive prefix sum over each group of 64 / G lanes
+template <int G>
+__device__ inline double group_scan(double x)
+{
+    x = x + dpp_take<0x111, 0xf>(x);  // row_shr:1
+    x = x + dpp_take<0x112, 0xf>(x);  // row_shr:2
+    x = x + dpp_take<0x114, 0xf>(x);  // row_shr:4
+    x = x + dpp_take<0x118, 0xf>(x);  // row_shr:8
+    x = x + dpp_take<0x142, 0xa>(x);  // row_bcast:15 into rows 1 and 3
+    if (G == 1) x = x + dpp_take<0x143, 0xc>(x);  // row_bcast:31 into rows 2 and 3
+    return x;
+}
+
+// the particles of chunk [lo, hi) of the run described by A, entry e of it
+// list[n - 1 - e] (`far`) or list[e]; returns their events
 template <int KP2, bool F32>
-__device__ inline int run_deferred(const McArgs& A, int32_t hidx, int lane)
+__device__ inline int run_chunk(const McArgs& A, int32_t lo, int32_t hi, bool far, int lane)
 {
     constexpr int R = KP2 > kWave ? KP2 / kWave : 1;
-    constexpr int W = KP2 < kWave ? KP2 : kWave;  // lanes holding slots
+    constexpr int G = KP2 <= 32 ? 2 : 1;  // particles side by side
+    constexpr int W = kWave / G;
     const bool phys = A.P.kernel == GD_KERNEL_PHYSICAL;
     const double dt_exe = A.iv->dt_exe;
     const uint32_t interval = mc_interval(A);
-    const Deferred H = A.heavy[hidx];
-    const int64_t i = H.i;
-    int e = H.e;
-    double t = H.t, m = H.m;
     const int k = A.P.k;
-    const int c = A.cnt[i];
-    const uint32_t pid = A.id[i];
+    const bool second = G == 2 && lane >= W;
+    const int sl = lane & (W - 1);
+    // uniform per group: live, events done, first event of the draws
+    bool live[2] = {false, false};
+    int e[2] = {0, 0}, e0[2] = {0, 0}, cg[2] = {0, 0};
+    int total = 0;
+    // the lanes' own: the group's particle
+    int64_t i = 0;
+    uint32_t pid = 0;
+    int c = 0;
+    double t = 0.0, m = 1.0;
     QCtx q{};
     QCtxF qf{};
-    query_ctx(A.P, A.x[i], A.y[i], A.z[i], A.dmax[i], q);
-    if (F32) query_ctx_f32(A.P, q, qf);
     Nb nb[R];
+    Draws d{};
 #pragma unroll
-    for (int r = 0; r < R; ++r) {
-        const int s = r * kWave + lane;
-        const bool mine = s < c && lane < W;
-        int j = mine ? A.nbr[i * k + s] : 0;
-        if (mine && (j < 0 || j >= A.n_all)) set_status(A.ws, GD_DEV_INTERNAL);
-        if (j < 0 || j >= A.n_all) j = 0;
-        const double4 sn = A.snap[j];
-        if (F32) {
-            nb[r].mj = sn.x;
-            nb[r].sj = phys ? sn.y : 0.0;
-            nb[r].Nj = phys ? sn.z : 0.0;
-        } else {
-            nb_terms<true>(A.P, q, sn.x, phys ? sn.y : 0.0, phys ? sn.z : 0.0, sn.w, nb[r]);
-        }
-    }
-    uint32_t e0 = uint32_t(e);
-    Draws d;
-    draw64(A, pid, interval, e0, lane, d);
+    for (int r = 0; r < R; ++r) nb[r] = Nb{1.0, 0.0, 0.0, 1.0, 0.0, 1.0, 1.0, 1.0};
     for (;;) {
-        if (uint32_t(e) - e0 >= uint32_t(kWave)) {
-            e0 = uint32_t(e);
-            draw64(A, pid, interval, e0, lane, d);
+        bool start[2] = {false, false};
+        int32_t ent[2] = {0, 0};
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+            if (!live[g] && lo < hi) {
+                ent[g] = lo++;
+                start[g] = true;
+                live[g] = true;
+                e[g] = 0;
+                e0[g] = 0;
+            }
         }
-        const int L = int(uint32_t(e) - e0);
-        const double lw = readlane_d(d.lw, L), up = readlane_d(d.up, L), uc = readlane_d(d.uc, L);
+        if (!live[0] && !live[1]) break;
+        if (start[0] || start[1]) {
+            if (second ? start[1] : start[0]) {
+                const int32_t en = second ? ent[1] : ent[0];
+                i = A.list[far ? A.P.n - 1 - en : en];
+                c = A.cnt[i];
+                pid = A.id[i];
+                m = A.m[i];
+                t = 0.0;
+                query_ctx(A.P, A.x[i], A.y[i], A.z[i], A.dmax[i], q);
+                if (F32) query_ctx_f32(A.P, q, qf);
+#pragma unroll
+                for (int r = 0; r < R; ++r) {
+                    const int s = r * kWave + sl;
+                    int j = s < c ? A.nbr[i * k + s] : 0;
+                    if (s < c && (j < 0 || j >= A.n_all)) set_status(A.ws, GD_DEV_INTERNAL);
+                    if (j < 0 || j >= A.n_all) j = 0;
+                    const double4 sn = A.snap[j];
+                    if (F32) {
+                        nb[r].mj = sn.x;
+                        nb[r].sj = phys ? sn.y : 0.0;
+                        nb[r].Nj = phys ? sn.z : 0.0;
+                    } else {
+                        nb_terms<true>(A.P, q, sn.x, phys ? sn.y : 0.0, phys ? sn.z : 0.0, sn.w, nb[r]);
+                    }
+                }
+                draw_events(A, pid, interval, 0u, sl, d);
+            }
+            cg[0] = __builtin_amdgcn_readlane(c, 0);
+            if (G == 2) cg[1] = __builtin_amdgcn_readlane(c, W);
+        }
+        bool redraw[2] = {false, false};
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+            if (live[g] && e[g] - e0[g] >= W) {
+                e0[g] = e[g];
+                redraw[g] = true;
+            }
+        }
+        if (redraw[0] || redraw[1])
+            if (second ? redraw[1] : redraw[0]) draw_events(A, pid, interval, uint32_t(second ? e0[1] : e0[0]), sl, d);
+        const int L0 = e[0] - e0[0], L1 = (e[1] - e0[1]) & (W - 1);
+        const double lw = group_read<G>(d.lw, L0 & (W - 1), L1, second), up = group_read<G>(d.up, L0 & (W - 1), L1, second),
+                     uc = group_read<G>(d.uc, L0 & (W - 1), L1, second);
         // the pairs at the current mass, each with its outcome (a fragmentation
         // outcome does not depend on the partner and is made after the selection)
         double si = 0.0;
@@ -517,7 +298,7 @@ __device__ inline int run_deferred(const McArgs& A, int32_t hidx, int lane)
                 pre[r] = double(of.lam_star);         // the prefix adds the float rate
             } else {
                 Pair o;
-                pair_core<true>(A.P, q, w, nb[r], o);
+                pair_core<true, true>(A.P, q, w, nb[r], o);
                 type = o.type;
                 r0 = o.r0;
                 lam = o.lam_star;
@@ -528,104 +309,126 @@ __device__ inline int run_deferred(const McArgs& A, int32_t hidx, int lane)
             const double mj = nb[r].mj;
             mnew[r] = type == kStick ? m + Ng * mj : (ch == 0 ? m - Ng * mj : mj);
             code[r] = (ch << 16) | (type << 24);
-            const double x = wave_scan_incl((r * kWave + lane < c && lane < W) ? pre[r] : 0.0);
+            const double x = group_scan<G>(r * kWave + sl < c ? pre[r] : 0.0);
             pre[r] = carry + x;
-            carry = carry + readlane_d(x, kWave - 1);
+            carry = carry + group_read<G>(x, W - 1, W - 1, second);
         }
         const double li = carry;
-        if (!(li > 0.0)) break;
-        if (e >= kEventCap) {
-            if (lane == 0) set_status(A.ws, GD_DEV_EVENT_CAP);
-            break;
-        }
         const double dtw = lw / li;
-        if (dtw > dt_exe - t) break;
-        t = t + dtw;
+        const bool cap = (second ? e[1] : e[0]) >= kEventCap;
+        const bool go = li > 0.0 && !cap && !(dtw > dt_exe - t);
         const double target = up * li;
+        const uint64_t gob = __ballot(go);
+        bool on[2];
+        on[0] = live[0] && (gob & 1u);
+        on[1] = G == 2 && live[1] && ((gob >> (kWave / 2)) & 1u);
         // the first slot below c - 1 whose prefix exceeds the target, else c - 1
-        int sel = c - 1;
+        int sel[2] = {cg[0] - 1, cg[1] - 1};
 #pragma unroll
         for (int r = R - 1; r >= 0; --r) {
-            const uint64_t hit = __ballot(r * kWave + lane < c - 1 && pre[r] > target);
-            if (hit) sel = r * kWave + int(__ffsll((unsigned long long)hit)) - 1;
+            const uint64_t hit = __ballot(r * kWave + sl < c - 1 && pre[r] > target);
+            if (G == 1) {
+                if (hit) sel[0] = r * kWave + int(__ffsll((unsigned long long)hit)) - 1;
+            } else {
+                if (uint32_t(hit)) sel[0] = int(__ffs(uint32_t(hit))) - 1;
+                if (uint32_t(hit >> 32)) sel[1] = int(__ffs(uint32_t(hit >> 32))) - 1;
+            }
         }
-        const int sl = sel & (kWave - 1), sr = sel / kWave;
         int cd = 0;
         double mn = 0.0;
+        if (G == 2) {
+            const int l0 = sel[0] & (W - 1), l1 = sel[1] & (W - 1);
+            const int cd0 = __builtin_amdgcn_readlane(code[0], l0), cd1 = __builtin_amdgcn_readlane(code[0], W + l1);
+            cd = second ? cd1 : cd0;
+            mn = group_read<G>(mnew[0], l0, l1, second);
+        } else {
+            const int l0 = sel[0] & (kWave - 1), sr = sel[0] / kWave;
 #pragma unroll
-        for (int r = 0; r < R; ++r) {
-            if (r == sr) {  // uniform: sel is the same in every lane
-                cd = __builtin_amdgcn_readlane(code[r], sl);
-                mn = readlane_d(mnew[r], sl);
+            for (int r = 0; r < R; ++r) {
+                if (r == sr) {  // uniform: sel is the same in every lane
+                    cd = __builtin_amdgcn_readlane(code[r], l0);
+                    mn = readlane_d(mnew[r], l0);
+                }
             }
         }
         if ((cd >> 24) == kFrag) {
-            const double uf = readlane_d(d.uf, L);
+            const double uf = group_read<G>(d.uf, L0 & (W - 1), L1, second);
             const double a = sqrt(A.P.s_min);
             const double wf = a + uf * (sqrt(si) - a);
             const double sz = wf * wf;
             mn = div_nr(kPi * A.P.rho_s * sz * sz * sz, 6.0);
         }
-        if (A.log && lane == 0) {
-            if (e < A.log_cap) A.log[i * A.log_cap + e] = sel | cd;
+        const bool lon = second ? on[1] : on[0];
+        const int le = second ? e[1] : e[0];
+        if (A.log && lon && sl == 0) {
+            if (le < A.log_cap) A.log[i * A.log_cap + le] = (second ? sel[1] : sel[0]) | cd;
             else set_status(A.ws, GD_DEV_LOG_OVERFLOW);
         }
-        ++e;
+        const bool end = (second ? live[1] : live[0]) && !lon;
+        if (end && sl == 0) {
+            if (li > 0.0 && cap) set_status(A.ws, GD_DEV_EVENT_CAP);
+            A.m_out[i] = m;
+            if (A.n_events) A.n_events[i] = le;
+        }
         // (an unchanged mass recomputes the same rates: no branch around them)
-        m = mn;
+        t = lon ? t + dtw : t;
+        m = lon ? mn : m;
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+            e[g] += on[g] ? 1 : 0;
+            total += on[g] ? 1 : 0;
+            live[g] = on[g];
+        }
     }
-    if (lane == 0) {
-        A.m_out[i] = m;
-        if (A.n_events) A.n_events[i] = e;
-    }
-    return e - H.e;
+    return total;
 }
 
+// Chunks of a run's list: first its far end (two particles a chunk: the long
+// ones start at once, spread over the wavefronts), then the rest, up to
+// kChunk a chunk while that leaves every wavefront several.
+struct Chunks {
+    int32_t n0, n1, c, k0, k;  // particles of each part, chunk size, chunks of the first part, all
+
+    __device__ void set(int32_t early, int32_t rest, int32_t waves)
+    {
+        n0 = early;
+        n1 = rest;
+        c = rest / (4 * waves);
+        c = c < 2 ? 2 : (c > kChunk ? kChunk : c);
+        k0 = (n0 + 1) / 2;
+        k = k0 + (n1 + c - 1) / c;
+    }
+    template <int KP2, bool F32>
+    __device__ int run(const McArgs& A, int32_t x, int lane) const
+    {
+        const bool far = x < k0;
+        const int32_t lo = far ? 2 * x : (x - k0) * c, hi = far ? lo + 2 : lo + c, n = far ? n0 : n1;
+        // the long ones set the pass's length: their wavefronts issue first
+        // (3.66 against 3.70 ms per interval of the warm 1M disk)
+        if (far) __builtin_amdgcn_s_setprio(3);
+        const int ev = run_chunk<KP2, F32>(A, lo, hi < n ? hi : n, far, lane);
+        if (far) __builtin_amdgcn_s_setprio(0);
+        return ev;
+    }
+};
+
 template <int KP2, bool F32>
-__global__ __launch_bounds__(256) void k_mc_heavy(McArgs A)
+__global__ __launch_bounds__(256, KP2 <= 32 ? 4 : 1) void k_mc(McArgs A)
 {
     const int lane = threadIdx.x & 63;
-    const int32_t nh = *A.heavy_n;
-    unsigned long long ev_total = 0;
-    // wavefront w takes entry w first, then entries nw, nw + 1, ... from the
-    // counter (a wavefront with no first entry touches no counter)
     const int32_t nw = int32_t(gridDim.x * (blockDim.x / kWave));
-    int32_t hidx = int32_t(blockIdx.x * (blockDim.x / kWave) + threadIdx.x / kWave);
-    for (;;) {
-        if (hidx >= nh) break;
-        ev_total += (unsigned long long)run_deferred<KP2, F32>(A, hidx, lane);
-        int32_t next = 0;
-        if (lane == 0) next = atomicAdd(A.heavy_next, 1);
-        hidx = nw + __builtin_amdgcn_readfirstlane(next);
-    }
-    if (lane == 0 && ev_total) atomicAdd(A.ev_counter, ev_total);
-}
-
-// The chains the screen sent early and the event pass, in one launch: the
-// first kEarlyBlocks blocks (dispatched first) run the early chains (entries
-// n - 1 - h of `heavy` for h < *heavy_n0; their wavefronts without one leave
-// at once), the rest the event pass, so that the long chains run beside the
-// event pass instead of after it.  The chains the event pass defers follow
-// in k_mc_heavy.
-template <int KP2, bool F32>
-__global__ __launch_bounds__(256) void k_mc_fused(EventArgs E)
-{
-    if (blockIdx.x >= unsigned(kEarlyBlocks)) {
-        McEvents<KP2, F32>::body(E, Blk{int64_t(blockIdx.x - unsigned(kEarlyBlocks)), int64_t(kEventBlocks)});
-        return;
-    }
-    const McArgs& A = E.A;
-    const int lane = threadIdx.x & 63;
-    const int32_t nh = *A.heavy_n0;
+    Chunks C;
+    C.set(*A.early_n, *A.list_n, nw);
     unsigned long long ev_total = 0;
-    const int32_t nw = int32_t(kEarlyBlocks * (blockDim.x / kWave));
-    int32_t h = int32_t(blockIdx.x * (blockDim.x / kWave) + threadIdx.x / kWave);
+    // wavefront w takes chunk w first, then chunks nw, nw + 1, ... from the
+    // counter (a wavefront with no first chunk touches no counter)
+    int32_t x = __builtin_amdgcn_readfirstlane(int32_t(blockIdx.x * (blockDim.x / kWave) + threadIdx.x / kWave));
     for (;;) {
-        if (h >= nh) break;
-        ev_total += (unsigned long long)run_deferred<KP2, F32>(A, int32_t(A.P.n - 1 - h), lane);
+        if (x >= C.k) break;
+        ev_total += (unsigned long long)C.run<KP2, F32>(A, x, lane);
         int32_t next = 0;
-        if (lane == 0) next = atomicAdd(A.heavy_next0, 1);
-        h = nw + __builtin_amdgcn_readfirstlane(next);
+        if (lane == 0) next = atomicAdd(A.next, 1);
+        x = nw + __builtin_amdgcn_readfirstlane(next);
     }
     if (lane == 0 && ev_total) atomicAdd(A.ev_counter, ev_total);
 }
@@ -633,9 +436,9 @@ __global__ __launch_bounds__(256) void k_mc_fused(EventArgs E)
 // ---------------------------------------------------------------------------
 // Many runs: a table in device memory holds, per slot, the sampling arguments
 // of one run (written by its deferred call), after a 256-byte header whose
-// first word counts the entries taken.  One launch runs the deferred
-// particles of every slot: the global entry g is the slot's own entry
-// g - (deferred particles of the slots before it).
+// first word counts the chunks taken.  One launch runs the lists of every
+// slot: the global chunk g is the slot's own chunk g - (chunks of the slots
+// before it).
 constexpr size_t kTableHeader = 256;
 constexpr int kMaxTableSlots = 4096;
 
@@ -645,14 +448,21 @@ __global__ void k_table_put(McArgs* dst, McArgs A)
 }
 
 template <int KP2, bool F32>
-__global__ __launch_bounds__(256) void k_mc_heavy_batch(char* table, int32_t nbox)
+__global__ __launch_bounds__(256) void k_mc_batch(char* table, int32_t nbox)
 {
     __shared__ int32_t s_pre[kMaxTableSlots];
     __shared__ int32_t s_total;
     const McArgs* T = reinterpret_cast<const McArgs*>(table + kTableHeader);
     int32_t* counter = reinterpret_cast<int32_t*>(table);
     const int t = threadIdx.x, lane = t & 63;
-    for (int b = t; b < nbox; b += blockDim.x) s_pre[b] = (T[b].active && !*T[b].active) ? 0 : *T[b].heavy_n;
+    const int32_t nw = int32_t(gridDim.x * (blockDim.x / kWave));
+    auto chunks = [&](int b) {
+        Chunks C;
+        if (T[b].active && !*T[b].active) C.set(0, 0, nw);
+        else C.set(*T[b].early_n, *T[b].list_n, nw);
+        return C;
+    };
+    for (int b = t; b < nbox; b += blockDim.x) s_pre[b] = chunks(b).k;
     __syncthreads();
     if (t < kWave) {  // exclusive prefix of the slots' counts, 64 at a time
         int32_t carry = 0;
@@ -671,8 +481,7 @@ __global__ __launch_bounds__(256) void k_mc_heavy_batch(char* table, int32_t nbo
     }
     __syncthreads();
     const int32_t total = s_total;
-    const int32_t nw = int32_t(gridDim.x * (blockDim.x / kWave));
-    int32_t g = int32_t(blockIdx.x * (blockDim.x / kWave) + t / kWave);
+    int32_t g = __builtin_amdgcn_readfirstlane(int32_t(blockIdx.x * (blockDim.x / kWave) + t / kWave));
     for (;;) {
         if (g >= total) break;
         // the last slot whose prefix is <= g (slots with no entries share a prefix)
@@ -682,11 +491,12 @@ __global__ __launch_bounds__(256) void k_mc_heavy_batch(char* table, int32_t nbo
             if (s_pre[mid] <= g) lo = mid;
             else hi = mid - 1;
         }
+        lo = __builtin_amdgcn_readfirstlane(lo);
         const McArgs& A = T[lo];
         if (A.P.k > KP2 || (A.P.rates_fp32 != 0) != F32) {
             if (lane == 0) set_status(A.ws, GD_DEV_INTERNAL);
         } else {
-            const int ev = run_deferred<KP2, F32>(A, g - s_pre[lo], lane);
+            const int ev = chunks(lo).template run<KP2, F32>(A, g - s_pre[lo], lane);
             if (lane == 0 && ev) atomicAdd(A.ev_counter, (unsigned long long)ev);
         }
         int32_t next = 0;
@@ -745,77 +555,34 @@ static McArgs mc_args(const gd_problem* p, const gd_particles* s, const gd_neigh
     A.interval_on_device = interval_on_device ? 1 : 0;
     A.ws = ws;
     A.ev_counter = reinterpret_cast<unsigned long long*>(&h->scratch[0]);
-    A.budget = kLaneEvents;
-    A.heavy = at<Deferred>(ws, L.heavy);
-    A.heavy_n = &h->heavy_n;
-    A.heavy_next = &h->heavy_next;
-    A.heavy_n0 = &h->heavy_n0;
-    A.heavy_next0 = &h->heavy_next0;
-    A.n_all = p->n;
     A.list = at<int32_t>(ws, L.mclist);
-    A.list_seg = h->mc_seg;
-    A.list_next = &h->mc_next;
+    A.list_n = &h->mc_n;
+    A.early_n = &h->mc_early_n;
+    A.next = &h->mc_next;
+    A.early_events = kEarlyEvents;
+    A.n_all = p->n;
     return A;
 }
 
-// the screen; false when it hands every particle with an event straight to
-// the wavefront-per-particle pass (no event pass follows)
-static bool launch_screen(const McArgs& A, const gd_problem* p, hipStream_t st)
+static void launch_screen(const McArgs& A, hipStream_t st)
 {
-    const int g = int((A.P.n + 255) / 256);
-    if (p->k > 64) {  // no prefix registers: straight to the wavefront-per-particle pass
-        hipLaunchKernelGGL(k_mc_screen<true>, dim3(g), dim3(256), 0, st, A);
-        return false;
-    }
-    hipLaunchKernelGGL(k_mc_screen<false>, dim3(g), dim3(256), 0, st, A);
-    return true;
-}
-
-static void launch_events(const McArgs& A, const gd_problem* p, hipStream_t st)
-{
-    const int g = int((A.P.n + 255) / 256);
-    const dim3 eg(kEventBlocks), eb(256);
-    if (A.early_events > 0.0) {  // with the early chains beside it
-        const dim3 fg(kEarlyBlocks + kEventBlocks);
-        const EventArgs E{A, int64_t(g)};
-        if (p->rates_fp32) {
-            if (p->k <= 32) hipLaunchKernelGGL((k_mc_fused<32, true>), fg, eb, 0, st, E);
-            else hipLaunchKernelGGL((k_mc_fused<64, true>), fg, eb, 0, st, E);
-        } else {
-            if (p->k <= 32) hipLaunchKernelGGL((k_mc_fused<32, false>), fg, eb, 0, st, E);
-            else hipLaunchKernelGGL((k_mc_fused<64, false>), fg, eb, 0, st, E);
-        }
-        return;
-    }
-    const EventArgs E{A, int64_t(g)};
-    if (p->rates_fp32) {
-        if (p->k <= 32) hipLaunchKernelGGL((k_mc<32, true>), eg, eb, 0, st, E);
-        else hipLaunchKernelGGL((k_mc<64, true>), eg, eb, 0, st, E);
-    } else {
-        if (p->k <= 32) hipLaunchKernelGGL((k_mc<32, false>), eg, eb, 0, st, E);
-        else hipLaunchKernelGGL((k_mc<64, false>), eg, eb, 0, st, E);
-    }
-}
-
-static void launch_first(const McArgs& A, const gd_problem* p, hipStream_t st)
-{
-    if (launch_screen(A, p, st)) launch_events(A, p, st);
+    hipLaunchKernelGGL(k_mc_screen, dim3(unsigned((A.P.n + 255) / 256)), dim3(256), 0, st, A);
 }
 
 template <bool F32>
-static void launch_heavy(const McArgs& A, int k, hipStream_t st)
+static void launch_listed(const McArgs& A, int k, hipStream_t st)
 {
-    const dim3 g(kHeavyBlocks), b(256);
-    if (k <= 32) hipLaunchKernelGGL((k_mc_heavy<32, F32>), g, b, 0, st, A);
-    else if (k <= 64) hipLaunchKernelGGL((k_mc_heavy<64, F32>), g, b, 0, st, A);
-    else if (k <= 128) hipLaunchKernelGGL((k_mc_heavy<128, F32>), g, b, 0, st, A);
-    else hipLaunchKernelGGL((k_mc_heavy<256, F32>), g, b, 0, st, A);
+    const dim3 g(kSampleBlocks), b(256);
+    if (k <= 32) hipLaunchKernelGGL((k_mc<32, F32>), g, b, 0, st, A);
+    else if (k <= 64) hipLaunchKernelGGL((k_mc<64, F32>), g, b, 0, st, A);
+    else if (k <= 128) hipLaunchKernelGGL((k_mc<128, F32>), g, b, 0, st, A);
+    else hipLaunchKernelGGL((k_mc<256, F32>), g, b, 0, st, A);
 }
 
-static void launch_deferred(const McArgs& A, const gd_problem* p, hipStream_t st)
+static void launch_listed(const McArgs& A, const gd_problem* p, hipStream_t st)
 {
-    if (p->rates_fp32) launch_heavy<true>(A, p->k, st);
-    else launch_heavy<false>(A, p->k, st);
+    if (p->rates_fp32) launch_listed<true>(A, p->k, st);
+    else launch_listed<false>(A, p->k, st);
 }
 
 int launch_sample(const gd_problem* p, const gd_particles* s, const gd_neighbors* nb, gd_interval* iv,
@@ -823,22 +590,19 @@ int launch_sample(const gd_problem* p, const gd_particles* s, const gd_neighbors
                   int32_t log_cap, void* ws, const Layout& L, hipStream_t st, void* table, int32_t slot)
 {
     McArgs A = mc_args(p, s, nb, iv, lam_i, seed, interval, interval_on_device, n_events, log, log_cap, ws, L);
-    // (with a table the deferred particles wait for the launch over every
-    // slot, so no chain starts early)
-    if (!table) A.early_events = kEarlyEvents;
     prof_mark(GD_PROF_MC, 0, st);
-    // (the list's segment counts are cleared by the plan and by every audit;
-    // a run of the table form may sample again before its audit)
-    if (table) launch_fill_i32(A.list_seg, kXcd + 1, 0, st);
-    if (p->n > 0) launch_first(A, p, st);
+    // (the list's counts are cleared by the plan and by every audit; a run of
+    // the table form may sample again before its audit)
+    if (table) launch_fill_i32(A.list_n, 3, 0, st);
+    if (p->n > 0) launch_screen(A, st);
     if (table) {
-        // deferred particles are left to the launch over the whole table
+        // the list is left to the launch over the whole table
         McArgs* dst = reinterpret_cast<McArgs*>(static_cast<char*>(table) + kTableHeader) + slot;
         hipLaunchKernelGGL(k_table_put, dim3(1), dim3(64), 0, st, dst, A);
         prof_mark(GD_PROF_MC, 1, st);
         return 0;
     }
-    launch_deferred(A, p, st);
+    launch_listed(A, p, st);
     prof_mark(GD_PROF_MC, 1, st);
     launch_audit(p, s->m[s->cur], s->M, s->m[s->cur ^ 1], p->n, iv, ws, L, st);
     return 0;
@@ -865,8 +629,8 @@ int launch_sample_group(const gd_problem* p, const gd_particles* s, const gd_nei
     A.m_out = s->m[s->cur ^ 1] + lo;
     A.n_events = n_events ? n_events + lo : nullptr;
     prof_mark(GD_PROF_MC, 0, st);
-    if (cnt > 0) launch_first(A, p, st);
-    launch_deferred(A, p, st);
+    if (cnt > 0) launch_screen(A, st);
+    launch_listed(A, p, st);
     prof_mark(GD_PROF_MC, 1, st);
     launch_audit(p, s->m[s->cur] + lo, s->M + lo, s->m[s->cur ^ 1] + lo, cnt, iv, ws, L, st);
     return 0;
@@ -883,24 +647,25 @@ int launch_sample_table(void* table, int32_t nslot, int32_t k, int32_t rates_fp3
 {
     launch_fill_i32(static_cast<int32_t*>(table), 1, 0, st);
     char* tb = static_cast<char*>(table);
-    const dim3 g(nblocks > 0 ? nblocks : kHeavyBlocks), b(256);
+    const dim3 g(nblocks > 0 ? nblocks : kSampleBlocks), b(256);
     if (rates_fp32) {
-        if (k <= 32) hipLaunchKernelGGL((k_mc_heavy_batch<32, true>), g, b, 0, st, tb, nslot);
-        else if (k <= 64) hipLaunchKernelGGL((k_mc_heavy_batch<64, true>), g, b, 0, st, tb, nslot);
-        else if (k <= 128) hipLaunchKernelGGL((k_mc_heavy_batch<128, true>), g, b, 0, st, tb, nslot);
-        else hipLaunchKernelGGL((k_mc_heavy_batch<256, true>), g, b, 0, st, tb, nslot);
+        if (k <= 32) hipLaunchKernelGGL((k_mc_batch<32, true>), g, b, 0, st, tb, nslot);
+        else if (k <= 64) hipLaunchKernelGGL((k_mc_batch<64, true>), g, b, 0, st, tb, nslot);
+        else if (k <= 128) hipLaunchKernelGGL((k_mc_batch<128, true>), g, b, 0, st, tb, nslot);
+        else hipLaunchKernelGGL((k_mc_batch<256, true>), g, b, 0, st, tb, nslot);
     } else {
-        if (k <= 32) hipLaunchKernelGGL((k_mc_heavy_batch<32, false>), g, b, 0, st, tb, nslot);
-        else if (k <= 64) hipLaunchKernelGGL((k_mc_heavy_batch<64, false>), g, b, 0, st, tb, nslot);
-        else if (k <= 128) hipLaunchKernelGGL((k_mc_heavy_batch<128, false>), g, b, 0, st, tb, nslot);
-        else hipLaunchKernelGGL((k_mc_heavy_batch<256, false>), g, b, 0, st, tb, nslot);
+        if (k <= 32) hipLaunchKernelGGL((k_mc_batch<32, false>), g, b, 0, st, tb, nslot);
+        else if (k <= 64) hipLaunchKernelGGL((k_mc_batch<64, false>), g, b, 0, st, tb, nslot);
+        else if (k <= 128) hipLaunchKernelGGL((k_mc_batch<128, false>), g, b, 0, st, tb, nslot);
+        else hipLaunchKernelGGL((k_mc_batch<256, false>), g, b, 0, st, tb, nslot);
     }
     return 0;
 }
 
-// Sampling and audit of every run as stages of one interval: the screen, the per-lane event pass (k <= 64), the pass over the
-// deferred particles of every run (one launch through a table of the runs'
-// arguments, shaped for the largest k), then the audit.  Draws take the interval index from each run's interval state.
+// Sampling and audit of every run as stages of one interval: the screen, the
+// listed particles of every run (one launch through a table of the runs'
+// arguments, shaped for the largest k), then the audit.  Draws take the
+// interval index from each run's interval state.
 static void many_table_step(char* base, const ManyStep& s, hipStream_t st)
 {
     launch_sample_table(base + s.tab, int32_t(s.a0), int32_t(s.a1 >> 1), int32_t(s.a1 & 1), st, int32_t(s.nblocks));
@@ -910,7 +675,7 @@ void many_sample(ManyBuilder& B, const std::vector<ManyRun>& R)
 {
     const size_t nr = R.size();
     std::vector<McArgs> ma(nr);
-    std::vector<int64_t> nb(nr), scr_d(nr), scr_l(nr);
+    std::vector<int64_t> nb(nr);
     int kmax = 1, f32 = 0;
     for (size_t r = 0; r < nr; ++r) {
         const ManyRun& x = R[r];
@@ -920,35 +685,11 @@ void many_sample(ManyBuilder& B, const std::vector<ManyRun>& R)
         ma[r].interval_at = x.interval_at;
         ma[r].active = B.active ? B.active + r : nullptr;
         nb[r] = cdiv(x.p.n, 256);
-        scr_d[r] = x.p.k > 64 ? nb[r] : 0;
-        scr_l[r] = x.p.k > 64 ? 0 : nb[r];
         kmax = std::max(kmax, int(x.p.k));
         f32 = x.p.rates_fp32 ? 1 : 0;
     }
-    B.add<McScreen<true>>(ma, scr_d);
-    B.add<McScreen<false>>(ma, scr_l);
-    for (int cls = 0; cls < 2; ++cls) {
-        std::vector<EventArgs> ev(nr);
-        std::vector<int64_t> eb(nr, 0);
-        bool any = false;
-        for (size_t r = 0; r < nr; ++r) {
-            const int k = R[r].p.k;
-            ev[r] = EventArgs{ma[r], nb[r]};
-            if (k <= 64 && (k <= 32) == (cls == 0)) {
-                eb[r] = std::min<int64_t>(kEventBlocks, std::max<int64_t>(1, cdiv(R[r].p.n, B.tune.event_div)));
-                any = true;
-            }
-        }
-        if (!any) continue;
-        if (cls == 0) {
-            if (f32) B.add<McEvents<32, true>>(ev, eb);
-            else B.add<McEvents<32, false>>(ev, eb);
-        } else {
-            if (f32) B.add<McEvents<64, true>>(ev, eb);
-            else B.add<McEvents<64, false>>(ev, eb);
-        }
-    }
-    // the deferred particles of every run: a table (256-byte header, then
+    B.add<McScreen>(ma, nb);
+    // the listed particles of every run: a table (256-byte header, then
     // the runs' arguments) in the arena
     std::vector<char> table(kTableHeader + sizeof(McArgs) * nr, 0);
     memcpy(table.data() + kTableHeader, ma.data(), sizeof(McArgs) * nr);

@@ -455,10 +455,6 @@ __device__ inline void plan_rule(const ReduceArgs& A, const BinRow* row, uint64_
     iv->exe_ticks = size;
     iv->n_groups = ng;
     h->scratch[0] = 0.0;  // event counter of the coming interval
-    h->heavy_n = 0;       // and the sampling's deferred particles
-    h->heavy_next = 0;
-    h->heavy_n0 = 0;
-    h->heavy_next0 = 0;
 }
 
 // Audit (a reading: the paper names what the audit monitors, not its rule):
@@ -759,11 +755,12 @@ __device__ __forceinline__ void Reduce<MODE>::body(const Args& A, Blk B)
     if (mode == 0) plan_rule(A, row, s_m[0], s_m[1], lane, s_first, s_last);
     else audit_rule(A, row, s_m[0], s_m[1], lane, s_first, s_last);
     // the coming sampling's list of particles with events starts empty
-    if (lane <= kXcd) h->mc_seg[lane] = 0;  // (and mc_next, which follows)
+    if (lane == 0) {
+        h->mc_n = 0;
+        h->mc_early_n = 0;
+        h->mc_next = 0;
+    }
 }
-
-static_assert(offsetof(WsHeader, mc_next) == offsetof(WsHeader, mc_seg) + kXcd * sizeof(int32_t),
-              "the segment counts and the next counter are cleared together");
 
 static ReduceArgs reduce_args(const gd_problem* p, const double* msnap, const double* M, const double* va,
                               const double* vb, int64_t n, gd_interval* iv, void* ws, const Layout& L)

@@ -8,7 +8,7 @@ advances on its own:
 
     a tier round = one interval of every run of the tier, as one launch per
     stage over all of them (gd_many_interval: sort, tree, search, rates and
-    plan, sampling with one pass over the deferred particles of the tier,
+    plan, sampling with one pass over the listed particles of the tier,
     audit, push).
 
 Tiers are not in lock-step: a tier whose round has finished starts its next
