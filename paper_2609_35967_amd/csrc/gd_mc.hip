@@ -49,6 +49,7 @@ struct McArgs {
     int32_t* early_n;
     int32_t* next;
     double early_events;
+    int32_t screen_rounds;  // particles per thread of the screen
     int64_t n_all;  // length of the snapshot: neighbour indices lie in [0, n_all)
     const int64_t* interval_at;  // when set: the interval index (a spatial group's number in planning order)
     const int32_t* active;       // when set and 0: the run has no interval now (its list is skipped)
@@ -78,37 +79,55 @@ constexpr int kChunk = 8;
 // each listed particle in half a wavefront (k <= 32) or a whole one, the long
 // ones first, and redraws the first event's numbers (the same counters, so
 // the same numbers).  One atomic per workgroup and list end.
+constexpr int kScreenRounds = 4;
+
+// particles per thread of the screen: each block's add to the list's count
+// waits about 12 ns for the ones before it, which is all of the pass at one
+// particle a thread and a million particles
+static int32_t screen_rounds(int64_t n) { return n > 131072 ? kScreenRounds : 1; }
+
 struct McScreen {
     using Args = McArgs;
     static constexpr int kThreads = 256;
     static __device__ __forceinline__ void body(const Args& A, Blk B)
     {
         __shared__ int32_t s_w[2][4], s_base[2];
-        const int64_t i = B.id * int64_t(blockDim.x) + threadIdx.x;
+        const int64_t i0 = B.id * int64_t(256 * A.screen_rounds) + threadIdx.x;
         const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-        bool ev = false, early = false;
-        if (i < A.P.n) {
-            const int c = A.cnt[i];
-            const double m = A.m[i];
-            const double li = A.lam_i[i];
-            if (c > 1 && li > 0.0) {
-                const uint32_t interval = mc_interval(A);
-                double u[4];
-                event_uniforms(A.seed, A.id[i], interval, 0u, u);
-                ev = !(-log(u[0]) / li > A.iv->dt_exe);
-                early = ev && A.early_events > 0.0 && li * A.iv->dt_exe >= A.early_events;
+        const uint64_t below = (uint64_t(1) << lane) - 1;
+        const uint32_t interval = mc_interval(A);
+        const double dt_exe = A.iv->dt_exe;
+        uint64_t bl[kScreenRounds], be[kScreenRounds];  // lanes listed, at the start and at the end
+        int32_t nl = 0, ne = 0;
+#pragma unroll
+        for (int r = 0; r < kScreenRounds; ++r) {
+            const int64_t i = i0 + r * 256;
+            bool ev = false, early = false;
+            if (r < A.screen_rounds && i < A.P.n) {
+                const int c = A.cnt[i];
+                const double m = A.m[i];
+                const double li = A.lam_i[i];
+                if (c > 1 && li > 0.0) {
+                    double u[4];
+                    event_uniforms(A.seed, A.id[i], interval, 0u, u);
+                    ev = !(-log(u[0]) / li > dt_exe);
+                    early = ev && A.early_events > 0.0 && li * dt_exe >= A.early_events;
+                }
+                if (!ev) {
+                    A.m_out[i] = m;
+                    if (A.n_events) A.n_events[i] = 0;
+                }
+                if (A.log)
+                    for (int f = 0; f < A.log_cap; ++f) A.log[i * A.log_cap + f] = -1;
             }
-            if (!ev) {
-                A.m_out[i] = m;
-                if (A.n_events) A.n_events[i] = 0;
-            }
-            if (A.log)
-                for (int f = 0; f < A.log_cap; ++f) A.log[i * A.log_cap + f] = -1;
+            bl[r] = __ballot(ev && !early);
+            be[r] = __ballot(early);
+            nl += int32_t(__popcll(bl[r]));
+            ne += int32_t(__popcll(be[r]));
         }
-        const uint64_t bl = __ballot(ev && !early), be = __ballot(early);
         if (lane == 0) {
-            s_w[0][wv] = int32_t(__popcll(bl));
-            s_w[1][wv] = int32_t(__popcll(be));
+            s_w[0][wv] = nl;
+            s_w[1][wv] = ne;
         }
         __syncthreads();
         if (threadIdx.x < 2) {
@@ -117,11 +136,19 @@ struct McScreen {
             s_base[threadIdx.x] = tot ? atomicAdd(threadIdx.x == 0 ? A.list_n : A.early_n, tot) : 0;
         }
         __syncthreads();
-        if (!ev) return;
-        const int e = early ? 1 : 0;
-        int32_t at = s_base[e] + int32_t(__popcll((early ? be : bl) & ((uint64_t(1) << lane) - 1)));
-        for (int w = 0; w < wv; ++w) at += s_w[e][w];
-        A.list[early ? A.P.n - 1 - at : at] = int32_t(i);
+        int32_t al = s_base[0], ae = s_base[1];
+        for (int w = 0; w < wv; ++w) {
+            al += s_w[0][w];
+            ae += s_w[1][w];
+        }
+#pragma unroll
+        for (int r = 0; r < kScreenRounds; ++r) {
+            const int32_t i = int32_t(i0 + r * 256);
+            if ((bl[r] >> lane) & 1u) A.list[al + int32_t(__popcll(bl[r] & below))] = i;
+            if ((be[r] >> lane) & 1u) A.list[A.P.n - 1 - (ae + int32_t(__popcll(be[r] & below)))] = i;
+            al += int32_t(__popcll(bl[r]));
+            ae += int32_t(__popcll(be[r]));
+        }
     }
 };
 
@@ -419,18 +446,26 @@ __global__ __launch_bounds__(256, KP2 <= 32 ? 4 : 1) void k_mc(McArgs A)
     const int32_t nw = int32_t(gridDim.x * (blockDim.x / kWave));
     Chunks C;
     C.set(*A.early_n, *A.list_n, nw);
-    unsigned long long ev_total = 0;
     // wavefront w takes chunk w first, then chunks nw, nw + 1, ... from the
-    // counter (a wavefront with no first chunk touches no counter)
+    // counter (which is left alone when there are no more than nw); one add of
+    // the events per workgroup: adds to one address wait 12 ns each for the
+    // ones before them
+    __shared__ unsigned long long s_ev[4];
+    unsigned long long ev = 0;
     int32_t x = __builtin_amdgcn_readfirstlane(int32_t(blockIdx.x * (blockDim.x / kWave) + threadIdx.x / kWave));
-    for (;;) {
-        if (x >= C.k) break;
-        ev_total += (unsigned long long)C.run<KP2, F32>(A, x, lane);
+    while (x < C.k) {
+        ev += (unsigned long long)C.run<KP2, F32>(A, x, lane);
+        if (C.k <= nw) break;
         int32_t next = 0;
         if (lane == 0) next = atomicAdd(A.next, 1);
         x = nw + __builtin_amdgcn_readfirstlane(next);
     }
-    if (lane == 0 && ev_total) atomicAdd(A.ev_counter, ev_total);
+    if (lane == 0) s_ev[threadIdx.x / kWave] = ev;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        ev = s_ev[0] + s_ev[1] + s_ev[2] + s_ev[3];
+        if (ev) atomicAdd(A.ev_counter, ev);
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -560,13 +595,14 @@ static McArgs mc_args(const gd_problem* p, const gd_particles* s, const gd_neigh
     A.early_n = &h->mc_early_n;
     A.next = &h->mc_next;
     A.early_events = kEarlyEvents;
+    A.screen_rounds = screen_rounds(p->n);
     A.n_all = p->n;
     return A;
 }
 
 static void launch_screen(const McArgs& A, hipStream_t st)
 {
-    hipLaunchKernelGGL(k_mc_screen, dim3(unsigned((A.P.n + 255) / 256)), dim3(256), 0, st, A);
+    hipLaunchKernelGGL(k_mc_screen, dim3(unsigned(cdiv(A.P.n, 256 * A.screen_rounds))), dim3(256), 0, st, A);
 }
 
 template <bool F32>
@@ -629,6 +665,7 @@ int launch_sample_group(const gd_problem* p, const gd_particles* s, const gd_nei
     A.m_out = s->m[s->cur ^ 1] + lo;
     A.n_events = n_events ? n_events + lo : nullptr;
     prof_mark(GD_PROF_MC, 0, st);
+    A.screen_rounds = screen_rounds(cnt);
     if (cnt > 0) launch_screen(A, st);
     launch_listed(A, p, st);
     prof_mark(GD_PROF_MC, 1, st);
@@ -684,7 +721,7 @@ void many_sample(ManyBuilder& B, const std::vector<ManyRun>& R)
         if (x.n_all >= 0) ma[r].n_all = x.n_all;
         ma[r].interval_at = x.interval_at;
         ma[r].active = B.active ? B.active + r : nullptr;
-        nb[r] = cdiv(x.p.n, 256);
+        nb[r] = cdiv(x.p.n, 256 * ma[r].screen_rounds);
         kmax = std::max(kmax, int(x.p.k));
         f32 = x.p.rates_fp32 ? 1 : 0;
     }
