@@ -70,21 +70,24 @@ __device__ inline double sinc_(double a)
     return sin(a) / a;
 }
 
-__device__ inline void drift(double& r, double& th, double& ph, double vr, double lth, double lph, double tau)
+// (sine and cosine of each angle are formed once: every angle is used several
+// times over the drift, the forces and the position)
+__device__ inline void drift(double& r, double& th, double& ph, double& st, double& ct, double vr, double lth,
+                             double lph, double tau)
 {
-    const double r0 = r, th0 = th;
+    const double r0 = r, st0 = st;
     const double r1 = r0 + vr * tau;
     const double u = tau / (r0 * r1);
     const double a = lth * u;
-    const double th1 = th0 + a;
-    ph = ph + lph * u * sinc_(a) / (sin(th0) * sin(th1));
+    th = th + a;
+    sincos(th, &st, &ct);
+    ph = ph + lph * u * sinc_(a) / (st0 * st);
     r = r1;
-    th = th1;
 }
 
-__device__ inline void forces(double GM, double r, double th, double lth, double lph, double& fr, double& fth)
+__device__ inline void forces(double GM, double r, double st, double ct, double lth, double lph, double& fr,
+                              double& fth)
 {
-    const double st = sin(th), ct = cos(th);
     const double r2 = r * r, r3 = r2 * r;
     fr = -GM / r2 + lth * lth / r3 + lph * lph / (r3 * (st * st));
     fth = lph * lph * ct / (r2 * (st * st * st));
@@ -119,12 +122,14 @@ __device__ __forceinline__ void PushGlobal::body(const Args& A, Blk B)
     const double h = 0.5 * dt;
     double ri = A.r[i], ti = A.th[i], pi_ = A.ph[i];
     const double y0 = A.vr[i], y1 = A.lth[i], y2 = A.lph[i];
-    drift(ri, ti, pi_, y0, y1, y2, h);
+    double sti, cti;
+    sincos(ti, &sti, &cti);
+    drift(ri, ti, pi_, sti, cti, y0, y1, y2, h);
     double fr0, ft0;
-    forces(P.GM, ri, ti, y1, y2, fr0, ft0);
+    forces(P.GM, ri, sti, cti, y1, y2, fr0, ft0);
     double n0, n1, n2;
     if (P.drag) {
-        const double R = ri * sin(ti), Z = ri * cos(ti);
+        const double R = ri * sti, Z = ri * cti;
         Gas g;
         gas_at(P, R, Z, g);
         const double s = grain_size(P, A.m[i]);
@@ -136,29 +141,30 @@ __device__ __forceinline__ void PushGlobal::body(const Args& A, Blk B)
         const double p1 = y1 * Eh + (ft0 * ts) * Gh;
         const double p2 = y2 * Eh + lg * Gh;
         double fr1, ft1;
-        forces(P.GM, ri, ti, p1, p2, fr1, ft1);
+        forces(P.GM, ri, sti, cti, p1, p2, fr1, ft1);
         n0 = y0 * E + (fr1 * ts) * G;
         n1 = y1 * E + (ft1 * ts) * G;
         n2 = y2 * E + lg * G;
     } else {
         const double p1 = y1 + ft0 * h;
         double fr1, ft1;
-        forces(P.GM, ri, ti, p1, y2, fr1, ft1);
+        forces(P.GM, ri, sti, cti, p1, y2, fr1, ft1);
         n0 = y0 + fr1 * dt;
         n1 = y1 + ft1 * dt;
         n2 = y2;
     }
-    drift(ri, ti, pi_, n0, n1, n2, h);
+    drift(ri, ti, pi_, sti, cti, n0, n1, n2, h);
     A.r[i] = ri;
     A.th[i] = ti;
     A.ph[i] = pi_;
     A.vr[i] = n0;
     A.lth[i] = n1;
     A.lph[i] = n2;
-    const double st = sin(ti);
-    A.x[i] = ri * st * cos(pi_);
-    A.y[i] = ri * st * sin(pi_);
-    A.z[i] = ri * cos(ti);
+    double sp, cp;
+    sincos(pi_, &sp, &cp);
+    A.x[i] = ri * sti * cp;
+    A.y[i] = ri * sti * sp;
+    A.z[i] = ri * cti;
     if (ri < P.r_in || ri > P.r_out) A.M[i] = 0.0;
 }
 
