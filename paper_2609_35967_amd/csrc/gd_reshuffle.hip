@@ -36,53 +36,69 @@ __device__ inline uint32_t feistel4(uint32_t x, int h, uint32_t mask, uint32_t k
     return (L << h) | R;
 }
 
-__device__ inline uint32_t pi_of(uint32_t j, int64_t N, uint64_t seed, uint32_t refresh)
+// pi once per active slot: table[j] = pi(j), j < N.  A walk takes up to
+// 4^h / N applications on average (2.1 at N = 500,009) but several times that
+// in the slowest of 64 lanes, so a lane whose walk has ended goes on with the
+// next of its slots (kWalks of them in large sets) instead of waiting.
+constexpr int kWalks = 8;
+
+__global__ __launch_bounds__(256) void k_reshuffle_table(int32_t* __restrict__ table,
+                                                         const int32_t* __restrict__ n_active, int64_t n,
+                                                         uint64_t seed, uint32_t refresh)
 {
+    const int64_t stride = int64_t(gridDim.x) * blockDim.x;
+    const int64_t N = *n_active < n ? *n_active : n;
+    if (N <= 1) return;
     int bits = 0;
     while ((int64_t(1) << bits) < N) ++bits;
     const int h = (bits + 1) >> 1;
     const uint32_t mask = (1u << h) - 1u;
     const uint32_t k0 = uint32_t(seed), k1 = uint32_t(seed >> 32);
-    const int64_t cap = int64_t(1) << (2 * h);  // the network's domain: a walk is shorter
-    uint32_t x = j;
-    for (int64_t step = 0; step < cap; ++step) {
+    int64_t j = blockIdx.x * int64_t(blockDim.x) + threadIdx.x;
+    uint32_t x = uint32_t(j);
+    int64_t left = int64_t(1) << (2 * h);  // the network's domain: a walk is shorter
+    while (j < N) {
         x = feistel4(x, h, mask, k0, k1, refresh);
-        if (int64_t(x) < N) break;
+        if (int64_t(x) < N || --left == 0) {
+            table[j] = int32_t(x);
+            j += stride;
+            x = uint32_t(j);
+            left = int64_t(1) << (2 * h);
+        }
     }
-    return x;
 }
 
-// pi once per active slot: table[j] = pi(j), j < N
-__global__ __launch_bounds__(256) void k_reshuffle_table(int32_t* __restrict__ table,
-                                                         const int32_t* __restrict__ n_active, int64_t n,
-                                                         uint64_t seed, uint32_t refresh)
-{
-    const int64_t j = blockIdx.x * int64_t(blockDim.x) + threadIdx.x;
-    const int64_t N = *n_active;
-    if (j >= n || j >= N || N <= 1) return;
-    table[j] = int32_t(pi_of(uint32_t(j), N, seed, refresh));
-}
-
-// one thread per (particle, slot); slots 1 .. cnt-1 of active rows are
-// relabelled.  n * k < 2^31 (checked on the host), so 32-bit index arithmetic
+// Slots 1 .. cnt-1 of active rows are relabelled, kRun consecutive entries per
+// thread, read before any is looked up so that their reads are in flight
+// together.  n * k < 2^31 (checked on the host), so 32-bit index arithmetic
 // holds; KS > 0 is log2(k) for a power-of-two k, 0 for any other k.
+constexpr int kRun = 4;
+
 template <int KS>
 __global__ __launch_bounds__(256) void k_reshuffle_apply(int32_t* __restrict__ nbr, const int32_t* __restrict__ cnt,
                                                          const int32_t* __restrict__ n_active,
                                                          const int32_t* __restrict__ table, uint32_t total, uint32_t k)
 {
-    const uint32_t e = blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= total) return;
-    const uint32_t i = KS > 0 ? (e >> KS) : e / k;
-    const uint32_t s = e - i * k;
     const int32_t N = *n_active;
-    if (s == 0 || N <= 1 || int32_t(i) >= N || int32_t(s) >= cnt[i]) return;
-    const int32_t j = nbr[e];
-    if (j < 0 || j >= N) return;
+    const uint32_t e0 = blockIdx.x * (256u * kRun) + threadIdx.x;
+    uint32_t i[kRun];
+    int32_t j[kRun], v[kRun];
+#pragma unroll
+    for (int t = 0; t < kRun; ++t) {
+        const uint32_t e = e0 + t * 256u;
+        i[t] = KS > 0 ? (e >> KS) : e / k;
+        j[t] = e < total ? nbr[e] : -1;
+        const uint32_t s = e - i[t] * k;
+        const bool in = e < total && s != 0 && N > 1 && int32_t(i[t]) < N;
+        if (!in || int32_t(s) >= cnt[i[t]] || j[t] >= N) j[t] = -1;
+    }
+#pragma unroll
+    for (int t = 0; t < kRun; ++t) v[t] = j[t] >= 0 ? table[j[t]] : 0;
     // pi is a bijection and the row's others exclude i, so exactly one other
     // can be sent onto i; it takes pi(i), which no other slot receives
-    const int32_t v = table[j];
-    nbr[e] = v == int32_t(i) ? table[i] : v;
+#pragma unroll
+    for (int t = 0; t < kRun; ++t)
+        if (j[t] >= 0) nbr[e0 + t * 256u] = v[t] == int32_t(i[t]) ? table[i[t]] : v[t];
 }
 
 // pi of every active slot into `table`, then every cached entry relabelled
@@ -91,9 +107,10 @@ static void launch_with_table(const gd_problem* p, const gd_neighbors* nb, uint6
 {
     const int64_t total = p->n * int64_t(p->k);
     if (total <= 0) return;
-    hipLaunchKernelGGL(k_reshuffle_table, dim3(unsigned((p->n + 255) / 256)), dim3(256), 0, st, table, nb->n_active,
-                       p->n, seed, refresh);
-    const dim3 grid(unsigned((total + 255) / 256));
+    const int64_t tb = cdiv(p->n, 256 * (p->n > 131072 ? kWalks : 1));
+    hipLaunchKernelGGL(k_reshuffle_table, dim3(unsigned(tb)), dim3(256), 0, st, table, nb->n_active, p->n, seed,
+                       refresh);
+    const dim3 grid(unsigned(cdiv(total, 256 * kRun)));
     const uint32_t t32 = uint32_t(total), k = uint32_t(p->k);
     if (k == 32)
         hipLaunchKernelGGL(k_reshuffle_apply<5>, grid, dim3(256), 0, st, nb->nbr, nb->cnt, nb->n_active, table, t32, k);
