@@ -97,7 +97,7 @@ __host__ inline Layout make_layout(int64_t n, int32_t k)
     // takes as long as its longest block); about as many groups as blocks in
     // a group, since every scatter block adds up a row of each
     L.sort_rounds = 1;
-    while (L.sort_rounds < kSortRounds && n > int64_t(128) * 256 * L.sort_rounds) L.sort_rounds *= 2;
+    while (L.sort_rounds < kSortRounds && n > int64_t(512) * 256 * L.sort_rounds) L.sort_rounds *= 2;
     L.nsort_blocks = int32_t((n + 256 * L.sort_rounds - 1) / (256 * L.sort_rounds));
     L.sort_sup = 8;
     while (int64_t(L.sort_sup) * L.sort_sup < L.nsort_blocks) L.sort_sup *= 2;
