@@ -28,7 +28,8 @@ struct McArgs {
     const double* x;
     const double* y;
     const double* z;
-    const double4* snap;  // packed (m, s, N, 0) of the frozen neighbourhood
+    const double4* snap;  // packed (m, s, N, 1/m) of the frozen neighbourhood
+    const double* m_all;  // when set: the frozen masses in the records' place (dimensionless kernels)
     const double* lam_i;
     const gd_interval* iv;
     double* m_out;
@@ -274,7 +275,7 @@ __device__ inline int run_chunk(const McArgs& A, int32_t lo, int32_t hi, bool fa
                     int j = s < c ? A.nbr[i * k + s] : 0;
                     if (s < c && (j < 0 || j >= A.n_all)) set_status(A.ws, GD_DEV_INTERNAL);
                     if (j < 0 || j >= A.n_all) j = 0;
-                    const double4 sn = A.snap[j];
+                    const double4 sn = A.m_all ? make_double4(A.m_all[j], 0.0, 0.0, 0.0) : A.snap[j];
                     if (F32) {
                         nb[r].mj = sn.x;
                         nb[r].sj = phys ? sn.y : 0.0;
@@ -626,6 +627,7 @@ int launch_sample(const gd_problem* p, const gd_particles* s, const gd_neighbors
                   int32_t log_cap, void* ws, const Layout& L, hipStream_t st, void* table, int32_t slot)
 {
     McArgs A = mc_args(p, s, nb, iv, lam_i, seed, interval, interval_on_device, n_events, log, log_cap, ws, L);
+    if (p->kernel != GD_KERNEL_PHYSICAL) A.m_all = A.m;  // (as the rates pass)
     prof_mark(GD_PROF_MC, 0, st);
     // (the list's counts are cleared by the plan and by every audit; a run of
     // the table form may sample again before its audit)
@@ -718,6 +720,7 @@ void many_sample(ManyBuilder& B, const std::vector<ManyRun>& R)
         const ManyRun& x = R[r];
         ma[r] = mc_args(&x.p, &x.out, &x.nb, x.iv, x.lam_i, x.seed, 0u, true, x.n_events, nullptr, 0, x.ws, x.L);
         if (x.snap) ma[r].snap = x.snap;
+        else if (x.p.kernel != GD_KERNEL_PHYSICAL) ma[r].m_all = ma[r].m;
         if (x.n_all >= 0) ma[r].n_all = x.n_all;
         ma[r].interval_at = x.interval_at;
         ma[r].active = B.active ? B.active + r : nullptr;

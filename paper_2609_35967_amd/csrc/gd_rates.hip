@@ -63,7 +63,15 @@ struct RatesArgs {
     double* b;
     void* ws;
     int64_t n_all;  // length of the snapshot: neighbour indices lie in [0, n_all)
+    // when set: the frozen masses themselves, in the records' place (the
+    // dimensionless kernels read nothing else of a neighbour)
+    const double* m_all;
 };
+
+__device__ inline double4 neighbour_record(const double4* snap, const double* m_all, int j)
+{
+    return m_all ? make_double4(m_all[j], 0.0, 0.0, 0.0) : snap[j];
+}
 
 constexpr int kGather = 4;  // neighbours whose slot and record loads a lane has in flight together
 
@@ -73,7 +81,7 @@ constexpr int kGather = 4;  // neighbours whose slot and record loads a lane has
 // invalid slots are left for the caller to flag.
 template <int LANES>
 __device__ inline void gather_neighbours(const int32_t* row, int s0, int sub, int cmax, int64_t n, const double4* snap,
-                                         int (&jj)[kGather], double4 (&rec)[kGather])
+                                         const double* m_all, int (&jj)[kGather], double4 (&rec)[kGather])
 {
 #pragma unroll
     for (int t = 0; t < kGather; ++t) {
@@ -81,7 +89,8 @@ __device__ inline void gather_neighbours(const int32_t* row, int s0, int sub, in
         jj[t] = s < cmax ? row[s] : -1;
     }
 #pragma unroll
-    for (int t = 0; t < kGather; ++t) rec[t] = (jj[t] >= 0 && jj[t] < n) ? snap[jj[t]] : make_double4(0.0, 0.0, 0.0, 0.0);
+    for (int t = 0; t < kGather; ++t) 
+        rec[t] = (jj[t] >= 0 && jj[t] < n) ? neighbour_record(snap, m_all, jj[t]) : make_double4(0.0, 0.0, 0.0, 0.0);
 }
 
 // lane l of every group of LANES lanes read by the whole group (DPP quad
@@ -146,7 +155,7 @@ __device__ __forceinline__ void Rates<LANES>::body(const Args& A, Blk B)
         for (int s0 = 0; s0 < cmax; s0 += kGather * LANES) {
             int jj[kGather];
             double4 rec[kGather];
-            gather_neighbours<LANES>(A.nbr + i * k, s0, sub, cmax, A.n_all, A.snap, jj, rec);
+            gather_neighbours<LANES>(A.nbr + i * k, s0, sub, cmax, A.n_all, A.snap, A.m_all, jj, rec);
 #pragma unroll
             for (int t = 0; t < kGather; ++t) {
                 if (s0 + t * LANES >= cmax) break;  // the same in the particle's lanes
@@ -226,7 +235,7 @@ __device__ __forceinline__ void RatesF32<LANES>::body(const Args& A, Blk B)
         for (int s0 = 0; s0 < cmax; s0 += kGather * LANES) {
             int jj[kGather];
             double4 rec[kGather];
-            gather_neighbours<LANES>(A.nbr + i * k, s0, sub, cmax, A.n_all, A.snap, jj, rec);
+            gather_neighbours<LANES>(A.nbr + i * k, s0, sub, cmax, A.n_all, A.snap, A.m_all, jj, rec);
 #pragma unroll
             for (int t = 0; t < kGather; ++t) {
                 if (s0 + t * LANES >= cmax) break;
@@ -813,8 +822,12 @@ int launch_rates(const gd_problem* p, const gd_particles* s, const gd_neighbors*
     const double* m = s->m[s->cur];
     double4* snap = at<double4>(ws, L.snap);
     prof_mark(GD_PROF_RATES, 0, st);
-    hipLaunchKernelGGL(k_snapshot, dim3(g), dim3(256), 0, st, SnapArgs{P, m, s->M, n, snap});
+    // (the dimensionless kernels need no records: a launch less, and 8 bytes
+    // instead of 32 per neighbour)
+    const bool records = p->kernel == GD_KERNEL_PHYSICAL;
+    if (records) hipLaunchKernelGGL(k_snapshot, dim3(g), dim3(256), 0, st, SnapArgs{P, m, s->M, n, snap});
     RatesArgs A{};
+    A.m_all = records ? nullptr : m;
     A.P = P;
     A.nbr = nb->nbr;
     A.cnt = nb->cnt;
@@ -942,7 +955,9 @@ void many_rates(ManyBuilder& B, const std::vector<ManyRun>& R, bool own_snapshot
         A.b = at<double>(x.ws, x.L.b);
         A.ws = x.ws;
         A.n_all = x.n_all >= 0 ? x.n_all : n;
-        nb[r] = cdiv(n, 256);
+        const bool records = x.snap || p->kernel == GD_KERNEL_PHYSICAL;
+        A.m_all = records ? nullptr : m;
+        nb[r] = records ? cdiv(n, 256) : 0;
         f64[r] = p->rates_fp32 ? 0 : cdiv(n * lanes, 256);
         f32[r] = p->rates_fp32 ? cdiv(n * lanes, 256) : 0;
         nred[r] = std::min<int64_t>(kRedBlocks, std::max<int64_t>(1, cdiv(n, B.tune.red_div)));
