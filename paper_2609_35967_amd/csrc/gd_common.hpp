@@ -208,8 +208,13 @@ struct RunMap {
     const int32_t* active;  // per-run flags read on the device (null: every run); a run whose flag is 0 skips the stage
 };
 
+// wavefronts per SIMD asked of the compiler for K's many-run launch (the
+// one-run kernel of a body that asks for more than it would get states it too)
 template <class K>
-__global__ __launch_bounds__(K::kThreads) void k_many(const typename K::Args* __restrict__ T, RunMap M)
+constexpr int kWavesPerSimd = 1;
+
+template <class K>
+__global__ __launch_bounds__(K::kThreads, kWavesPerSimd<K>) void k_many(const typename K::Args* __restrict__ T, RunMap M)
 {
     const int32_t r = M.run[blockIdx.x];
     if (M.active && !M.active[r]) return;

@@ -195,13 +195,24 @@ struct TreeLowArgs {
     int32_t* zf;
 };
 
+struct TreeLow {
+    using Args = TreeLowArgs;
+    static constexpr int kThreads = 256;
+    static __device__ __forceinline__ void body(const Args& A, Blk B);
+};
+
 __global__ __launch_bounds__(256) void k_tree_low(TreeLowArgs A)
+{
+    TreeLow::body(A, Blk{int64_t(blockIdx.x), int64_t(gridDim.x)});
+}
+
+__device__ __forceinline__ void TreeLow::body(const Args& A, Blk B)
 {
     __shared__ FBox s0[256];
     __shared__ FBox s1[32];
     const int t = threadIdx.x;
-    if (blockIdx.x == 0 && t == 0) *A.zf = 0;
-    const int64_t b = int64_t(blockIdx.x) * 256 + t;
+    if (B.id == 0 && t == 0) *A.zf = 0;
+    const int64_t b = B.id * 256 + t;
     FBox x = empty_box();
     if (b < A.b.cap0) {
         x = bucket_box(A.b, b);
@@ -212,17 +223,17 @@ __global__ __launch_bounds__(256) void k_tree_low(TreeLowArgs A)
     if (t < 32) {
         FBox u = empty_box();
         for (int c = 0; c < kFan; ++c) box_union(u, s0[t * kFan + c]);
-        const int64_t i1 = int64_t(blockIdx.x) * 32 + t;
+        const int64_t i1 = B.id * 32 + t;
         if (i1 < A.cap1) A.box1[i1] = u;
         else u = empty_box();
         s1[t] = u;
     }
-    if (!A.box2) return;  // the same for every thread of the grid
+    if (!A.box2) return;  // the same for every thread of the run's blocks
     __syncthreads();
     if (t < 4) {
         FBox u = empty_box();
         for (int c = 0; c < kFan; ++c) box_union(u, s1[t * kFan + c]);
-        const int64_t i2 = int64_t(blockIdx.x) * 4 + t;
+        const int64_t i2 = B.id * 4 + t;
         if (i2 < A.cap2) A.box2[i2] = u;
     }
 }
@@ -238,7 +249,18 @@ struct TreeTailArgs {
     int32_t l0;
 };
 
+struct TreeTail {
+    using Args = TreeTailArgs;
+    static constexpr int kThreads = 256;
+    static __device__ __forceinline__ void body(const Args& A, Blk B);
+};
+
 __global__ __launch_bounds__(256) void k_tree_tail(TreeTailArgs A)
+{
+    TreeTail::body(A, Blk{0, 1});
+}
+
+__device__ __forceinline__ void TreeTail::body(const Args& A, Blk)
 {
     __shared__ FBox s[2][kTailCap];
     const int t = threadIdx.x;
@@ -926,6 +948,9 @@ struct KnnSetup {
     bool per;
     BucketArgs bucket;
     LevelArgs level[kMaxTreeLevels];
+    TreeLowArgs low;    // levels 0 .. built (trees of more than one level)
+    int built;
+    TreeTailArgs tail;  // levels tail.l0 and up, when there are any
     KnnArgs A;
 };
 
@@ -954,6 +979,15 @@ static KnnSetup knn_setup(const gd_problem* p, const gd_neighbors* nb, void* ws,
     S.bucket = BucketArgs{pos, h, boxes + T.off[0], T.cap[0], S.P};
     for (int l = 1; l < L.levels; ++l)
         S.level[l] = LevelArgs{boxes + T.off[l - 1], T.cap[l - 1], boxes + T.off[l], T.cap[l]};
+    if (L.levels > 1) {
+        const bool two = L.levels > 2 && cdiv(T.cap[0], 256) * 4 >= T.cap[2];
+        S.low = TreeLowArgs{S.bucket, S.level[1].cur, T.cap[1], two ? S.level[2].cur : nullptr, two ? T.cap[2] : 0,
+                            &at<WsHeader>(ws, L.hdr)->knn_fb_n};
+        S.built = two ? 2 : 1;
+    }
+    int l0 = S.built + 1;
+    while (l0 < L.levels && T.cap[l0] > kTailCap) ++l0;
+    S.tail = TreeTailArgs{boxes, T, int32_t(l0)};
     KnnArgs& A = S.A;
     A.pos = pos;
     A.boxes = boxes;
@@ -1000,25 +1034,13 @@ int launch_knn(const gd_problem* p, const gd_neighbors* nb, void* ws, const Layo
     prof_mark(GD_PROF_TREE, 0, st);
     // buckets and level 1 (and 2) in one pass, the wide levels above one
     // pass each, the small top levels in one workgroup
-    const int64_t g0 = (T.cap[0] + 255) / 256;
+    const unsigned g0 = unsigned(cdiv(T.cap[0], 256));
     WsHeader* hw = at<WsHeader>(ws, L.hdr);
-    int built = 0;
-    if (L.levels == 1) {
-        hipLaunchKernelGGL(k_bucket_boxes, dim3(unsigned(g0)), dim3(256), 0, st, S.bucket);
-    } else {
-        const bool two = L.levels > 2 && g0 * 4 >= T.cap[2];
-        const TreeLowArgs TL{S.bucket, S.level[1].cur, T.cap[1], two ? S.level[2].cur : nullptr, two ? T.cap[2] : 0,
-                             &hw->knn_fb_n};
-        hipLaunchKernelGGL(k_tree_low, dim3(unsigned(g0)), dim3(256), 0, st, TL);
-        built = two ? 2 : 1;
-    }
-    int l = built + 1;
-    for (; l < L.levels && T.cap[l] > kTailCap; ++l)
-        hipLaunchKernelGGL(k_level_boxes, dim3(unsigned((T.cap[l] + 255) / 256)), dim3(256), 0, st, S.level[l]);
-    if (l < L.levels) {
-        const TreeTailArgs TT{at<FBox>(ws, L.boxes), T, int32_t(l)};
-        hipLaunchKernelGGL(k_tree_tail, dim3(1), dim3(256), 0, st, TT);
-    }
+    if (L.levels == 1) hipLaunchKernelGGL(k_bucket_boxes, dim3(g0), dim3(256), 0, st, S.bucket);
+    else hipLaunchKernelGGL(k_tree_low, dim3(g0), dim3(256), 0, st, S.low);
+    for (int l = S.built + 1; l < S.tail.l0; ++l)
+        hipLaunchKernelGGL(k_level_boxes, dim3(unsigned(cdiv(T.cap[l], 256))), dim3(256), 0, st, S.level[l]);
+    if (S.tail.l0 < L.levels) hipLaunchKernelGGL(k_tree_tail, dim3(1), dim3(256), 0, st, S.tail);
     prof_mark(GD_PROF_TREE, 1, st);
     KnnArgs& A = S.A;
 #ifdef GD_KNN_STATS
@@ -1042,8 +1064,8 @@ int launch_knn(const gd_problem* p, const gd_neighbors* nb, void* ws, const Layo
     return 0;
 }
 
-// The search of every run as stages of one interval: the bucket boxes, each
-// tree level over the runs that have it, then the queries: k > 33, or few
+// The search of every run as stages of one interval: the tree passes of
+// launch_knn over the runs that have them, then the queries: k > 33, or few
 // particles in all, one wavefront per query; k <= 33 (with tiles) the tile
 // search and its fallback wavefronts; otherwise the per-lane search over
 // every query.  Runs are grouped by periodicity and
@@ -1052,28 +1074,39 @@ void many_knn(ManyBuilder& B, const std::vector<ManyRun>& R)
 {
     const size_t nr = R.size();
     std::vector<KnnSetup> S(nr);
-    int maxl = 0;
+    int wide = 0;  // wide levels of the tallest tree, each a launch
     for (size_t r = 0; r < nr; ++r) {
         S[r] = knn_setup(&R[r].p, &R[r].nb, R[r].ws, R[r].L);
-        maxl = std::max(maxl, R[r].L.levels);
+        wide = std::max(wide, S[r].tail.l0 - (S[r].built + 1));
     }
     std::vector<int64_t> nb(nr);
     {
-        std::vector<BucketArgs> tab(nr);
+        std::vector<BucketArgs> flat(nr);
+        std::vector<TreeLowArgs> low(nr);
+        std::vector<TreeTailArgs> tail(nr);
+        std::vector<int64_t> nflat(nr), nlow(nr), ntail(nr);
         for (size_t r = 0; r < nr; ++r) {
-            tab[r] = S[r].bucket;
-            nb[r] = cdiv(S[r].T.cap[0], 256);
+            const bool one = R[r].L.levels == 1;
+            flat[r] = S[r].bucket;
+            low[r] = S[r].low;
+            tail[r] = S[r].tail;
+            nflat[r] = one ? cdiv(S[r].T.cap[0], 256) : 0;
+            nlow[r] = one ? 0 : cdiv(S[r].T.cap[0], 256);
+            ntail[r] = S[r].tail.l0 < R[r].L.levels ? 1 : 0;
         }
-        B.add<BucketBoxes>(tab, nb);
-    }
-    for (int l = 1; l < maxl; ++l) {
-        std::vector<LevelArgs> tab(nr);
-        for (size_t r = 0; r < nr; ++r) {
-            const bool has = l < R[r].L.levels;
-            tab[r] = has ? S[r].level[l] : LevelArgs{};
-            nb[r] = has ? cdiv(S[r].T.cap[l], 256) : 0;
+        B.add<BucketBoxes>(flat, nflat);
+        B.add<TreeLow>(low, nlow);
+        for (int w = 0; w < wide; ++w) {
+            std::vector<LevelArgs> tab(nr);
+            for (size_t r = 0; r < nr; ++r) {
+                const int l = S[r].built + 1 + w;
+                const bool has = l < S[r].tail.l0;
+                tab[r] = has ? S[r].level[l] : LevelArgs{};
+                nb[r] = has ? cdiv(S[r].T.cap[l], 256) : 0;
+            }
+            B.add<LevelBoxes>(tab, nb);
         }
-        B.add<LevelBoxes>(tab, nb);
+        B.add<TreeTail>(tail, ntail);
     }
     // query groups: (periodic, class) with class 0: k <= 33, 1: beyond
     for (int per = 0; per < 2; ++per) {

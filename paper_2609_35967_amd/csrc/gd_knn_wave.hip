@@ -456,8 +456,14 @@ struct KnnWave {
     }
 };
 
+// The search waits on memory and LDS, so the wavefronts in flight set its
+// pace: with the short list 4, 5, 6, 7 and 8 of them (8 spills 44 bytes) took
+// 608, 577, 543, 538 and 539 us per cadence step at 131,072 particles.
 template <bool PER, int NL>
-__global__ __launch_bounds__(kWave, NL == 192 ? 7 : 5) void k_knn_wave(WaveArgs W)
+constexpr int kWavesPerSimd<KnnWave<PER, NL>> = NL == 192 ? 7 : 5;
+
+template <bool PER, int NL>
+__global__ __launch_bounds__(kWave, (kWavesPerSimd<KnnWave<PER, NL>>)) void k_knn_wave(WaveArgs W)
 {
     KnnWave<PER, NL>::body(W, Blk{W.list ? int64_t(blockIdx.x) : xcd_block(), int64_t(gridDim.x)});
 }

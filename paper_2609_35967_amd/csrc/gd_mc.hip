@@ -484,7 +484,7 @@ __global__ void k_table_put(McArgs* dst, McArgs A)
 }
 
 template <int KP2, bool F32>
-__global__ __launch_bounds__(256) void k_mc_batch(char* table, int32_t nbox)
+__global__ __launch_bounds__(256, KP2 <= 32 ? 4 : 1) void k_mc_batch(char* table, int32_t nbox)
 {
     __shared__ int32_t s_pre[kMaxTableSlots];
     __shared__ int32_t s_total;
