@@ -61,13 +61,14 @@ struct alignas(256) WsHeader {
     int32_t knn_fb_n;            // neighbour search: queries the tile search handed back
     uint32_t red_done;           // controller sums: blocks done (wraps to 0 at the last)
     int32_t mc_n, mc_early_n;    // sampling: particles with events, from the list's start and from its end
+    int32_t mc_long_n;           // sampling: particles with very many
     int32_t mc_next;             // sampling: next chunk of them to take
 };
 
 // Workspace layout (byte offsets), identical on host and device.
 struct Layout {
     size_t hdr, keys0, keys1, vals0, vals1, hist, red, pos4, boxes,
-        snap, a, b, part, hint, mclist, stats, total;
+        snap, a, b, part, hint, mclist, mclong, stats, total;
     int64_t n;
     int32_t k;
     // radix sort: keys per thread, blocks, blocks per group of the digit
@@ -136,6 +137,7 @@ __host__ inline Layout make_layout(int64_t n, int32_t k)
     L.part = take(sizeof(double) * 8 * kNBin * kRedBlocks);
     L.hint = take(8 * nn);
     L.mclist = take(4 * nn);  // sampling: particles with an event
+    L.mclong = take(4 * nn);  // and those with very many
 #ifdef GD_KNN_STATS
     L.stats = take(32 * nn);
 #endif

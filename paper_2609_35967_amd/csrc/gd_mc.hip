@@ -42,14 +42,15 @@ struct McArgs {
     void* ws;
     unsigned long long* ev_counter;
     // the particles with an event, from the screen: entry e < n in list[e],
-    // and those that expect many (early_events or more; 0: none apart) in
-    // list[n - 1 - e], counted by list_n and early_n; next is the sampling's
-    // next chunk
+    // those that expect kEarlyEvents or more in list[n - 1 - e] and those
+    // that expect kLongEvents in long_list[e], counted by list_n, early_n and
+    // long_n; next is the sampling's next chunk
     int32_t* list;
+    int32_t* long_list;
     int32_t* list_n;
     int32_t* early_n;
+    int32_t* long_n;
     int32_t* next;
-    double early_events;
     int32_t screen_rounds;  // particles per thread of the screen
     int64_t n_all;  // length of the snapshot: neighbour indices lie in [0, n_all)
     const int64_t* interval_at;  // when set: the interval index (a spatial group's number in planning order)
@@ -70,6 +71,12 @@ constexpr int kSampleBlocks = 1024;  // blocks (4 wavefronts each) of the sampli
 // with 64 and 32, 3.50 with 32 and 32, 3.34 with 32 and 8, 3.31 with 16 and 8,
 // 3.39 with 8 and 16: later starts and larger chunks leave a longer tail.
 constexpr double kEarlyEvents = 16.0;
+// Expected events from which a particle has a wavefront to itself: a round of
+// 64 local boxes takes 90.4 ms with 1024 and 91.1 with 256, and took 109 with
+// none apart (95.7 with a lane, then a wavefront for every particle); the
+// warm 1M disk, whose chains are shorter, 3.33 ms with either and 3.28 with
+// none (the second loop costs the first a few spilled registers).
+constexpr double kLongEvents = 1024.0;
 constexpr int kChunk = 8;
 
 // Sampling runs in two passes.  The screen (one lane per particle, few
@@ -92,18 +99,18 @@ struct McScreen {
     static constexpr int kThreads = 256;
     static __device__ __forceinline__ void body(const Args& A, Blk B)
     {
-        __shared__ int32_t s_w[2][4], s_base[2];
+        __shared__ int32_t s_w[3][4], s_base[3];
         const int64_t i0 = B.id * int64_t(256 * A.screen_rounds) + threadIdx.x;
         const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
         const uint64_t below = (uint64_t(1) << lane) - 1;
         const uint32_t interval = mc_interval(A);
         const double dt_exe = A.iv->dt_exe;
-        uint64_t bl[kScreenRounds], be[kScreenRounds];  // lanes listed, at the start and at the end
-        int32_t nl = 0, ne = 0;
+        uint64_t b[kScreenRounds][3];  // lanes listed: few, many, very many events
+        int32_t cnt[3] = {0, 0, 0};
 #pragma unroll
         for (int r = 0; r < kScreenRounds; ++r) {
             const int64_t i = i0 + r * 256;
-            bool ev = false, early = false;
+            int cls = -1;
             if (r < A.screen_rounds && i < A.P.n) {
                 const int c = A.cnt[i];
                 const double m = A.m[i];
@@ -111,44 +118,52 @@ struct McScreen {
                 if (c > 1 && li > 0.0) {
                     double u[4];
                     event_uniforms(A.seed, A.id[i], interval, 0u, u);
-                    ev = !(-log(u[0]) / li > dt_exe);
-                    early = ev && A.early_events > 0.0 && li * dt_exe >= A.early_events;
+                    const double x = li * dt_exe;  // expected events
+                    if (!(-log(u[0]) / li > dt_exe)) cls = x >= kLongEvents ? 2 : (x >= kEarlyEvents ? 1 : 0);
                 }
-                if (!ev) {
+                if (cls < 0) {
                     A.m_out[i] = m;
                     if (A.n_events) A.n_events[i] = 0;
                 }
                 if (A.log)
                     for (int f = 0; f < A.log_cap; ++f) A.log[i * A.log_cap + f] = -1;
             }
-            bl[r] = __ballot(ev && !early);
-            be[r] = __ballot(early);
-            nl += int32_t(__popcll(bl[r]));
-            ne += int32_t(__popcll(be[r]));
+#pragma unroll
+            for (int q = 0; q < 3; ++q) {
+                b[r][q] = __ballot(cls == q);
+                cnt[q] += int32_t(__popcll(b[r][q]));
+            }
         }
         if (lane == 0) {
-            s_w[0][wv] = nl;
-            s_w[1][wv] = ne;
+#pragma unroll
+            for (int q = 0; q < 3; ++q) s_w[q][wv] = cnt[q];
         }
         __syncthreads();
-        if (threadIdx.x < 2) {
+        if (threadIdx.x < 3) {
             const int32_t* w = s_w[threadIdx.x];
             const int32_t tot = w[0] + w[1] + w[2] + w[3];
-            s_base[threadIdx.x] = tot ? atomicAdd(threadIdx.x == 0 ? A.list_n : A.early_n, tot) : 0;
+            int32_t* to = threadIdx.x == 0 ? A.list_n : (threadIdx.x == 1 ? A.early_n : A.long_n);
+            s_base[threadIdx.x] = tot ? atomicAdd(to, tot) : 0;
         }
         __syncthreads();
-        int32_t al = s_base[0], ae = s_base[1];
-        for (int w = 0; w < wv; ++w) {
-            al += s_w[0][w];
-            ae += s_w[1][w];
+        int32_t at[3];
+#pragma unroll
+        for (int q = 0; q < 3; ++q) {
+            at[q] = s_base[q];
+            for (int w = 0; w < wv; ++w) at[q] += s_w[q][w];
         }
 #pragma unroll
         for (int r = 0; r < kScreenRounds; ++r) {
             const int32_t i = int32_t(i0 + r * 256);
-            if ((bl[r] >> lane) & 1u) A.list[al + int32_t(__popcll(bl[r] & below))] = i;
-            if ((be[r] >> lane) & 1u) A.list[A.P.n - 1 - (ae + int32_t(__popcll(be[r] & below)))] = i;
-            al += int32_t(__popcll(bl[r]));
-            ae += int32_t(__popcll(be[r]));
+#pragma unroll
+            for (int q = 0; q < 3; ++q) {
+                if ((b[r][q] >> lane) & 1u) {
+                    const int32_t e = at[q] + int32_t(__popcll(b[r][q] & below));
+                    if (q == 2) A.long_list[e] = i;
+                    else A.list[q == 0 ? e : A.P.n - 1 - e] = i;
+                }
+                at[q] += int32_t(__popcll(b[r][q]));
+            }
         }
     }
 };
@@ -411,31 +426,173 @@ __device__ inline int run_chunk(const McArgs& A, int32_t lo, int32_t hi, bool fa
     return total;
 }
 
-// Chunks of a run's list: first its far end (two particles a chunk: the long
-// ones start at once, spread over the wavefronts), then the rest, up to
-// kChunk a chunk while that leaves every wavefront several.
-struct Chunks {
-    int32_t n0, n1, c, k0, k;  // particles of each part, chunk size, chunks of the first part, all
+// The interval of particle i in a whole wavefront, with nothing else in its
+// loop: the latency of the longest chain's events sets how long the pass
+// takes where one particle has tens of thousands.
+template <int KP2, bool F32>
+__device__ inline int run_one(const McArgs& A, int32_t i, int lane)
+{
+    constexpr int R = KP2 > kWave ? KP2 / kWave : 1;
+    constexpr int W = KP2 < kWave ? KP2 : kWave;  // lanes holding slots
+    const bool phys = A.P.kernel == GD_KERNEL_PHYSICAL;
+    const double dt_exe = A.iv->dt_exe;
+    const uint32_t interval = mc_interval(A);
+    int e = 0;
+    double t = 0.0, m = A.m[i];
+    const int64_t k = A.P.k;
+    const int c = A.cnt[i];
+    const uint32_t pid = A.id[i];
+    QCtx q{};
+    QCtxF qf{};
+    query_ctx(A.P, A.x[i], A.y[i], A.z[i], A.dmax[i], q);
+    if (F32) query_ctx_f32(A.P, q, qf);
+    Nb nb[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        const int s = r * kWave + lane;
+        const bool mine = s < c && lane < W;
+        int j = mine ? A.nbr[i * k + s] : 0;
+        if (mine && (j < 0 || j >= A.n_all)) set_status(A.ws, GD_DEV_INTERNAL);
+        if (j < 0 || j >= A.n_all) j = 0;
+        const double4 sn = A.m_all ? make_double4(A.m_all[j], 0.0, 0.0, 0.0) : A.snap[j];
+        if (F32) {
+            nb[r].mj = sn.x;
+            nb[r].sj = phys ? sn.y : 0.0;
+            nb[r].Nj = phys ? sn.z : 0.0;
+        } else {
+            nb_terms<true>(A.P, q, sn.x, phys ? sn.y : 0.0, phys ? sn.z : 0.0, sn.w, nb[r]);
+        }
+    }
+    uint32_t e0 = 0;
+    Draws d;
+    draw_events(A, pid, interval, e0, lane, d);
+    for (;;) {
+        if (uint32_t(e) - e0 >= uint32_t(kWave)) {
+            e0 = uint32_t(e);
+            draw_events(A, pid, interval, e0, lane, d);
+        }
+        const int L = int(uint32_t(e) - e0);
+        const double lw = readlane_d(d.lw, L), up = readlane_d(d.up, L), uc = readlane_d(d.uc, L);
+        // the pairs at the current mass, each with its outcome (a fragmentation
+        // outcome does not depend on the partner and is made after the selection)
+        double si = 0.0;
+        Own w{};
+        if (phys) si = grain_size(A.P, m);
+        if (!F32) own_terms(A.P, q, m, si, false, w);
+        const float Stf = F32 && phys ? qf.stfac * float(si) : 0.0f;
+        double pre[R], mnew[R];
+        int code[R];
+        double carry = 0.0;
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            int type;
+            double r0, lam, Ng;
+            if (F32) {
+                PairF of;
+                pair_eval_f32(A.P, qf, m, 1.0 / m, float(si), Stf, nb[r].mj, float(nb[r].sj), nb[r].Nj, of);
+                type = of.type;
+                r0 = of.r0;
+                lam = double(of.r0) + double(of.r1);  // the channel choice's total
+                Ng = of.Ng;
+                pre[r] = double(of.lam_star);         // the prefix adds the float rate
+            } else {
+                Pair o;
+                pair_core<true>(A.P, q, w, nb[r], o);
+                type = o.type;
+                r0 = o.r0;
+                lam = o.lam_star;
+                Ng = o.Ng;
+                pre[r] = o.lam_star;
+            }
+            const int ch = (type == kErosion && !(r0 > uc * lam)) ? 1 : 0;
+            const double mj = nb[r].mj;
+            mnew[r] = type == kStick ? m + Ng * mj : (ch == 0 ? m - Ng * mj : mj);
+            code[r] = (ch << 16) | (type << 24);
+            const double x = group_scan<1>((r * kWave + lane < c && lane < W) ? pre[r] : 0.0);
+            pre[r] = carry + x;
+            carry = carry + readlane_d(x, kWave - 1);
+        }
+        const double li = carry;
+        if (!(li > 0.0)) break;
+        if (e >= kEventCap) {
+            if (lane == 0) set_status(A.ws, GD_DEV_EVENT_CAP);
+            break;
+        }
+        const double dtw = lw / li;
+        if (dtw > dt_exe - t) break;
+        t = t + dtw;
+        const double target = up * li;
+        // the first slot below c - 1 whose prefix exceeds the target, else c - 1
+        int sel = c - 1;
+#pragma unroll
+        for (int r = R - 1; r >= 0; --r) {
+            const uint64_t hit = __ballot(r * kWave + lane < c - 1 && pre[r] > target);
+            if (hit) sel = r * kWave + int(__ffsll((unsigned long long)hit)) - 1;
+        }
+        const int sl = sel & (kWave - 1), sr = sel / kWave;
+        int cd = 0;
+        double mn = 0.0;
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            if (r == sr) {  // uniform: sel is the same in every lane
+                cd = __builtin_amdgcn_readlane(code[r], sl);
+                mn = readlane_d(mnew[r], sl);
+            }
+        }
+        if ((cd >> 24) == kFrag) {
+            const double uf = readlane_d(d.uf, L);
+            const double a = sqrt(A.P.s_min);
+            const double wf = a + uf * (sqrt(si) - a);
+            const double sz = wf * wf;
+            mn = div_nr(kPi * A.P.rho_s * sz * sz * sz, 6.0);
+        }
+        if (A.log && lane == 0) {
+            if (e < A.log_cap) A.log[i * A.log_cap + e] = sel | cd;
+            else set_status(A.ws, GD_DEV_LOG_OVERFLOW);
+        }
+        ++e;
+        // (an unchanged mass recomputes the same rates: no branch around them)
+        m = mn;
+    }
+    if (lane == 0) {
+        A.m_out[i] = m;
+        if (A.n_events) A.n_events[i] = e;
+    }
+    return e;
+}
 
-    __device__ void set(int32_t early, int32_t rest, int32_t waves)
+// Chunks of a run's lists: first the long chains, one each; then the list's
+// far end, two particles a chunk (they start at once, spread over the
+// wavefronts), then the rest, up to kChunk a chunk while that leaves every
+// wavefront several.
+struct Chunks {
+    int32_t nl, n0, n1, c, k0, k;  // particles of each part, chunk size, chunks before the last part, all
+
+    __device__ void set(const McArgs& A, int32_t waves)
     {
-        n0 = early;
-        n1 = rest;
-        c = rest / (4 * waves);
+        nl = *A.long_n;
+        n0 = *A.early_n;
+        n1 = *A.list_n;
+        c = n1 / (4 * waves);
         c = c < 2 ? 2 : (c > kChunk ? kChunk : c);
-        k0 = (n0 + 1) / 2;
+        k0 = nl + (n0 + 1) / 2;
         k = k0 + (n1 + c - 1) / c;
     }
     template <int KP2, bool F32>
     __device__ int run(const McArgs& A, int32_t x, int lane) const
     {
-        const bool far = x < k0;
-        const int32_t lo = far ? 2 * x : (x - k0) * c, hi = far ? lo + 2 : lo + c, n = far ? n0 : n1;
         // the long ones set the pass's length: their wavefronts issue first
         // (3.66 against 3.70 ms per interval of the warm 1M disk)
-        if (far) __builtin_amdgcn_s_setprio(3);
-        const int ev = run_chunk<KP2, F32>(A, lo, hi < n ? hi : n, far, lane);
-        if (far) __builtin_amdgcn_s_setprio(0);
+        if (x < k0) __builtin_amdgcn_s_setprio(3);
+        int ev;
+        if (x < nl) {
+            ev = run_one<KP2, F32>(A, __builtin_amdgcn_readfirstlane(A.long_list[x]), lane);
+        } else {
+            const bool far = x < k0;
+            const int32_t lo = far ? 2 * (x - nl) : (x - k0) * c, hi = far ? lo + 2 : lo + c, n = far ? n0 : n1;
+            ev = run_chunk<KP2, F32>(A, lo, hi < n ? hi : n, far, lane);
+        }
+        if (x < k0) __builtin_amdgcn_s_setprio(0);
         return ev;
     }
 };
@@ -446,7 +603,7 @@ __global__ __launch_bounds__(256, KP2 <= 32 ? 4 : 1) void k_mc(McArgs A)
     const int lane = threadIdx.x & 63;
     const int32_t nw = int32_t(gridDim.x * (blockDim.x / kWave));
     Chunks C;
-    C.set(*A.early_n, *A.list_n, nw);
+    C.set(A, nw);
     // wavefront w takes chunk w first, then chunks nw, nw + 1, ... from the
     // counter (which is left alone when there are no more than nw); one add of
     // the events per workgroup: adds to one address wait 12 ns each for the
@@ -473,8 +630,7 @@ __global__ __launch_bounds__(256, KP2 <= 32 ? 4 : 1) void k_mc(McArgs A)
 // Many runs: a table in device memory holds, per slot, the sampling arguments
 // of one run (written by its deferred call), after a 256-byte header whose
 // first word counts the chunks taken.  One launch runs the lists of every
-// slot: the global chunk g is the slot's own chunk g - (chunks of the slots
-// before it).
+// slot, all slots' long chains first.
 constexpr size_t kTableHeader = 256;
 constexpr int kMaxTableSlots = 4096;
 
@@ -484,47 +640,52 @@ __global__ void k_table_put(McArgs* dst, McArgs A)
 }
 
 template <int KP2, bool F32>
-__global__ __launch_bounds__(256, KP2 <= 32 ? 4 : 1) void k_mc_batch(char* table, int32_t nbox)
+__global__ __launch_bounds__(256) void k_mc_batch(char* table, int32_t nbox)
 {
-    __shared__ int32_t s_pre[kMaxTableSlots];
-    __shared__ int32_t s_total;
+    // per slot, the chunks of the slots before it: of long chains and far
+    // ends [0], which go first in every slot, and of the rest [1]
+    __shared__ int32_t s_pre[2][kMaxTableSlots];
+    __shared__ int32_t s_total[2];
     const McArgs* T = reinterpret_cast<const McArgs*>(table + kTableHeader);
     int32_t* counter = reinterpret_cast<int32_t*>(table);
     const int t = threadIdx.x, lane = t & 63;
     const int32_t nw = int32_t(gridDim.x * (blockDim.x / kWave));
-    auto chunks = [&](int b) {
+    for (int b = t; b < nbox; b += blockDim.x) {
+        const bool on = !T[b].active || *T[b].active;
         Chunks C;
-        if (T[b].active && !*T[b].active) C.set(0, 0, nw);
-        else C.set(*T[b].early_n, *T[b].list_n, nw);
-        return C;
-    };
-    for (int b = t; b < nbox; b += blockDim.x) s_pre[b] = chunks(b).k;
+        C.set(T[b], nw);
+        s_pre[0][b] = on ? C.k0 : 0;
+        s_pre[1][b] = on ? C.k - C.k0 : 0;
+    }
     __syncthreads();
-    if (t < kWave) {  // exclusive prefix of the slots' counts, 64 at a time
+    if (t < 2 * kWave) {  // exclusive prefixes of the slots' counts, 64 at a time, a wavefront each
+        int32_t* pre = s_pre[t / kWave];
         int32_t carry = 0;
         for (int c0 = 0; c0 < nbox; c0 += kWave) {
-            const int32_t v = c0 + t < nbox ? s_pre[c0 + t] : 0;
+            const int32_t v = c0 + lane < nbox ? pre[c0 + lane] : 0;
             int32_t x = v;
 #pragma unroll
             for (int o = 1; o < kWave; o <<= 1) {
                 const int32_t y = __shfl_up(x, o, kWave);
-                if (t >= o) x += y;
+                if (lane >= o) x += y;
             }
-            if (c0 + t < nbox) s_pre[c0 + t] = carry + x - v;
+            if (c0 + lane < nbox) pre[c0 + lane] = carry + x - v;
             carry += __shfl(x, kWave - 1, kWave);
         }
-        if (t == 0) s_total = carry;
+        if (lane == 0) s_total[t / kWave] = carry;
     }
     __syncthreads();
-    const int32_t total = s_total;
+    const int32_t total0 = s_total[0], total = total0 + s_total[1];
     int32_t g = __builtin_amdgcn_readfirstlane(int32_t(blockIdx.x * (blockDim.x / kWave) + t / kWave));
-    for (;;) {
-        if (g >= total) break;
-        // the last slot whose prefix is <= g (slots with no entries share a prefix)
+    while (g < total) {
+        const bool first = g < total0;
+        const int32_t* pre = s_pre[first ? 0 : 1];
+        const int32_t gg = first ? g : g - total0;
+        // the last slot whose prefix is <= gg (slots with no chunks share a prefix)
         int lo = 0, hi = nbox - 1;
         while (lo < hi) {
             const int mid = (lo + hi + 1) >> 1;
-            if (s_pre[mid] <= g) lo = mid;
+            if (pre[mid] <= gg) lo = mid;
             else hi = mid - 1;
         }
         lo = __builtin_amdgcn_readfirstlane(lo);
@@ -532,7 +693,9 @@ __global__ __launch_bounds__(256, KP2 <= 32 ? 4 : 1) void k_mc_batch(char* table
         if (A.P.k > KP2 || (A.P.rates_fp32 != 0) != F32) {
             if (lane == 0) set_status(A.ws, GD_DEV_INTERNAL);
         } else {
-            const int ev = chunks(lo).template run<KP2, F32>(A, g - s_pre[lo], lane);
+            Chunks C;
+            C.set(A, nw);
+            const int ev = C.run<KP2, F32>(A, __builtin_amdgcn_readfirstlane(gg - pre[lo] + (first ? 0 : C.k0)), lane);
             if (lane == 0 && ev) atomicAdd(A.ev_counter, (unsigned long long)ev);
         }
         int32_t next = 0;
@@ -592,10 +755,11 @@ static McArgs mc_args(const gd_problem* p, const gd_particles* s, const gd_neigh
     A.ws = ws;
     A.ev_counter = reinterpret_cast<unsigned long long*>(&h->scratch[0]);
     A.list = at<int32_t>(ws, L.mclist);
+    A.long_list = at<int32_t>(ws, L.mclong);
     A.list_n = &h->mc_n;
     A.early_n = &h->mc_early_n;
+    A.long_n = &h->mc_long_n;
     A.next = &h->mc_next;
-    A.early_events = kEarlyEvents;
     A.screen_rounds = screen_rounds(p->n);
     A.n_all = p->n;
     return A;
@@ -631,7 +795,7 @@ int launch_sample(const gd_problem* p, const gd_particles* s, const gd_neighbors
     prof_mark(GD_PROF_MC, 0, st);
     // (the list's counts are cleared by the plan and by every audit; a run of
     // the table form may sample again before its audit)
-    if (table) launch_fill_i32(A.list_n, 3, 0, st);
+    if (table) launch_fill_i32(A.list_n, 4, 0, st);
     if (p->n > 0) launch_screen(A, st);
     if (table) {
         // the list is left to the launch over the whole table

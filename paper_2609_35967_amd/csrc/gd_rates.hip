@@ -767,6 +767,7 @@ __device__ __forceinline__ void Reduce<MODE>::body(const Args& A, Blk B)
     if (lane == 0) {
         h->mc_n = 0;
         h->mc_early_n = 0;
+        h->mc_long_n = 0;
         h->mc_next = 0;
     }
 }
