@@ -11,7 +11,11 @@
 // rounding of the single-precision box tests, so a box is never pruned while
 // it holds a point within the search radius.
 //
-// Query: one lane per particle, stackless walk that keeps, per level, the
+// Queries go to shared tiles (gd_knn_tile.hip) or a wavefront each
+// (gd_knn_wave.hip), as use_tiles() below picks; the many-run form can ask
+// for the per-lane walk of this file instead.
+//
+// Per-lane query: one lane per particle, stackless walk that keeps, per level, the
 // 8-bit mask of children still to visit (all levels in one 64-bit register).
 // It starts at the level-1 ancestor of the query's bucket and climbs one
 // ancestor at a time, so the space near the query is seen first.  Each
