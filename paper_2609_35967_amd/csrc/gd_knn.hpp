@@ -160,6 +160,14 @@ __device__ inline uint32_t child_mask(const KnnArgs& A, const FBox (&b)[kFan], c
     return m;
 }
 
+// nodes of `level` that hold active slots (node i covers the 4 8^level slots
+// from 4 8^level i on, and the active slots are [0, na))
+__device__ inline int live_nodes(int na, int level)
+{
+    const int sh = 2 + 3 * level;
+    return int((int64_t(na) + (int64_t(1) << sh) - 1) >> sh);
+}
+
 // mask of the children of node `idx` at `level` (>= 1) that hold active
 // slots: child c covers the 4 8^(level-1) slots from (8 idx + c) 4 8^(level-1)
 // on, and the active slots are [0, na).  Children without any (the padding

@@ -353,6 +353,7 @@ __device__ __forceinline__ void KnnTile<PER>::body(const Args& TA, Blk B)
         constexpr int kU = 4;
         while (lv >= 1 && wave_ok) {
             int nn = 0;  // next frontier written
+            const int nlive = live_nodes(na, lv - 1);  // the children that hold active slots
             for (int f0 = 0; f0 < nf && wave_ok; f0 += kU * kFan) {
                 FBox bx[kU];
                 uint32_t pm[kU];
@@ -370,10 +371,10 @@ __device__ __forceinline__ void KnnTile<PER>::body(const Args& TA, Blk B)
 #pragma unroll
                 for (int u = 0; u < kU; ++u) {
                     const int fi = f0 + u * kFan + (lane >> 3), c = lane & 7;
-                    const int idx = int(fe[u] & 0xFFFFFFu);
-                    const bool live = fi < nf && ((live_children(na, lv, idx) >> c) & 1u);
+                    const int ch = int(fe[u] & 0xFFFFFFu) * kFan + c;
+                    const bool live = fi < nf && ch < nlive;
                     pm[u] = live ? fe[u] >> 24 : 0u;
-                    child[u] = live ? idx * kFan + c : 0;
+                    child[u] = live ? ch : 0;
                 }
 #pragma unroll
                 for (int u = 0; u < kU; ++u) bx[u] = A.boxes[level_off(A.T, lv - 1) + child[u]];

@@ -374,16 +374,17 @@ __device__ __forceinline__ void knn_wave_query(const KnnArgs& A, int q, WaveLds<
             const int lv = node >> 27, idx = node & ((1 << 27) - 1);
             bool pass = false;
             bool leaf = false;
-            if (my < nt && ((live_children(na, lv, idx) >> c) & 1u)) {
-                const FBox bx = A.boxes[level_off(A.T, lv - 1) + idx * kFan + c];
+            const int child = idx * kFan + c;
+            if (my < nt && (child << (3 * lv - 1)) < na) {  // the child holds active slots (its first is 4 8^(lv-1) child < 2^31)
+                const FBox bx = A.boxes[level_off(A.T, lv - 1) + child];
                 pass = box2f<PER>(A, qf, bx) <= R2f;
                 leaf = lv == 1;
             }
             const uint64_t bin = __ballot(pass && !leaf), bleaf = __ballot(pass && leaf);
             const int ni = int(__popcll(bin));
             if (pass && !leaf)
-                L.stack[sp + ni - 1 - int(__popcll(bin & lanes_below(lane)))] = ((lv - 1) << 27) | (idx * kFan + c);
-            if (pass && leaf) L.buf[nbuf + int(__popcll(bleaf & lanes_below(lane)))] = idx * kFan + c;
+                L.stack[sp + ni - 1 - int(__popcll(bin & lanes_below(lane)))] = ((lv - 1) << 27) | child;
+            if (pass && leaf) L.buf[nbuf + int(__popcll(bleaf & lanes_below(lane)))] = child;
             sp += ni;
             nbuf += int(__popcll(bleaf));
             __syncthreads();
