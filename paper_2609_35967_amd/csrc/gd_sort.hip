@@ -259,6 +259,11 @@ __device__ inline uint32_t block_scan_excl_256(uint32_t v, uint32_t* s_w)
 // its digits first, the four counts become places, and then every round of
 // 64 keys takes its places from the wavefront's own row, with no barrier
 // (four barriers a round, shared rows: 12.7 us a pass on 10,000 keys).
+// With kStageRounds keys a thread or more the tile goes to LDS in its new
+// order first and from there out, so that the keys of a digit are stored side
+// by side.
+constexpr int kStageRounds = 4;
+
 struct RadixScatter {
     using Args = RadixArgs;
     static constexpr int kThreads = 256;
@@ -270,7 +275,9 @@ __device__ __forceinline__ void RadixScatter::body(const Args& A, Blk B)
     const int64_t n = A.n;
     const int shift = A.shift, rounds = A.rounds;
     __shared__ uint32_t at[4][256];  // per wavefront: counts, then the next place of each digit
-    __shared__ uint32_t s_w[4];
+    __shared__ uint32_t s_w[4], s_w2[4];
+    __shared__ uint32_t s_key[256 * kSortRounds], s_val[256 * kSortRounds], s_delta[256];
+    const bool stage = rounds >= kStageRounds;
     const int t = threadIdx.x, lane = t & 63, w = t >> 6;
     // the tile's keys and values are loaded first, all in flight together
     const int64_t base = B.id * int64_t(256 * rounds) + int64_t(w) * (64 * rounds) + lane;
@@ -283,16 +290,26 @@ __device__ __forceinline__ void RadixScatter::body(const Args& A, Blk B)
     }
     // digit t: the keys of it in all blocks, and in the blocks before this one
     const int grp = int(B.id / A.sup), ngrp = (A.nblk + A.sup - 1) / A.sup;
+    // (kRows rows in flight at a time, the missing ones read as row 0 and dropped)
+    constexpr int kRows = 16;
     uint32_t total = 0, before = 0;
-#pragma unroll 8
-    for (int g = 0; g < ngrp; ++g) {
-        const uint32_t c = A.sums[g * 256 + t];
-        total += c;
-        before += g < grp ? c : 0u;
+    for (int g0 = 0; g0 < ngrp; g0 += kRows) {
+        uint32_t c[kRows];
+#pragma unroll
+        for (int u = 0; u < kRows; ++u) c[u] = A.sums[(g0 + u < ngrp ? g0 + u : 0) * 256 + t];
+#pragma unroll
+        for (int u = 0; u < kRows; ++u) {
+            total += g0 + u < ngrp ? c[u] : 0u;
+            before += g0 + u < grp ? c[u] : 0u;
+        }
     }
-    const int b0 = grp * A.sup;
-#pragma unroll 8
-    for (int b = b0; b < int(B.id); ++b) before += A.hist[b * 256 + t];
+    for (int b0 = grp * A.sup; b0 < int(B.id); b0 += kRows) {
+        uint32_t c[kRows];
+#pragma unroll
+        for (int u = 0; u < kRows; ++u) c[u] = A.hist[(b0 + u < int(B.id) ? b0 + u : 0) * 256 + t];
+#pragma unroll
+        for (int u = 0; u < kRows; ++u) before += b0 + u < int(B.id) ? c[u] : 0u;
+    }
 #pragma unroll
     for (int ww = 0; ww < 4; ++ww) at[ww][t] = 0;
     const uint32_t goff = block_scan_excl_256(total, s_w) + before;  // (holds a barrier)
@@ -302,6 +319,11 @@ __device__ __forceinline__ void RadixScatter::body(const Args& A, Blk B)
     __syncthreads();
     {
         uint32_t p = goff;
+        if (stage) {  // places within the tile; digit t's lie s_delta[t] below their global ones
+            const uint32_t c = at[0][t] + at[1][t] + at[2][t] + at[3][t];
+            p = block_scan_excl_256(c, s_w2);
+            s_delta[t] = goff - p;
+        }
 #pragma unroll
         for (int ww = 0; ww < 4; ++ww) {
             const uint32_t c = at[ww][t];
@@ -326,13 +348,29 @@ __device__ __forceinline__ void RadixScatter::body(const Args& A, Blk B)
         const uint32_t rank = uint32_t(__popcll(peers & lt));
         if (valid) {
             const uint32_t off = at[w][dig] + rank;
-            A.kout[off] = kr[r];
-            A.vout[off] = vr[r];
+            if (stage) {
+                s_key[off] = kr[r];
+                s_val[off] = vr[r];
+            } else {
+                A.kout[off] = kr[r];
+                A.vout[off] = vr[r];
+            }
             // (the wavefront's LDS operations run in order: every peer has
             // read its place when the last of them moves it on)
             if (rank + 1 == uint32_t(__popcll(peers))) at[w][dig] = off + 1;
         }
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    }
+    if (!stage) return;
+    __syncthreads();
+    const int64_t left = n - B.id * int64_t(256 * rounds);
+    const int m = left < 256 * rounds ? int(left) : 256 * rounds;
+#pragma unroll 4
+    for (int e = t; e < m; e += 256) {
+        const uint32_t key = s_key[e];
+        const uint32_t to = uint32_t(e) + s_delta[(key >> shift) & 0xFFu];
+        A.kout[to] = key;
+        A.vout[to] = s_val[e];
     }
 }
 
