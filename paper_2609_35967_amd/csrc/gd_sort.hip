@@ -258,10 +258,13 @@ __device__ inline uint32_t block_scan_excl_256(uint32_t v, uint32_t* s_w)
 // The wavefronts rank their quarters of the tile on their own: each counts
 // its digits first, the four counts become places, and then every round of
 // 64 keys takes its places from the wavefront's own row, with no barrier
-// (four barriers a round, shared rows: 12.7 us a pass on 10,000 keys).
+// (four barriers a round, shared rows: 12.7 us a pass on 10,007 keys, 7.3 so;
+// 5.1 with the count rows read kRows at a time).
 // With kStageRounds keys a thread or more the tile goes to LDS in its new
 // order first and from there out, so that the keys of a digit are stored side
-// by side.
+// by side: 16.5 -> 13.0 us a pass on 1M keys (16 a thread), 10.0 -> 9.1 on
+// 300,007; with fewer a digit has a run of one to three keys, and the barriers
+// cost what the stores save.
 constexpr int kStageRounds = 4;
 
 struct RadixScatter {
