@@ -59,6 +59,7 @@ struct alignas(256) WsHeader {
     double scratch[16];
     int32_t xq[4][8];            // per-die work queues of the gather-heavy kernels
     int32_t knn_fb_n;            // neighbour search: queries the tile search handed back
+    int32_t knn_hints;           // 1: previous distances were found (see Permute), the tile search has a start
     uint32_t red_done;           // controller sums: blocks done (wraps to 0 at the last)
     int32_t mc_n, mc_early_n;    // sampling: particles with events, from the list's start and from its end
     int32_t mc_long_n;           // sampling: particles with very many

@@ -19,6 +19,7 @@ struct PermuteArgs {
     double4* pos4;
     const double* hint_src;  // previous neighbour distance per input slot, or null
     double* hint_dst;        // into Morton order (0 when absent)
+    int32_t* hints;          // set to 1 when a sampled particle has one
 };
 
 DevProblem to_dev(const gd_problem* p);

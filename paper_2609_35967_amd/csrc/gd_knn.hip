@@ -57,10 +57,10 @@ constexpr int kDMax = 3;  // levels of the nested bin chain
 constexpr int kRescales = 4;  // restarts of pass A on a finer distance scale
 constexpr int kQBlock = 128;
 // one-wavefront workgroups for the handed-back queries: most leave at once
-// when few were (a million-particle interval takes as long with 7168, as many
-// as are resident), and a run's first search, all of it handed back, balances
-// over them (300,007 particles: 0.86 ms against 0.98 with 7168)
-constexpr int kFallbackBlocks = 32768;
+// when few were (a million-particle interval takes 1.372, 1.369 and 1.376 ms
+// with 32768, 65536 and 131072), and a run's first search, all of it taken
+// here, balances over them (300,007 particles: 742, 728 and 724 us)
+constexpr int kFallbackBlocks = 65536;
 constexpr int kQueue = 4;  // level-1 bucket masks a walk keeps queued
 static_assert(kQueue >= 1 && kQueue <= 4, "the queue keeps its masks in the bytes of one word");
 
@@ -1058,8 +1058,8 @@ int launch_knn(const gd_problem* p, const gd_neighbors* nb, void* ws, const Layo
         return 0;
     }
     // shared candidate tiles first; the queries they cannot complete (usually
-    // well under 1%: sparse regions with many candidates; all of them in a
-    // run's first search) take a wavefront each
+    // well under 1%: sparse regions with many candidates) take a wavefront
+    // each, and every query does in a run's first search
     int32_t* fb = at<int32_t>(ws, L.vals1);  // n entries, free after the sort
     if (L.levels == 1) launch_fill_i32(&hw->knn_fb_n, 1, 0, st);  // (else cleared by the tree's first pass)
     launch_knn_tile(A, per, fb, &hw->knn_fb_n, st);

@@ -157,6 +157,8 @@ template <bool PER>
 __device__ __forceinline__ void KnnTile<PER>::body(const Args& TA, Blk B)
 {
     const KnnArgs& A = TA.A;
+    // a run's first search: the wavefronts after this launch take every query
+    if (!A.h->knn_hints) return;
     __shared__ TileLds<PER> L;
     const int lane = threadIdx.x;
     const int64_t item = xcd_item(B.id, B.n);

@@ -443,13 +443,16 @@ struct KnnWave {
         __shared__ WaveLds<NL> L;
         const int lane = threadIdx.x;
         if (W.list) {
-            // each die's workgroups take a contiguous range of the list, which
-            // is in Morton order where it is long (a run's first search)
-            const int32_t nl = *W.count;
+            // each die's workgroups take a contiguous range of the list, or,
+            // with no previous distances, of all queries (the tile search
+            // handed them back in 60 us and less in order: a first search of
+            // 300,007 took 806 us, so 728)
+            const bool all = !W.A.h->knn_hints;
+            const int32_t nl = all ? int32_t(W.A.n) : *W.count;
             const int x = int(B.id % kXcd);
             const int32_t hi = xcd_range_lo(x + 1, nl), step = int32_t((B.n - x + kXcd - 1) / kXcd);
             for (int32_t t = xcd_range_lo(x, nl) + int32_t(B.id / kXcd); t < hi; t += step)
-                knn_wave_query<PER, NL>(W.A, W.list[t], L, lane);
+                knn_wave_query<PER, NL>(W.A, all ? t : W.list[t], L, lane);
         } else {
             const int64_t q = B.id;
             if (q < W.A.n) knn_wave_query<PER, NL>(W.A, int(q), L, lane);

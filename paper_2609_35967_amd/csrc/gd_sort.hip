@@ -115,6 +115,7 @@ __device__ __forceinline__ void Bbox::body(const Args& A, Blk B)
     }
     h->inv = ext > 0.0 ? 1024.0 / ext : 0.0;
     h->n_active = int32_t(v[6]);
+    h->knn_hints = 0;
     if (A.na_out) *A.na_out = int32_t(v[6]);
 }
 
@@ -413,6 +414,9 @@ __device__ __forceinline__ void Permute::body(const Args& A, Blk B)
     A.id_dst[i] = id;
     A.pos4[i] = make_double4(v[0], v[1], v[2], 0.0);  // x, y, z are the first three arrays
     A.hint_dst[i] = hint;
+    // one block in 16 tells the search whether there are previous distances
+    // (it picks the faster of two exact searches, so a sample will do)
+    if ((B.id & 15) == 0 && hint > 0.0) *A.hints = 1;
 }
 
 __global__ void k_fill_i32(int32_t* __restrict__ a, int64_t n, int32_t v)
@@ -484,6 +488,7 @@ static SortArgs sort_args(const gd_problem* p, const gd_particles* in, gd_partic
     A.pos4 = at<double4>(ws, L.pos4);
     A.hint_src = hint;
     A.hint_dst = at<double>(ws, L.hint);
+    A.hints = &h->knn_hints;
     return S;
 }
 

@@ -80,3 +80,22 @@ def test_tiles(name, n, k, hint):
     assert np.array_equal(eng.nbr.cpu().numpy()[q], nbr)
     np.testing.assert_allclose(eng.dmax.cpu().numpy()[q], dmax, rtol=1e-15)
     assert eng.status() & 0x21 == 0
+
+
+@pytest.mark.parametrize("kept", ["one in 50", "blocks 1 to 15 of 16", "block 0"])
+@pytest.mark.parametrize("name, n", [("disk3d", 163_841), ("additive_col", 400_003)])
+def test_some_previous_distances(name, n, kept):
+    """Previous distances for a part of the particles only: the search that a
+    sample of them picks finds the same lists as with all of them."""
+    params, st = workloads.by_name(name, 9, n)
+    eng = Engine(params, st, seed=3)
+    eng.build_neighbors()
+    eng.build_neighbors()
+    want = [t.clone() for t in (eng.nbr, eng.cnt, eng.dmax)]
+    i = torch.arange(n, device=eng.dmax.device)
+    keep = {"one in 50": i % 50 == 7, "blocks 1 to 15 of 16": (i // 256) % 16 != 0, "block 0": i < 256}[kept]
+    eng.dmax.mul_(keep)
+    eng.build_neighbors()
+    for a, b in zip((eng.nbr, eng.cnt, eng.dmax), want):
+        assert torch.equal(a, b)
+    assert eng.status() & 0x21 == 0
