@@ -7,11 +7,11 @@
 #include <stdint.h>
 
 #include "../../include/gd.h"
+#include "gd_share.hpp"
 
 namespace gd {
 
 constexpr int kWave = 64;
-constexpr int kXcd = 8;             // accelerator dies, each with its own L2
 constexpr int kNBin = 128;          // controller bins: ilogb(m) in [-64, 63]
 constexpr int kBinOff = 64;
 constexpr int64_t kTicks = int64_t(1) << 30;  // ticks per collision step
@@ -157,11 +157,6 @@ __host__ inline Layout make_layout(int64_t n, int32_t k)
 // provided the grid holds exactly `nitems` wavefronts and the counters start
 // at zero.  No LDS, no barrier.
 enum { kQueueKnn = 0 };
-
-__device__ inline int32_t xcd_range_lo(int x, int32_t nitems)
-{
-    return (nitems / kXcd) * x + (x < nitems % kXcd ? x : nitems % kXcd);
-}
 
 __device__ inline int32_t xcd_take(int32_t* q, int32_t nitems)
 {

@@ -443,15 +443,12 @@ struct KnnWave {
         __shared__ WaveLds<NL> L;
         const int lane = threadIdx.x;
         if (W.list) {
-            // each die's workgroups take a contiguous range of the list, or,
-            // with no previous distances, of all queries (the tile search
-            // handed them back in 60 us and less in order: a first search of
-            // 300,007 took 806 us, so 728)
+            // the list, or, with no previous distances, all queries (the tile
+            // search handed them back in 60 us and less in order: a first
+            // search of 300,007 took 806 us, so 728)
             const bool all = !W.A.h->knn_hints;
-            const int32_t nl = all ? int32_t(W.A.n) : *W.count;
-            const int x = int(B.id % kXcd);
-            const int32_t hi = xcd_range_lo(x + 1, nl), step = int32_t((B.n - x + kXcd - 1) / kXcd);
-            for (int32_t t = xcd_range_lo(x, nl) + int32_t(B.id / kXcd); t < hi; t += step)
+            const ListShare s = list_share(B.id, B.n, all ? int32_t(W.A.n) : *W.count);
+            for (int32_t t = s.first; t < s.end; t += s.step)
                 knn_wave_query<PER, NL>(W.A, all ? t : W.list[t], L, lane);
         } else {
             const int64_t q = B.id;
