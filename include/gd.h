@@ -350,7 +350,9 @@ int32_t gd_transport_dt(const gd_problem* p, const gd_particles* st, const gd_ne
  *   knn_tile      1: the search the library picks by the runs' total size
  *                 (k <= 33: shared candidate tiles or a wavefront per query),
  *                 0: the per-lane search for every query;
- *   fallback_div  wavefronts of the tile search's fallback pass: n / fallback_div per run;
+ *   fallback_div  wavefronts of the pass over the queries the tiles hand back (all of them in a
+ *                 first search): n / fallback_div per run, or the run's share of 65536 when that
+ *                 is more;
  *   event_div     accepted, without effect (the sampling has one pass);
  *   red_div       workgroups of each bin sum: n / red_div per run (<= 256);
  *   heavy_blocks  workgroups (4 wavefronts each) of the pass over the listed particles.

@@ -1153,7 +1153,13 @@ void many_knn(ManyBuilder& B, const std::vector<ManyRun>& R)
                     tt[r] = TileArgs{S[r].A, fb, &hw->knn_fb_n};
                     wt[r] = WaveArgs{S[r].A, fb, &hw->knn_fb_n};
                     nb[r] = mine[r] ? cdiv(R[r].p.n, kWave) : 0;
-                    fnb[r] = mine[r] ? std::max<int64_t>(1, cdiv(R[r].p.n, B.tune.fallback_div)) : 0;
+                    // in a first search these take every query, so the run has
+                    // at least its share of the one-run form's workgroups (three
+                    // disks of 100,003: 2.82 ms with n / 256 and 9.12 with
+                    // n / 1024, 0.94 so; later intervals 0.64 either way)
+                    const int64_t rn = R[r].p.n;
+                    const int64_t share = std::min(rn, cdiv(rn * kFallbackBlocks, total));
+                    fnb[r] = mine[r] ? std::max(share, cdiv(rn, B.tune.fallback_div)) : 0;
                 }
                 many_add_tile(B, tt, nb, per);
                 many_add_wave(B, wt, fnb, per);
