@@ -199,8 +199,8 @@ int32_t gd_build_neighbors(const gd_problem* p, const gd_particles* in, gd_parti
  * lam_pair [n*k] and controller moments a_i, b_i into ab [2n] (a then b).  Then
  * bins of ilogb(m), merged to >= nbin_min particles, A_b, B_b, dt_req and the
  * dyadic executed interval are written into *iv on the device.  The workspace
- * keeps a packed copy of the snapshot (m, grain size, N) for the sampling
- * call that follows. */
+ * keeps a copy of the snapshot (m, grain size, N; m alone for the dimensionless
+ * kernels) for the sampling call that follows. */
 int32_t gd_collision_rates(const gd_problem* p, const gd_particles* st, const gd_neighbors* nb,
                            gd_interval* iv, double* lam_i, double* lam_pair, double* ab,
                            void* ws, size_t ws_bytes, void* stream);

@@ -29,7 +29,7 @@ struct McArgs {
     const double* y;
     const double* z;
     const double4* snap;  // packed (m, s, N, 1/m) of the frozen neighbourhood
-    const double* m_all;  // when set: the frozen masses in the records' place (dimensionless kernels)
+    const double* m_all;  // dimensionless kernels: its masses, in the records' place
     const double* lam_i;
     const gd_interval* iv;
     double* m_out;
@@ -727,6 +727,13 @@ void launch_interval_init(gd_interval* iv, double dt_coll, hipStream_t st)
     hipLaunchKernelGGL(k_interval_init, dim3(1), dim3(64), 0, st, iv, dt_coll);
 }
 
+// the snapshot that the rates pass (or a snapshot launch) left
+static void set_snapshot(McArgs& A, const gd_problem* p, const double4* snap)
+{
+    A.snap = snap;
+    A.m_all = p->kernel == GD_KERNEL_PHYSICAL ? nullptr : reinterpret_cast<const double*>(snap);
+}
+
 static McArgs mc_args(const gd_problem* p, const gd_particles* s, const gd_neighbors* nb, gd_interval* iv,
                       const double* lam_i, uint64_t seed, uint32_t interval, bool interval_on_device,
                       int32_t* n_events, int32_t* log, int32_t log_cap, void* ws, const Layout& L)
@@ -742,7 +749,7 @@ static McArgs mc_args(const gd_problem* p, const gd_particles* s, const gd_neigh
     A.x = s->x;
     A.y = s->y;
     A.z = s->z;
-    A.snap = at<double4>(ws, L.snap);
+    set_snapshot(A, p, at<double4>(ws, L.snap));
     A.lam_i = lam_i;
     A.iv = iv;
     A.m_out = s->m[s->cur ^ 1];
@@ -791,7 +798,6 @@ int launch_sample(const gd_problem* p, const gd_particles* s, const gd_neighbors
                   int32_t log_cap, void* ws, const Layout& L, hipStream_t st, void* table, int32_t slot)
 {
     McArgs A = mc_args(p, s, nb, iv, lam_i, seed, interval, interval_on_device, n_events, log, log_cap, ws, L);
-    if (p->kernel != GD_KERNEL_PHYSICAL) A.m_all = A.m;  // (as the rates pass)
     prof_mark(GD_PROF_MC, 0, st);
     // (the list's counts are cleared by the plan and by every audit; a run of
     // the table form may sample again before its audit)
@@ -883,8 +889,7 @@ void many_sample(ManyBuilder& B, const std::vector<ManyRun>& R)
     for (size_t r = 0; r < nr; ++r) {
         const ManyRun& x = R[r];
         ma[r] = mc_args(&x.p, &x.out, &x.nb, x.iv, x.lam_i, x.seed, 0u, true, x.n_events, nullptr, 0, x.ws, x.L);
-        if (x.snap) ma[r].snap = x.snap;
-        else if (x.p.kernel != GD_KERNEL_PHYSICAL) ma[r].m_all = ma[r].m;
+        if (x.snap) set_snapshot(ma[r], &x.p, x.snap);
         if (x.n_all >= 0) ma[r].n_all = x.n_all;
         ma[r].interval_at = x.interval_at;
         ma[r].active = B.active ? B.active + r : nullptr;

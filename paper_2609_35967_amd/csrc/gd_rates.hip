@@ -1,8 +1,9 @@
 // gd_rates.hip -- rates over the frozen neighbourhood and the interval plan
 // (Sect. 2.5.1-2.5.3).
 //
-//  k_snapshot    derived snapshot of every particle: diameter s_j and grain
-//                count N_j = M_j/m_j (the frozen properties neighbours read)
+//  k_snapshot    snapshot of every particle, the frozen properties neighbours
+//                read: mass, diameter s_j, grain count N_j = M_j/m_j, 1/m_j (the
+//                dimensionless kernels': the mass, copied by the rates pass)
 //  k_rates       one lane per particle: lambda*_ij over its slots in slot order,
 //                lambda*_i, controller moments a_i = sum rate <J>, b_i = sum rate <J^2>
 //  k_reduce      per-block sums over ilogb(m) bins in double-double, grouped per
@@ -18,8 +19,10 @@
 
 namespace gd {
 
-// packed snapshot of every particle: (m_j, s_j, N_j = M_j / m_j, 1 / m_j),
-// one 32-byte record per neighbour gather
+// The snapshot of every particle.  Physical kernel: a packed record (m_j, s_j,
+// N_j = M_j / m_j, 1 / m_j), one 32-byte gather per neighbour.  The
+// dimensionless kernels read nothing of a neighbour but its mass, so there the
+// snapshot is the masses alone, 8 bytes each, in the records' place.
 struct SnapArgs {
     DevProblem P;
     const double* m;
@@ -36,8 +39,10 @@ struct Snapshot {
         const int64_t i = B.id * int64_t(blockDim.x) + threadIdx.x;
         if (i >= A.n) return;
         const double mi = A.m[i];
-        const bool phys = A.P.kernel == GD_KERNEL_PHYSICAL;
-        A.snap[i] = make_double4(mi, phys ? grain_size(A.P, mi) : 0.0, phys ? A.M[i] / mi : 0.0, 1.0 / mi);
+        if (A.P.kernel == GD_KERNEL_PHYSICAL)
+            A.snap[i] = make_double4(mi, grain_size(A.P, mi), A.M[i] / mi, 1.0 / mi);
+        else
+            reinterpret_cast<double*>(A.snap)[i] = mi;
     }
 };
 
@@ -63,9 +68,10 @@ struct RatesArgs {
     double* b;
     void* ws;
     int64_t n_all;  // length of the snapshot: neighbour indices lie in [0, n_all)
-    // when set: the frozen masses themselves, in the records' place (the
-    // dimensionless kernels read nothing else of a neighbour)
+    // dimensionless kernels: the frozen masses, and (when set) the snapshot
+    // that the pass makes of them for the calls that follow
     const double* m_all;
+    double* m_copy;
 };
 
 __device__ inline double4 neighbour_record(const double4* snap, const double* m_all, int j)
@@ -182,6 +188,7 @@ __device__ __forceinline__ void Rates<LANES>::body(const Args& A, Blk B)
         }
     }
     if (sub != 0) return;
+    if (A.m_copy) A.m_copy[i] = A.m[i];
     if (A.lam_pair)
         for (int s = (c > 1 ? c : 0); s < k; ++s) A.lam_pair[i * k + s] = 0.0;
     A.lam[i] = lam;
@@ -263,6 +270,7 @@ __device__ __forceinline__ void RatesF32<LANES>::body(const Args& A, Blk B)
         }
     }
     if (sub != 0) return;
+    if (A.m_copy) A.m_copy[i] = A.m[i];
     if (A.lam_pair)
         for (int s = (c > 1 ? c : 0); s < k; ++s) A.lam_pair[i * k + s] = 0.0;
     A.lam[i] = lam;
@@ -823,12 +831,14 @@ int launch_rates(const gd_problem* p, const gd_particles* s, const gd_neighbors*
     const double* m = s->m[s->cur];
     double4* snap = at<double4>(ws, L.snap);
     prof_mark(GD_PROF_RATES, 0, st);
-    // (the dimensionless kernels need no records: a launch less, and 8 bytes
-    // instead of 32 per neighbour)
+    // (the dimensionless kernels read the masses themselves and copy them as
+    // they go: 4096 particles take 40.3 us an interval with a snapshot launch
+    // before the rates, 37.8 without)
     const bool records = p->kernel == GD_KERNEL_PHYSICAL;
     if (records) hipLaunchKernelGGL(k_snapshot, dim3(g), dim3(256), 0, st, SnapArgs{P, m, s->M, n, snap});
     RatesArgs A{};
     A.m_all = records ? nullptr : m;
+    A.m_copy = records ? nullptr : reinterpret_cast<double*>(snap);
     A.P = P;
     A.nbr = nb->nbr;
     A.cnt = nb->cnt;
@@ -902,6 +912,7 @@ int launch_rates_group(const gd_problem* p, const gd_particles* s, const gd_neig
     A.z = s->z + lo;
     A.snap = snap;
     A.snap_own = snap + lo;
+    A.m_all = p->kernel == GD_KERNEL_PHYSICAL ? nullptr : reinterpret_cast<const double*>(snap);
     A.lam = lam_i + lo;
     A.lam_pair = nullptr;
     A.a = at<double>(ws, L.a) + lo;
@@ -956,8 +967,10 @@ void many_rates(ManyBuilder& B, const std::vector<ManyRun>& R, bool own_snapshot
         A.b = at<double>(x.ws, x.L.b);
         A.ws = x.ws;
         A.n_all = x.n_all >= 0 ? x.n_all : n;
-        const bool records = x.snap || p->kernel == GD_KERNEL_PHYSICAL;
-        A.m_all = records ? nullptr : m;
+        const bool records = p->kernel == GD_KERNEL_PHYSICAL;
+        double* masses = reinterpret_cast<double*>(snap);
+        A.m_all = records ? nullptr : (x.snap ? masses : m);
+        A.m_copy = records || x.snap ? nullptr : masses;
         nb[r] = records ? cdiv(n, 256) : 0;
         f64[r] = p->rates_fp32 ? 0 : cdiv(n * lanes, 256);
         f32[r] = p->rates_fp32 ? cdiv(n * lanes, 256) : 0;
