@@ -434,7 +434,9 @@ __device__ inline void put_device(uint64_t* p, uint64_t v)
     __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-__device__ inline void done_stores() { __builtin_amdgcn_s_waitcnt(0); }
+// (the memory clobber keeps the compiler's order: stores, wait, then what
+// follows; the instruction alone says nothing to it about memory)
+__device__ inline void done_stores() { asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory"); }
 
 // true in the last of `blocks` blocks to count itself (the counter wraps to
 // 0 there); by one thread, after the block's barrier and before another
