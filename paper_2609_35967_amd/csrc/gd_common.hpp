@@ -45,6 +45,16 @@ struct FBox {
     float hi[3];
 };
 
+// Sampling's lists.  Each form that samples right after its screen finds the
+// counts at 0 (the plan and the form's own audit clear them); the deferred
+// call of the table form has counts of its own, cleared by itself, so that a
+// list that no audit followed is never added to.
+struct McCounts {
+    int32_t n, early_n;  // particles with events, from the list's start and from its end
+    int32_t long_n;      // particles with very many
+    int32_t next;        // next chunk of them to take
+};
+
 // Device-resident header at the start of the workspace.
 struct alignas(256) WsHeader {
     int32_t status;
@@ -61,9 +71,8 @@ struct alignas(256) WsHeader {
     int32_t knn_fb_n;            // neighbour search: queries the tile search handed back
     int32_t knn_hints;           // 1: previous distances were found (see Permute), the tile search has a start
     uint32_t red_done;           // controller sums: blocks done (wraps to 0 at the last)
-    int32_t mc_n, mc_early_n;    // sampling: particles with events, from the list's start and from its end
-    int32_t mc_long_n;           // sampling: particles with very many
-    int32_t mc_next;             // sampling: next chunk of them to take
+    McCounts mc;                 // of gd_sample_collisions, the group and the many-run calls: 0 between calls
+    McCounts mc_table;           // of the table form, whose list outlives the call that makes it
 };
 
 // Workspace layout (byte offsets), identical on host and device.

@@ -734,6 +734,14 @@ static void set_snapshot(McArgs& A, const gd_problem* p, const double4* snap)
     A.m_all = p->kernel == GD_KERNEL_PHYSICAL ? nullptr : reinterpret_cast<const double*>(snap);
 }
 
+static void set_counts(McArgs& A, McCounts* c)
+{
+    A.list_n = &c->n;
+    A.early_n = &c->early_n;
+    A.long_n = &c->long_n;
+    A.next = &c->next;
+}
+
 static McArgs mc_args(const gd_problem* p, const gd_particles* s, const gd_neighbors* nb, gd_interval* iv,
                       const double* lam_i, uint64_t seed, uint32_t interval, bool interval_on_device,
                       int32_t* n_events, int32_t* log, int32_t log_cap, void* ws, const Layout& L)
@@ -763,10 +771,7 @@ static McArgs mc_args(const gd_problem* p, const gd_particles* s, const gd_neigh
     A.ev_counter = reinterpret_cast<unsigned long long*>(&h->scratch[0]);
     A.list = at<int32_t>(ws, L.mclist);
     A.long_list = at<int32_t>(ws, L.mclong);
-    A.list_n = &h->mc_n;
-    A.early_n = &h->mc_early_n;
-    A.long_n = &h->mc_long_n;
-    A.next = &h->mc_next;
+    set_counts(A, &h->mc);
     A.screen_rounds = screen_rounds(p->n);
     A.n_all = p->n;
     return A;
@@ -799,9 +804,11 @@ int launch_sample(const gd_problem* p, const gd_particles* s, const gd_neighbors
 {
     McArgs A = mc_args(p, s, nb, iv, lam_i, seed, interval, interval_on_device, n_events, log, log_cap, ws, L);
     prof_mark(GD_PROF_MC, 0, st);
-    // (the list's counts are cleared by the plan and by every audit; a run of
-    // the table form may sample again before its audit)
-    if (table) launch_fill_i32(A.list_n, 4, 0, st);
+    if (table) {
+        McCounts* c = &at<WsHeader>(ws, L.hdr)->mc_table;
+        set_counts(A, c);
+        launch_fill_i32(&c->n, sizeof(McCounts) / 4, 0, st);
+    }
     if (p->n > 0) launch_screen(A, st);
     if (table) {
         // the list is left to the launch over the whole table

@@ -772,12 +772,7 @@ __device__ __forceinline__ void Reduce<MODE>::body(const Args& A, Blk B)
     if (mode == 0) plan_rule(A, row, s_m[0], s_m[1], lane, s_first, s_last);
     else audit_rule(A, row, s_m[0], s_m[1], lane, s_first, s_last);
     // the coming sampling's list of particles with events starts empty
-    if (lane == 0) {
-        h->mc_n = 0;
-        h->mc_early_n = 0;
-        h->mc_long_n = 0;
-        h->mc_next = 0;
-    }
+    if (lane == 0) h->mc = McCounts{0, 0, 0, 0};
 }
 
 static ReduceArgs reduce_args(const gd_problem* p, const double* msnap, const double* M, const double* va,
