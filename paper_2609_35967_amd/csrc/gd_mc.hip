@@ -77,6 +77,7 @@ constexpr double kEarlyEvents = 16.0;
 // warm 1M disk, whose chains are shorter, 3.33 ms with either and 3.28 with
 // none (the second loop costs the first a few spilled registers).
 constexpr double kLongEvents = 1024.0;
+
 constexpr int kChunk = 8;
 
 // Sampling runs in two passes.  The screen (one lane per particle, few
@@ -562,20 +563,23 @@ __device__ inline int run_one(const McArgs& A, int32_t i, int lane)
 }
 
 // Chunks of a run's lists: first the long chains, one each; then the list's
-// far end, two particles a chunk (they start at once, spread over the
-// wavefronts), then the rest, up to kChunk a chunk while that leaves every
-// wavefront several.
+// far end, a particle per group of lanes (they start at once, spread over the
+// wavefronts; two particles one after the other made the sampling of 20,000
+// warm grains at k = 256 3.32 ms, 2.93 so), then the rest, up to kChunk a
+// chunk while that leaves every wavefront several.
 struct Chunks {
     int32_t nl, n0, n1, c, k0, k;  // particles of each part, chunk size, chunks before the last part, all
 
+    template <int KP2>
     __device__ void set(const McArgs& A, int32_t waves)
     {
+        constexpr int G = KP2 <= 32 ? 2 : 1;
         nl = *A.long_n;
         n0 = *A.early_n;
         n1 = *A.list_n;
         c = n1 / (4 * waves);
         c = c < 2 ? 2 : (c > kChunk ? kChunk : c);
-        k0 = nl + (n0 + 1) / 2;
+        k0 = nl + (n0 + G - 1) / G;
         k = k0 + (n1 + c - 1) / c;
     }
     template <int KP2, bool F32>
@@ -588,8 +592,9 @@ struct Chunks {
         if (x < nl) {
             ev = run_one<KP2, F32>(A, __builtin_amdgcn_readfirstlane(A.long_list[x]), lane);
         } else {
+            constexpr int G = KP2 <= 32 ? 2 : 1;
             const bool far = x < k0;
-            const int32_t lo = far ? 2 * (x - nl) : (x - k0) * c, hi = far ? lo + 2 : lo + c, n = far ? n0 : n1;
+            const int32_t lo = far ? G * (x - nl) : (x - k0) * c, hi = far ? lo + G : lo + c, n = far ? n0 : n1;
             ev = run_chunk<KP2, F32>(A, lo, hi < n ? hi : n, far, lane);
         }
         if (x < k0) __builtin_amdgcn_s_setprio(0);
@@ -603,7 +608,7 @@ __global__ __launch_bounds__(256, KP2 <= 32 ? 4 : 1) void k_mc(McArgs A)
     const int lane = threadIdx.x & 63;
     const int32_t nw = int32_t(gridDim.x * (blockDim.x / kWave));
     Chunks C;
-    C.set(A, nw);
+    C.set<KP2>(A, nw);
     // wavefront w takes chunk w first, then chunks nw, nw + 1, ... from the
     // counter (which is left alone when there are no more than nw); one add of
     // the events per workgroup: adds to one address wait 12 ns each for the
@@ -653,7 +658,7 @@ __global__ __launch_bounds__(256) void k_mc_batch(char* table, int32_t nbox)
     for (int b = t; b < nbox; b += blockDim.x) {
         const bool on = !T[b].active || *T[b].active;
         Chunks C;
-        C.set(T[b], nw);
+        C.template set<KP2>(T[b], nw);
         s_pre[0][b] = on ? C.k0 : 0;
         s_pre[1][b] = on ? C.k - C.k0 : 0;
     }
@@ -694,7 +699,7 @@ __global__ __launch_bounds__(256) void k_mc_batch(char* table, int32_t nbox)
             if (lane == 0) set_status(A.ws, GD_DEV_INTERNAL);
         } else {
             Chunks C;
-            C.set(A, nw);
+            C.set<KP2>(A, nw);
             const int ev = C.run<KP2, F32>(A, __builtin_amdgcn_readfirstlane(gg - pre[lo] + (first ? 0 : C.k0)), lane);
             if (lane == 0 && ev) atomicAdd(A.ev_counter, (unsigned long long)ev);
         }
