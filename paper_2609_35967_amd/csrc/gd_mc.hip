@@ -566,18 +566,23 @@ __device__ inline int run_one(const McArgs& A, int32_t i, int lane)
 // far end, a particle per group of lanes (they start at once, spread over the
 // wavefronts; two particles one after the other made the sampling of 20,000
 // warm grains at k = 256 3.32 ms, 2.93 so), then the rest, up to kChunk a
-// chunk while that leaves every wavefront several.
+// chunk while that leaves every wavefront kPer.  A chunk costs an add to the
+// counter, 10 ns after the one before it: of a column of 65,536, 43 thousand
+// particles with a few events each took 184 us with kPer = 4, 143 with 2 and
+// 97 with 1, but 50,021 warm grains, with longer chains, 1.40, 1.41 and 1.43
+// ms; over many runs their balance is worth more (64 local boxes 94.5 ms with
+// 4, 96.5 with 1).
 struct Chunks {
     int32_t nl, n0, n1, c, k0, k;  // particles of each part, chunk size, chunks before the last part, all
 
-    template <int KP2>
+    template <int KP2, int kPer>
     __device__ void set(const McArgs& A, int32_t waves)
     {
         constexpr int G = KP2 <= 32 ? 2 : 1;
         nl = *A.long_n;
         n0 = *A.early_n;
         n1 = *A.list_n;
-        c = n1 / (4 * waves);
+        c = n1 / (kPer * waves);
         c = c < 2 ? 2 : (c > kChunk ? kChunk : c);
         k0 = nl + (n0 + G - 1) / G;
         k = k0 + (n1 + c - 1) / c;
@@ -608,7 +613,7 @@ __global__ __launch_bounds__(256, KP2 <= 32 ? 4 : 1) void k_mc(McArgs A)
     const int lane = threadIdx.x & 63;
     const int32_t nw = int32_t(gridDim.x * (blockDim.x / kWave));
     Chunks C;
-    C.set<KP2>(A, nw);
+    C.set<KP2, 2>(A, nw);
     // wavefront w takes chunk w first, then chunks nw, nw + 1, ... from the
     // counter (which is left alone when there are no more than nw); one add of
     // the events per workgroup: adds to one address wait 12 ns each for the
@@ -658,7 +663,7 @@ __global__ __launch_bounds__(256) void k_mc_batch(char* table, int32_t nbox)
     for (int b = t; b < nbox; b += blockDim.x) {
         const bool on = !T[b].active || *T[b].active;
         Chunks C;
-        C.template set<KP2>(T[b], nw);
+        C.set<KP2, 4>(T[b], nw);
         s_pre[0][b] = on ? C.k0 : 0;
         s_pre[1][b] = on ? C.k - C.k0 : 0;
     }
@@ -699,7 +704,7 @@ __global__ __launch_bounds__(256) void k_mc_batch(char* table, int32_t nbox)
             if (lane == 0) set_status(A.ws, GD_DEV_INTERNAL);
         } else {
             Chunks C;
-            C.set<KP2>(A, nw);
+            C.set<KP2, 4>(A, nw);
             const int ev = C.run<KP2, F32>(A, __builtin_amdgcn_readfirstlane(gg - pre[lo] + (first ? 0 : C.k0)), lane);
             if (lane == 0 && ev) atomicAdd(A.ev_counter, (unsigned long long)ev);
         }
