@@ -52,6 +52,7 @@ struct McArgs {
     int32_t* long_n;
     int32_t* next;
     int32_t screen_rounds;  // particles per thread of the screen
+    double long_events;     // expected events of a very long chain
     int64_t n_all;  // length of the snapshot: neighbour indices lie in [0, n_all)
     const int64_t* interval_at;  // when set: the interval index (a spatial group's number in planning order)
     const int32_t* active;       // when set and 0: the run has no interval now (its list is skipped)
@@ -77,6 +78,18 @@ constexpr double kEarlyEvents = 16.0;
 // warm 1M disk, whose chains are shorter, 3.33 ms with either and 3.28 with
 // none (the second loop costs the first a few spilled registers).
 constexpr double kLongEvents = 1024.0;
+
+// A run alone that gives the launch's 4096 wavefronts no more than a few
+// particles waits for its longest chains, and theirs is the shorter loop: all
+// that start first then go there (sampling of 5000 warm grains at k = 32: 600
+// us in pairs, 457 so; of 20,000 at k = 64: 1.70 and 1.63 ms; but of 131,072
+// at k = 64: 1.57 and 1.74).  Above k = 128 the other loop is the shorter one
+// (50,021 at k = 256: 4.72 and 4.97 ms).
+static double long_events(int64_t n, int32_t k)
+{
+    const int64_t top = k <= 32 ? 8192 : (k <= 128 ? 32768 : 0);
+    return n <= top ? kEarlyEvents : kLongEvents;
+}
 
 constexpr int kChunk = 8;
 
@@ -120,7 +133,7 @@ struct McScreen {
                     double u[4];
                     event_uniforms(A.seed, A.id[i], interval, 0u, u);
                     const double x = li * dt_exe;  // expected events
-                    if (!(-log(u[0]) / li > dt_exe)) cls = x >= kLongEvents ? 2 : (x >= kEarlyEvents ? 1 : 0);
+                    if (!(-log(u[0]) / li > dt_exe)) cls = x >= A.long_events ? 2 : (x >= kEarlyEvents ? 1 : 0);
                 }
                 if (cls < 0) {
                     A.m_out[i] = m;
@@ -783,6 +796,7 @@ static McArgs mc_args(const gd_problem* p, const gd_particles* s, const gd_neigh
     A.long_list = at<int32_t>(ws, L.mclong);
     set_counts(A, &h->mc);
     A.screen_rounds = screen_rounds(p->n);
+    A.long_events = kLongEvents;
     A.n_all = p->n;
     return A;
 }
@@ -818,6 +832,8 @@ int launch_sample(const gd_problem* p, const gd_particles* s, const gd_neighbors
         McCounts* c = &at<WsHeader>(ws, L.hdr)->mc_table;
         set_counts(A, c);
         launch_fill_i32(&c->n, sizeof(McCounts) / 4, 0, st);
+    } else {
+        A.long_events = long_events(p->n, p->k);
     }
     if (p->n > 0) launch_screen(A, st);
     if (table) {
@@ -855,6 +871,7 @@ int launch_sample_group(const gd_problem* p, const gd_particles* s, const gd_nei
     A.n_events = n_events ? n_events + lo : nullptr;
     prof_mark(GD_PROF_MC, 0, st);
     A.screen_rounds = screen_rounds(cnt);
+    A.long_events = long_events(cnt, p->k);
     if (cnt > 0) launch_screen(A, st);
     launch_listed(A, p, st);
     prof_mark(GD_PROF_MC, 1, st);
