@@ -15,6 +15,7 @@
 // allocation-free form), then every cached entry is relabelled by one read
 // of the table.  The one other that pi sends onto the row's own particle
 // takes pi of that particle instead, so a row never holds itself twice.
+#include <algorithm>
 #include <mutex>
 
 #include "gd_common.hpp"
@@ -39,8 +40,12 @@ __device__ inline uint32_t feistel4(uint32_t x, int h, uint32_t mask, uint32_t k
 // pi once per active slot: table[j] = pi(j), j < N.  A walk takes up to
 // 4^h / N applications on average (2.1 at N = 500,009) but several times that
 // in the slowest of 64 lanes, so a lane whose walk has ended goes on with the
-// next of its slots (kWalks of them in large sets) instead of waiting.
-constexpr int kWalks = 8;
+// next of its slots (up to kWalks of them) instead of waiting.  Up to
+// kTableBlocks workgroups have a slot a thread: fewer leave SIMDs idle
+// (relabelling of 131,073 particles, k = 32: 37.9 us with 8 slots a thread,
+// 27.5 with 256 workgroups at least, 25.8 with 512, 25.9 with 1024; of 350,000
+// 76.0, 67.9, 62.3, 66.7).
+constexpr int kWalks = 8, kTableBlocks = 512;
 
 __global__ __launch_bounds__(256) void k_reshuffle_table(int32_t* __restrict__ table,
                                                          const int32_t* __restrict__ n_active, int64_t n,
@@ -107,7 +112,7 @@ static void launch_with_table(const gd_problem* p, const gd_neighbors* nb, uint6
 {
     const int64_t total = p->n * int64_t(p->k);
     if (total <= 0) return;
-    const int64_t tb = cdiv(p->n, 256 * (p->n > 131072 ? kWalks : 1));
+    const int64_t tb = std::max<int64_t>(cdiv(p->n, 256 * kWalks), std::min<int64_t>(kTableBlocks, cdiv(p->n, 256)));
     hipLaunchKernelGGL(k_reshuffle_table, dim3(unsigned(tb)), dim3(256), 0, st, table, nb->n_active, p->n, seed,
                        refresh);
     const dim3 grid(unsigned(cdiv(total, 256 * kRun)));
