@@ -79,16 +79,21 @@ constexpr double kEarlyEvents = 16.0;
 // none (the second loop costs the first a few spilled registers).
 constexpr double kLongEvents = 1024.0;
 
-// A run alone that gives the launch's 4096 wavefronts no more than a few
-// particles waits for its longest chains, and theirs is the shorter loop: all
-// that start first then go there (sampling of 5000 warm grains at k = 32: 600
-// us in pairs, 457 so; of 20,000 at k = 64: 1.70 and 1.63 ms; but of 131,072
-// at k = 64: 1.57 and 1.74).  Above k = 128 the other loop is the shorter one
-// (50,021 at k = 256: 4.72 and 4.97 ms).
+// For a run alone the line lies lower: the longest chain is the end of the
+// pass, and beside another particle its events wait for both (sampling of warm
+// grains, k = 20, with 1024, 256 and 128: 49,153 of them 1317, 995 and 988 us,
+// 160,001 1478, 1110 and 1097, 262,145 2226, 1601 and 1596; a million at k = 32
+// 1.92 ms with each).  In a set that gives the launch's 4096 wavefronts only a
+// few particles each, all that start first are taken so (5000 at k = 32: 457 us
+// with 128, 449 with 16; 20,000 at k = 64: 1.69 and 1.63 ms; but 131,072 at
+// k = 64: 1.55 and 1.74).  Above k = 128 that loop is not the shorter one
+// (50,021 at k = 256: 4.97 ms with 16, 4.61 with 128).
+constexpr double kLongAlone = 128.0;
+
 static double long_events(int64_t n, int32_t k)
 {
     const int64_t top = k <= 32 ? 8192 : (k <= 128 ? 32768 : 0);
-    return n <= top ? kEarlyEvents : kLongEvents;
+    return n <= top ? kEarlyEvents : kLongAlone;
 }
 
 constexpr int kChunk = 8;
