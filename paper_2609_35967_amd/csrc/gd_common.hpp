@@ -70,7 +70,7 @@ struct alignas(256) WsHeader {
     int32_t xq[4][8];            // per-die work queues of the gather-heavy kernels
     int32_t knn_fb_n;            // neighbour search: queries the tile search handed back
     int32_t knn_hints;           // 1: previous distances were found (see Permute), the tile search has a start
-    uint32_t red_done;           // controller sums: blocks done (wraps to 0 at the last)
+    uint32_t red_done;           // bounding box, controller sums: blocks done (wraps to 0 at the last)
     McCounts mc;                 // of gd_sample_collisions, the group and the many-run calls: 0 between calls
     McCounts mc_table;           // of the table form, whose list outlives the call that makes it
 };

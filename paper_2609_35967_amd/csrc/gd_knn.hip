@@ -1021,7 +1021,13 @@ static KnnSetup knn_setup(const gd_problem* p, const gd_neighbors* nb, void* ws,
 // 0.28 ms; a wavefront per query keeps 7 on each SIMD.  Measured intervals at
 // k = 32, tiles against wavefronts: open disks 360 / 311 us at 100,003
 // particles, 432 / 426 at 150,001, 498 / 529 at 200,003; periodic columns
-// 611 / 388 at 131,072, 847 / 678 at 262,144, 1022 / 998 at 400,000.
+// 611 / 388 at 131,072, 847 / 678 at 262,144, 1022 / 998 at 400,000.  One
+// line serves k = 2 .. 33: neighbour builds without motion take, at k = 5, 16
+// and 33, in open disks 207 / 192, 234 / 206 and 271 / 221 us at 131,072, 228
+// / 242, 262 / 261 and 299 / 282 at 160,000, 278 / 342, 319 / 374 and 379 /
+// 410 at 262,144; in periodic columns 517 / 375, 599 / 413 and 598 / 463 at
+// 262,144, 564 / 554, 672 / 614 and 804 / 693 at 400,000, 571 / 690, 714 /
+// 765 and 868 / 865 at 524,288.
 constexpr int64_t kTileOpen = 160000, kTilePeriodic = 400000;
 
 static bool use_tiles(int32_t k, int64_t n, bool per)

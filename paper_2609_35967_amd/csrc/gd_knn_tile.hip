@@ -25,10 +25,10 @@
 //   5. the bin holding the (k-1)-th other splits the list into sure entries
 //      and a boundary bin ranked by (d^2, slot); the row is written once, in
 //      slot order;
-//   6. lanes without a usable previous distance, whose radius held fewer than k-1 others, whose list or group
-//      list overflowed, or whose boundary bin is over-full, go to a list that
-//      the wavefront-per-query search then completes.  The result never
-//      depends on which lanes go there.
+//   6. lanes without a usable previous distance, whose radius held fewer than
+//      k-1 others, whose list or group list overflowed, or whose boundary bin
+//      is over-full, go to a list that the wavefront-per-query search then
+//      completes.  The result never depends on which lanes go there.
 // d^2 is (dx*dx + dy*dy) + dz*dz with every operation rounded on its own, and
 // every bin function is monotone in d^2, so each row is the k-1 smallest
 // (d^2, slot) exactly.

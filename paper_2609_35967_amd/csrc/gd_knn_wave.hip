@@ -443,9 +443,9 @@ struct KnnWave {
         __shared__ WaveLds<NL> L;
         const int lane = threadIdx.x;
         if (W.list) {
-            // the list, or, with no previous distances, all queries (the tile
-            // search handed them back in 60 us and less in order: a first
-            // search of 300,007 took 806 us, so 728)
+            // the list, or, with no previous distances, all queries in slot
+            // order (handed back by the tiles they came in any order, after 60
+            // us: a first search of 300,007 took 806 us, so 728)
             const bool all = !W.A.h->knn_hints;
             const ListShare s = list_share(B.id, B.n, all ? int32_t(W.A.n) : *W.count);
             for (int32_t t = s.first; t < s.end; t += s.step)
